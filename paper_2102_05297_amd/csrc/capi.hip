@@ -58,6 +58,30 @@ constexpr int kDefaultBlockLog2 = 12;
 
 } // namespace
 
+// ------------------------------------------------------------------ draws
+namespace {
+
+// A draw result as the host uses it (kNoPick without a pick).
+struct Pick {
+  uint64_t valid, raw, total;
+};
+
+// Takes *res when it is complete under sequence number seq.
+bool read_pick(const DrawResult *res, uint64_t seq, Pick *p) {
+  uint32_t part[4];
+  for (int i = 0; i < 4; ++i) {
+    const uint64_t w = __atomic_load_n(&res->word[i], __ATOMIC_ACQUIRE);
+    if ((uint32_t)w != (uint32_t)seq) return false;
+    part[i] = (uint32_t)(w >> 32);
+  }
+  p->valid = part[0] == kNoIndex ? kNoPick : part[0];
+  p->raw = part[1] == kNoIndex ? kNoPick : part[1];
+  p->total = (uint64_t)part[3] << 32 | part[2];
+  return true;
+}
+
+} // namespace
+
 // ------------------------------------------------------------------ handles
 struct cgs_space_s {
   // 1 for the caller's handle + 1 per live model or session; the space is
@@ -345,7 +369,8 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
   if (e == hipSuccess)
     e = hipMemcpyAsync(&n_valid, d_total, sizeof(uint64_t), hipMemcpyDeviceToHost, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
-  if (e == hipSuccess) e = dalloc(&sp->d_idx, n_valid);
+  // whole runs of draw weights (draws load the raw indices with the scores)
+  if (e == hipSuccess) e = dalloc(&sp->d_idx, (n_valid + 63) & ~(uint64_t)63);
   if (e == hipSuccess && n_valid > 0)
     e = launch_enumeration(sp->d_desc, (uint32_t)n_raw, sp->d_mask, d_tile_count, d_tile_off,
                            d_total, sp->d_idx, sp->d_rank, 1, sp->stream);
@@ -1069,7 +1094,7 @@ extern "C" void cgs_default_tuning_opts(cgs_tuning_opts *out) {
 namespace {
 
 hipError_t launch_pending(cgs_session s, bool do_draw, uint64_t u64);
-cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq);
+cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq, Pick *pick);
 
 // The next n draws of a full step (1 <= n <= kMaxDrawSeries + 1) with
 // uniforms u64[0..n): the first as cgs_sample_next makes it (launching a
@@ -1102,11 +1127,9 @@ cgs_status draw_series(cgs_session s, int n, const uint64_t *u64, uint64_t *vali
   }
   for (int i = 0; i < n; ++i) {
     const DrawResult *slot = i == 0 ? s->h_res : s->h_ring + (i - 1);
-    const cgs_status ws = wait_draw(s, slot, seq_first + (uint64_t)i);
+    Pick r;
+    const cgs_status ws = wait_draw(s, slot, seq_first + (uint64_t)i, &r);
     if (ws != CGS_OK) return ws;
-    DrawResult r;
-    std::memcpy(&r, const_cast<const DrawResult *>(static_cast<volatile const DrawResult *>(slot)),
-                sizeof r);
     s->last_total = r.total;
     if (r.total == 0) return CGS_OK;
     if (r.valid == kNoPick)
@@ -1824,18 +1847,18 @@ hipError_t mark_span(cgs_session s, const TimedSpan *sp, int k) {
 // pinned memory before its kernel ends, so the host polls that instead of
 // sleeping on the stream; past kSpinLimit it waits for the stream, and a
 // draw that still has not published is an error.
-cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq) {
+cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq, Pick *pick) {
   constexpr auto kSpinLimit = std::chrono::milliseconds(5);
   const auto t0 = std::chrono::steady_clock::now();
   for (uint32_t it = 0;; ++it) {
-    if (__atomic_load_n(&res->seq, __ATOMIC_ACQUIRE) == seq) return CGS_OK;
+    if (read_pick(res, seq, pick)) return CGS_OK;
     if ((it & 1023u) == 1023u && std::chrono::steady_clock::now() - t0 > kSpinLimit) break;
 #if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
     __builtin_ia32_pause();
 #endif
   }
   HIP_TRY(hipStreamSynchronize(s->space->stream));
-  if (__atomic_load_n(&res->seq, __ATOMIC_ACQUIRE) != seq)
+  if (!read_pick(res, seq, pick))
     return fail(CGS_EDEVICE, "draw %llu did not publish its result", (unsigned long long)seq);
   return CGS_OK;
 }
@@ -2232,12 +2255,10 @@ extern "C" cgs_status cgs_search_run(cgs_session s, cgs_model m, int n_steps,
       ++launched;
     }
     const DrawResult *slot = s->h_ring + k % kResultRing;
-    const cgs_status ws = wait_draw(s, slot, seq0 + (uint64_t)k + 1);
+    Pick r;
+    const cgs_status ws = wait_draw(s, slot, seq0 + (uint64_t)k + 1, &r);
     if (ws != CGS_OK) return finish(ws);
     const auto t = std::chrono::steady_clock::now();
-    DrawResult r;
-    std::memcpy(&r, const_cast<const DrawResult *>(static_cast<volatile const DrawResult *>(slot)),
-                sizeof r);
     s->last_total = r.total;
     s->n_active = acts[k].n;
     if (r.total == 0) return finish(fail(CGS_EEMPTY, "no unexplored valid configuration is left"));
@@ -2560,11 +2581,9 @@ extern "C" cgs_status cgs_sample_next(cgs_session s, uint64_t u64, uint64_t *raw
                           ++s->seq, sp->stream));
     if (span) HIP_TRY(mark_span(s, span, 0));
   }
-  const cgs_status ws = wait_draw(s, s->h_res, s->seq);
+  Pick r;
+  const cgs_status ws = wait_draw(s, s->h_res, s->seq, &r);
   if (ws != CGS_OK) return ws;
-  DrawResult r;
-  std::memcpy(&r, const_cast<const DrawResult *>(static_cast<volatile DrawResult *>(s->h_res)),
-              sizeof r);
   s->last_total = r.total;
   if (r.total == 0) return fail(CGS_EEMPTY, "no unexplored valid configuration is left");
   if (r.valid == kNoPick)
@@ -2954,9 +2973,10 @@ extern "C" cgs_status cgs_batch_step(cgs_batch b, const uint64_t *profile_raw, c
     s->ran_in_batch = true;
     s->batch_ms = b->last_ms;
     s->n_active = b->h_step[i].n_act;
-    DrawResult r;
-    std::memcpy(&r, const_cast<const DrawResult *>(static_cast<volatile DrawResult *>(b->h_res + i)),
-                sizeof r);
+    Pick r;
+    if (!read_pick(b->h_res + i, b->seq, &r))
+      return fail(CGS_EDEVICE, "session %d: draw %llu did not publish its result", i,
+                  (unsigned long long)b->seq);
     s->last_total = r.total;
     int32_t status = CGS_OK;
     if (r.total == 0) status = CGS_EEMPTY;
@@ -3138,9 +3158,10 @@ extern "C" cgs_status cgs_batch_draw(cgs_batch b, const uint64_t *u64, uint64_t 
   ++b->seq;
   HIP_TRY(hipStreamSynchronize(b->stream));
   for (int i = 0; i < b->n; ++i) {
-    DrawResult r;
-    std::memcpy(&r, const_cast<const DrawResult *>(static_cast<volatile DrawResult *>(b->h_res + i)),
-                sizeof r);
+    Pick r;
+    if (!read_pick(b->h_res + i, b->seq, &r))
+      return fail(CGS_EDEVICE, "session %d: draw %llu did not publish its result", i,
+                  (unsigned long long)b->seq);
     b->sess[i]->last_total = r.total;
     int32_t status = CGS_OK;
     if (r.total == 0) status = CGS_EEMPTY;
@@ -3356,9 +3377,11 @@ cgs_status sample_resident(cgs_space sp, uint32_t *d_q, uint64_t n, int lg, uint
     e = launch_array_draw(d_q, (uint32_t)n, lg, d_bsum, n_blocks, u64[i], sp->d_res, sp->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
     if (e == hipSuccess) {
-      if (sp->h_res->total == 0) break;
-      if (sp->h_res->valid == kNoPick) return fail(CGS_EDEVICE, "draw found no index although Q > 0");
-      picks[i] = (int64_t)sp->h_res->valid;
+      Pick p;
+      if (!read_pick(sp->h_res, 1, &p)) return fail(CGS_EDEVICE, "draw did not publish its result");
+      if (p.total == 0) break;
+      if (p.valid == kNoPick) return fail(CGS_EDEVICE, "draw found no index although Q > 0");
+      picks[i] = (int64_t)p.valid;
     }
   }
   if (e != hipSuccess) return fail(CGS_EDEVICE, "sampler: %s", hipGetErrorString(e));
@@ -3385,7 +3408,7 @@ extern "C" cgs_status cgs_sample_weights(cgs_space sp, const uint32_t *q, uint64
   const uint32_t n_blocks = (uint32_t)((n + (1ull << lg) - 1) >> lg);
   uint32_t *d_q = nullptr;
   uint64_t *d_bsum = nullptr;
-  HIP_TRY(dalloc(&d_q, n));
+  HIP_TRY(dalloc(&d_q, (n + 63) & ~(uint64_t)63)); // whole runs of draw weights
   hipError_t e = dalloc(&d_bsum, n_blocks);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_q, q, n * sizeof(uint32_t), hipMemcpyHostToDevice, sp->stream);

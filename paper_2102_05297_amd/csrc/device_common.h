@@ -174,43 +174,91 @@ __device__ __forceinline__ bool explored_bit(const uint32_t *__restrict__ ex, ui
 }
 
 // ------------------------------------------------------------ wave / block
+// Cross-lane moves of the integer scans and reductions are DPP operand
+// modifiers of the VALU (a few cycles each) rather than ds_bpermute round
+// trips through the LDS crossbar (~60 cycles, two per 64-bit value): a
+// 64-lane 64-bit scan is 6 steps of two moves and one add.  The steps are the
+// four in-row shifts by 1, 2, 4 and 8, then row 0 to row 1 and row 2 to row
+// 3 (row_bcast15 into rows 1 and 3), then the lower half's last lane into
+// rows 2 and 3 (row_bcast31).  A lane without a source gets `none`.
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t v, uint32_t none) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, kCtrl, kRows, 0xf, false);
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_move(uint64_t v, uint64_t none) {
+  const uint32_t lo = dpp_move<kCtrl, kRows>((uint32_t)v, (uint32_t)none);
+  const uint32_t hi = dpp_move<kCtrl, kRows>((uint32_t)(v >> 32), (uint32_t)(none >> 32));
+  return (uint64_t)hi << 32 | lo;
+}
+// Inclusive scan of v under `op` across the wave's 64 lanes (all of them
+// active); lane 63 holds the reduction.
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_scan(T v, T none, Op op) {
+  v = op(v, dpp_move<kDppShr1, 0xf>(v, none));
+  v = op(v, dpp_move<kDppShr2, 0xf>(v, none));
+  v = op(v, dpp_move<kDppShr4, 0xf>(v, none));
+  v = op(v, dpp_move<kDppShr8, 0xf>(v, none));
+  v = op(v, dpp_move<kDppBcast15, 0xa>(v, none));
+  return op(v, dpp_move<kDppBcast31, 0xc>(v, none));
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+__device__ __forceinline__ uint64_t last_lane(uint64_t v) {
+  return (uint64_t)last_lane((uint32_t)(v >> 32)) << 32 | last_lane((uint32_t)v);
+}
+struct AddOp {
+  template <typename T> __device__ T operator()(T a, T b) const { return a + b; }
+};
+
+// Sums, minima and maxima over the wave, in every lane.  The float sum keeps
+// the butterfly order its results are defined by.
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
   return v;
 }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  return last_lane(wave_scan(v, 0u, AddOp{}));
+}
+__device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
+  return last_lane(wave_scan(v, (uint64_t)0, AddOp{}));
+}
 __device__ __forceinline__ uint32_t wave_umin(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-  return v;
+  return last_lane(wave_scan(v, 0xffffffffu, [](uint32_t a, uint32_t b) { return min(a, b); }));
 }
 __device__ __forceinline__ uint32_t wave_umax(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, kWave));
-  return v;
+  return last_lane(wave_scan(v, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }));
 }
 
 // Inclusive scan across a wave.
-__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v, uint32_t lane) {
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint64_t t = __shfl_up(v, o, kWave);
-    if (lane >= (uint32_t)o) v += t;
-  }
-  return v;
+__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) {
+  return wave_scan(v, (uint64_t)0, AddOp{});
+}
+
+// A barrier that orders LDS accesses only: loads and stores of global memory
+// stay in flight across it (__syncthreads waits for all of them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Exclusive scan over the whole block (NT threads, NT % 64 == 0); `total`
 // receives the block sum.  `scratch` holds NT / 64 entries.  Contains
-// barriers: every thread must call it.
-template <int NT>
+// barriers (kLdsOnly: of LDS only): every thread must call it.
+template <int NT, bool kLdsOnly = false>
 __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t *scratch, uint64_t &total) {
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   constexpr int NW = NT / kWave;
-  const uint64_t incl = wave_incl_scan(v, lane);
-  __syncthreads();
+  const uint64_t incl = wave_incl_scan(v);
+  kLdsOnly ? lds_barrier() : __syncthreads();
   if (lane == kWave - 1) scratch[wave] = incl;
-  __syncthreads();
+  kLdsOnly ? lds_barrier() : __syncthreads();
   uint64_t before = 0, all = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {

@@ -54,14 +54,15 @@ struct StepAccSums {
 };
 constexpr int kAccSlots = 64;
 
-// Result of one draw (device memory, copied to pinned host memory).
+// Result of one draw in pinned host memory: 32 bits of it in the upper half
+// of each word (valid index, raw index, low and high half of the total
+// weight Q at this draw; kNoIndex in the first two without a pick) and the
+// low half of the draw's sequence number in the lower.  A word is stored
+// whole, so the result is complete once every word carries the number.
 struct DrawResult {
-  uint64_t valid;  // picked valid index, or ~0 when the total weight is 0
-  uint64_t raw;    // its raw index
-  uint64_t total;  // Q at this draw
-  uint64_t r;      // floor(U * Q / 2^64)
-  uint64_t seq;    // sequence number of the draw, stored last (release)
+  uint64_t word[4];
 };
+constexpr uint32_t kNoIndex = ~0u;
 
 constexpr uint64_t kNoPick = ~0ull;
 constexpr uint32_t kNoProfile = ~0u; // step prologue: no configuration to mark

@@ -31,9 +31,9 @@
 // r = mulhi64(U, Q); recompute that block's q and scan it to l with
 // prefix_l <= r < prefix_l + q_l; mark l explored and subtract q_l from its
 // block sum (Alg. 1 zeroes S_l before the next draw of the iteration).  The
-// result goes to pinned host memory, closed by a sequence number that the
-// host polls.  Every phase issues all of its loads before the first use, so
-// a draw costs about four dependent memory round trips.
+// result goes to pinned host memory in words that carry the draw's sequence
+// number, which the host polls.  Every phase issues all of its loads before
+// the first use, so a draw costs about two dependent memory round trips.
 #include <algorithm>
 #include <type_traits>
 
@@ -45,7 +45,7 @@ namespace {
 
 constexpr int kScoreThreads = 256;
 constexpr int kWeightThreads = 256;
-constexpr int kDrawThreads = 1024;
+constexpr int kDrawThreads = 256;
 constexpr int kRowsInFlight = 8;
 constexpr uint32_t kScoreGrid = 2048; // 8 workgroups of 256 threads per CU
 
@@ -194,11 +194,23 @@ __device__ __forceinline__ void reduce_slot_values(const StepAcc &slot, StepAccS
   }
 }
 
-// Quantised weight of valid index l (0 past the end, for explored
-// configurations and for the profiled one).  The step's s_min / s_max come
-// from its accumulator slots in three stages, so a draw can overlap their
-// load with its first loads: stage_load (every thread), stage_reduce (after
-// the caller's own loads), then a barrier, then stage_read.
+// Sources of quantised weights for a draw.  A thread weighs runs of
+// kRunWeights consecutive positions: load() issues every load of a run (from
+// clamped addresses, so that no branch separates them; their arrays are
+// padded to whole runs), weigh() turns it into weights, 0 for the positions
+// of `out` (bit e: first + e) and past the end.  The step's s_min / s_max
+// come from its accumulator slots in three stages, so a draw can overlap
+// their load with its first loads: stage_load (every thread), stage_reduce
+// (after the caller's own loads), then a barrier, then stage_read.
+constexpr uint32_t kRunWeights = 16;
+
+// Positions first .. first + kRunWeights - 1 at or past n.
+__device__ __forceinline__ uint32_t past_end(uint32_t first, uint32_t n) {
+  return first >= n ? 0xffffu : n - first < kRunWeights ? (0xffffu << (n - first)) & 0xffffu : 0u;
+}
+
+// The scores of a full step; explored configurations and the profiled one
+// weigh 0.
 struct ScoreWeights {
   const float *s;
   uint32_t *explored;
@@ -208,6 +220,11 @@ struct ScoreWeights {
   float gamma, w_min;
   StepNorm nm{};
   StepAcc slot{};
+  struct Run {
+    float4 s[kRunWeights / 4];
+    uint4 raw[kRunWeights / 4];
+    uint32_t mask;
+  };
   __device__ void stage_load() {
     if (threadIdx.x < kWave) slot = acc[threadIdx.x];
   }
@@ -219,213 +236,281 @@ struct ScoreWeights {
     if (l >= n) return 0u;
     return quantized_weight(s[l], explored_bit(explored, l) || l == profile, nm);
   }
-  // Weights of l = first .. first + cnt - 1 (cnt <= K) into q[], 0 beyond;
-  // every load is issued before the first is used.
-  template <int K> __device__ void run(uint32_t first, uint32_t cnt, uint32_t (&q)[K]) const {
-    float sv[K];
-    uint32_t ew[K];
+  __device__ void load(uint32_t first, const uint32_t *idx, Run &r) const {
+    const uint32_t f = first < n ? first : 0u;
+    r.mask = explored[f >> 5];
 #pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const uint32_t l = first + e;
-      const bool in = (uint32_t)e < cnt && l < n;
-      sv[e] = in ? s[l] : 0.0f;
-      ew[e] = in ? explored[l >> 5] : 0xffffffffu;
-    }
-#pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const uint32_t l = first + e;
-      const bool ex = ((ew[e] >> (l & 31u)) & 1u) || l == profile;
-      q[e] = quantized_weight(sv[e], ex, nm);
+    for (uint32_t k = 0; k < kRunWeights / 4; ++k) {
+      r.s[k] = reinterpret_cast<const float4 *>(s + f)[k];
+      // the raw indices arrive with the scores: the pick's costs no further
+      // round trip
+      r.raw[k] = reinterpret_cast<const uint4 *>(idx + f)[k];
     }
   }
+  __device__ void weigh(uint32_t first, const Run &r, uint32_t out,
+                        uint32_t (&q)[kRunWeights]) const {
+    uint32_t ex = out | past_end(first, n) | (r.mask >> (first & 31u) & 0xffffu);
+    if (profile - first < kRunWeights) ex |= 1u << (profile - first);
+    auto all = [&](auto wide) { // the choice of division path is made once
+#pragma unroll
+      for (uint32_t k = 0; k < kRunWeights / 4; ++k) {
+        const float v[4] = {r.s[k].x, r.s[k].y, r.s[k].z, r.s[k].w};
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+          q[4 * k + e] =
+              quantized_weight_t<decltype(wide)::value>(v[e], (ex >> (4 * k + e)) & 1u, nm);
+      }
+    };
+    if (nm.wide) all(std::true_type{});
+    else all(std::false_type{});
+  }
+  __device__ uint32_t raw_at(const Run &r, uint32_t e, uint32_t, const uint32_t *) const {
+    uint32_t v = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kRunWeights / 4; ++k) {
+      const uint32_t w[4] = {r.raw[k].x, r.raw[k].y, r.raw[k].z, r.raw[k].w};
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) v = e == 4 * k + i ? w[i] : v;
+    }
+    return v;
+  }
   __device__ void remove(uint32_t l) const { atomicOr(&explored[l >> 5], 1u << (l & 31u)); }
-  __device__ uint64_t valid_of(uint32_t l) const { return l; }
-  __device__ uint64_t raw_of(uint32_t l, const uint32_t *idx) const { return idx ? idx[l] : l; }
+  __device__ uint32_t valid_of(uint32_t l) const { return l; }
 };
+// Caller-given weights.
 struct ArrayWeights {
   uint32_t *q;
   uint32_t n;
+  struct Run {
+    uint4 q[kRunWeights / 4];
+  };
   __device__ void stage_load() {}
   __device__ void stage_reduce(StepAccSums *) const {}
   __device__ void stage_read(const StepAccSums *) {}
-  __device__ uint32_t operator()(uint32_t l) const { return l < n ? q[l] : 0u; }
-  template <int K> __device__ void run(uint32_t first, uint32_t cnt, uint32_t (&out)[K]) const {
+  __device__ void load(uint32_t first, const uint32_t *, Run &r) const {
+    const uint32_t f = first < n ? first : 0u;
 #pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const uint32_t l = first + e;
-      out[e] = ((uint32_t)e < cnt && l < n) ? q[l] : 0u;
+    for (uint32_t k = 0; k < kRunWeights / 4; ++k) r.q[k] = reinterpret_cast<const uint4 *>(q + f)[k];
+  }
+  __device__ void weigh(uint32_t first, const Run &r, uint32_t out,
+                        uint32_t (&w)[kRunWeights]) const {
+    const uint32_t ex = out | past_end(first, n);
+#pragma unroll
+    for (uint32_t k = 0; k < kRunWeights / 4; ++k) {
+      const uint32_t v[4] = {r.q[k].x, r.q[k].y, r.q[k].z, r.q[k].w};
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) w[4 * k + e] = (ex >> (4 * k + e)) & 1u ? 0u : v[e];
     }
   }
+  __device__ uint32_t raw_at(const Run &, uint32_t, uint32_t l, const uint32_t *) const { return l; }
   __device__ void remove(uint32_t l) const { q[l] = 0u; }
-  __device__ uint64_t valid_of(uint32_t l) const { return l; }
-  __device__ uint64_t raw_of(uint32_t l, const uint32_t *idx) const { return idx ? idx[l] : l; }
+  __device__ uint32_t valid_of(uint32_t l) const { return l; }
 };
 // Quantised weights of a restricted step's candidates (position l in
 // candidate order): drawing candidate l removes it and marks its
 // configuration nb[l] explored.
-struct NbWeights {
-  uint32_t *q;
+struct NbWeights : ArrayWeights {
   const uint32_t *nb;
   uint32_t *explored;
-  uint32_t n;
-  __device__ void stage_load() {}
-  __device__ void stage_reduce(StepAccSums *) const {}
-  __device__ void stage_read(const StepAccSums *) {}
-  __device__ uint32_t operator()(uint32_t l) const { return l < n ? q[l] : 0u; }
-  template <int K> __device__ void run(uint32_t first, uint32_t cnt, uint32_t (&out)[K]) const {
-#pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const uint32_t l = first + e;
-      out[e] = ((uint32_t)e < cnt && l < n) ? q[l] : 0u;
-    }
+  __device__ uint32_t raw_at(const Run &, uint32_t, uint32_t l, const uint32_t *idx) const {
+    return idx[nb[l]];
   }
   __device__ void remove(uint32_t l) const {
     q[l] = 0u;
     atomicOr(&explored[nb[l] >> 5], 1u << (nb[l] & 31u));
   }
-  __device__ uint64_t valid_of(uint32_t l) const { return nb[l]; }
-  __device__ uint64_t raw_of(uint32_t l, const uint32_t *idx) const { return idx[nb[l]]; }
+  __device__ uint32_t valid_of(uint32_t l) const { return nb[l]; }
 };
 
-// The draw result lives in mapped, coherent pinned host memory.  The thread
-// that settles a draw stores its fields with system-scope stores and then
-// `seq` with a system-scope release, so a host that sees `seq` sees the
-// fields (the host polls `seq` instead of waiting for the stream).
-__device__ __forceinline__ void put(uint64_t *field, uint64_t v) {
-  __hip_atomic_store(field, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-__device__ __forceinline__ void publish(DrawResult *res, uint64_t valid, uint64_t raw,
-                                        uint64_t total, uint64_t r, uint64_t seq) {
-  put(&res->valid, valid);
-  put(&res->raw, raw);
-  put(&res->total, total);
-  put(&res->r, r);
-  __hip_atomic_store(&res->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+// The draw result lives in mapped, coherent pinned host memory: four 64-bit
+// words, each carrying 32 bits of the result and the draw's sequence number,
+// stored with system scope.  The host (which polls instead of waiting for
+// the stream) takes the result once all four words carry the number, so the
+// stores need no order among them and the device no release fence, whose
+// write-back of the L2 cost about 1 us of every draw.
+__device__ __forceinline__ void publish(DrawResult *res, uint32_t valid, uint32_t raw,
+                                        uint64_t total, uint64_t seq) {
+  const uint32_t part[4] = {valid, raw, (uint32_t)total, (uint32_t)(total >> 32)};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    __hip_atomic_store(&res->word[i], (uint64_t)part[i] << 32 | (uint32_t)seq, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-constexpr uint32_t kNoLane = 0xffffffffu;
-constexpr uint32_t kKeepWeights = 8; // weights per thread kept in registers
+static_assert(kNoIndex == kNoProfile, "a draw without a pick leaves no profile");
 
-// One draw by one workgroup of NT threads.
+// n draws, one after another, by one workgroup of NT threads; draw i uses
+// u64[i] and publishes into res[i] under sequence number seq0 + i.
 //  1. Thread t owns the contiguous run of block sums [t * per, t * per + per);
 //     one exclusive scan over the run totals gives Q and, for the thread
 //     whose run holds r, the block b with prefix_b <= r < prefix_b + bsum_b.
 //  2. Every thread takes 2^block_log2 / NT consecutive configurations of
 //     block b; a second scan finds l with prefix_l <= r' < prefix_l + q_l.
-// The winner removes l, subtracts q_l from bsum_b and publishes the result.
+// The winner removes l; the run's owner subtracts q_l.
+// Bound: the dependent round trips to memory of one workgroup (block sums,
+// then scores with their raw indices; a further draw of a series waits for
+// scores only, the run totals stay in registers) and its instruction issue:
+// with 1,024 threads the two scans alone put 16 waves' instructions on four
+// SIMDs, so a draw has 256 threads of 16 configurations.  The barriers order
+// LDS only: removals are in flight across them, and the series keeps its own
+// picks out of later draws.
+// Measured (a draw launch): 5.6 us on 4.0M configurations and 5.2 us on
+// 7,616, four further draws of one series 14.5 us; 7.9, 7.7 and 28 us with
+// 1,024 threads, scans through the LDS crossbar, __syncthreads, the raw
+// index fetched after the pick and a releasing store per result.  16 block
+// sums a round trip: 6.0, 5.7 and 15.9 us (more instructions for the few
+// sums there are), 8.2 instead of 8.5 us on 27.7M configurations.
 template <int NT, typename W>
-__device__ void draw_body(W &wsrc, int block_log2, uint64_t *__restrict__ bsum,
-                          uint32_t n_blocks, uint64_t u64, const uint32_t *__restrict__ idx,
-                          DrawResult *__restrict__ res, uint64_t seq,
-                          uint32_t *__restrict__ prof_out = nullptr) {
+__device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum,
+                            uint32_t n_blocks, int n, const uint64_t *u64,
+                            const uint32_t *__restrict__ idx, DrawResult *__restrict__ res,
+                            uint64_t seq0, uint32_t *__restrict__ prof_out = nullptr) {
   __shared__ uint64_t scratch[NT / kWave];
   __shared__ StepAccSums sums;
   __shared__ uint32_t found_block;
   __shared__ uint64_t found_rem;
-  __shared__ int picked;
+  __shared__ uint32_t picked; // q of the pick, 0 without one
+  __shared__ uint32_t pick_pos[kMaxDrawSeries], pick_valid[kMaxDrawSeries],
+      pick_raw[kMaxDrawSeries];
+  __shared__ uint64_t pick_total[kMaxDrawSeries];
   const uint32_t tid = threadIdx.x;
 
   wsrc.stage_load();
   const uint32_t per = (n_blocks + NT - 1) / NT;
-  const uint32_t b0 = tid * per;
+  const uint32_t b0 = min(n_blocks, tid * per);
   const uint32_t b1 = min(n_blocks, b0 + per);
-  constexpr uint32_t kChunk = 4; // block sums loaded per round trip
-  uint64_t mine = 0;
-  for (uint32_t c = b0; c < b1; c += kChunk) {
-    uint64_t v[kChunk];
+  constexpr uint32_t kChunk = 8; // block sums loaded per round trip
+  uint64_t mine, run0[kChunk];   // the run's total and its first block sums
+  auto load_sums = [&](uint32_t c, uint64_t (&v)[kChunk]) {
 #pragma unroll
-    for (uint32_t k = 0; k < kChunk; ++k) v[k] = c + k < b1 ? bsum[c + k] : 0ull;
+    for (uint32_t k = 0; k < kChunk; ++k) v[k] = bsum[min(c + k, n_blocks - 1)];
+    uint64_t sum = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kChunk; ++k) mine += v[k];
+    for (uint32_t k = 0; k < kChunk; ++k) {
+      v[k] = c + k < b1 ? v[k] : 0ull;
+      sum += v[k];
+    }
+    return sum;
+  };
+  if (n_blocks != 0) {
+    mine = load_sums(b0, run0);
+    for (uint32_t c = b0 + kChunk; c < b1; c += kChunk) {
+      uint64_t v[kChunk];
+      mine += load_sums(c, v);
+    }
+  } else {
+    mine = 0;
   }
   wsrc.stage_reduce(&sums);
-  if (tid == 0) picked = 0;
-  uint64_t Q;
-  const uint64_t pre = block_excl_scan<NT>(mine, scratch, Q); // barriers publish sums
-  wsrc.stage_read(&sums);
-  if (Q == 0) {
-    if (tid == 0) {
-      if (prof_out) *prof_out = kNoProfile;
-      publish(res, kNoPick, kNoPick, 0, 0, seq);
+  for (int i = 0; i < n; ++i) {
+    uint64_t Q;
+    const uint64_t pre = block_excl_scan<NT, true>(mine, scratch, Q); // barriers publish sums
+    if (i == 0) wsrc.stage_read(&sums);
+    if (tid == 0) { // until the draw has a pick
+      picked = 0;
+      pick_pos[i] = kNoIndex;
+      pick_valid[i] = kNoIndex;
+      pick_raw[i] = kNoIndex;
+      pick_total[i] = Q;
     }
-    return;
-  }
-  const uint64_t r = __umul64hi(u64, Q);
-  if (mine != 0 && pre <= r && r < pre + mine) {
-    uint64_t run = pre;
-    bool hit = false;
-    for (uint32_t c = b0; c < b1 && !hit; c += kChunk) {
-      uint64_t v[kChunk];
+    if (Q == 0) continue; // uniform
+    const uint64_t r = __umul64hi(u64[i], Q);
+    const bool owner = mine != 0 && pre <= r && r < pre + mine;
+    if (owner) {
+      uint64_t run = pre;
+      uint32_t at = kNoIndex;
+      uint64_t rem = 0;
+      auto find = [&](uint32_t c, const uint64_t (&v)[kChunk]) {
 #pragma unroll
-      for (uint32_t k = 0; k < kChunk; ++k) v[k] = c + k < b1 ? bsum[c + k] : 0ull;
-#pragma unroll
-      for (uint32_t k = 0; k < kChunk; ++k) {
-        if (!hit && r < run + v[k]) {
-          found_block = c + k;
-          found_rem = r - run;
-          hit = true;
+        for (uint32_t k = 0; k < kChunk; ++k) {
+          const bool hit = at == kNoIndex && r < run + v[k];
+          rem = hit ? r - run : rem;
+          at = hit ? c + k : at;
+          run += v[k];
         }
-        run += v[k];
+      };
+      find(b0, run0);
+      for (uint32_t c = b0 + kChunk; c < b1 && at == kNoIndex; c += kChunk) {
+        uint64_t v[kChunk];
+        load_sums(c, v);
+        find(c, v);
       }
+      found_block = at;
+      found_rem = rem;
     }
-  }
-  __syncthreads();
-  const uint32_t blk = found_block;
-  const uint64_t rem = found_rem;
+    lds_barrier();
+    const uint32_t blk = found_block;
+    const uint64_t rem = found_rem;
 
-  // 2^block_log2 / NT >= 4 consecutive configurations per thread, weighed in
-  // chunks of kKeepWeights (the first chunk stays in registers)
-  const uint32_t per2 = (1u << block_log2) / NT;
-  const uint32_t first = (blk << block_log2) + tid * per2;
-  uint32_t qk[kKeepWeights];
-  wsrc.run(first, min(per2, kKeepWeights), qk);
-  uint64_t mine2 = 0;
+    // 2^block_log2 / NT consecutive configurations per thread, kRunWeights
+    // at a time; the weights of the first run stay in registers
+    const uint32_t per2 = (1u << block_log2) / NT;
+    const uint32_t first = (blk << block_log2) + tid * per2;
+    auto weigh = [&](uint32_t f, const typename W::Run &run, uint32_t (&q)[kRunWeights]) {
+      uint32_t out = 0; // this series' earlier picks
+      for (int j = 0; j < i; ++j)
+        if (pick_pos[j] - f < kRunWeights) out |= 1u << (pick_pos[j] - f);
+      wsrc.weigh(f, run, out, q);
+      uint64_t sum = 0;
 #pragma unroll
-  for (uint32_t e = 0; e < kKeepWeights; ++e) mine2 += qk[e];
-  for (uint32_t c = kKeepWeights; c < per2; c += kKeepWeights) {
-    uint32_t t[kKeepWeights];
-    wsrc.run(first + c, min(per2 - c, kKeepWeights), t);
-#pragma unroll
-    for (uint32_t e = 0; e < kKeepWeights; ++e) mine2 += t[e];
-  }
-  uint64_t blk_total;
-  const uint64_t pre2 = block_excl_scan<NT>(mine2, scratch, blk_total);
-  if (mine2 != 0 && pre2 <= rem && rem < pre2 + mine2) {
-    uint32_t l = kNoLane, ql = 0;
-    uint64_t run = pre2;
-#pragma unroll
-    for (uint32_t e = 0; e < kKeepWeights; ++e) {
-      if (l == kNoLane && rem < run + qk[e]) {
-        l = first + e;
-        ql = qk[e];
-      }
-      run += qk[e];
+      for (uint32_t e = 0; e < kRunWeights; ++e) sum += q[e];
+      return sum;
+    };
+    typename W::Run run;
+    uint32_t q[kRunWeights];
+    wsrc.load(first, idx, run);
+    const uint64_t sum0 = weigh(first, run, q);
+    uint64_t mine2 = sum0;
+    for (uint32_t c = kRunWeights; c < per2; c += kRunWeights) {
+      typename W::Run more;
+      uint32_t t[kRunWeights];
+      wsrc.load(first + c, idx, more);
+      mine2 += weigh(first + c, more, t);
     }
-    for (uint32_t c = kKeepWeights; l == kNoLane && c < per2; c += kKeepWeights) {
-      uint32_t t[kKeepWeights];
-      wsrc.run(first + c, min(per2 - c, kKeepWeights), t);
+    uint64_t blk_total;
+    const uint64_t pre2 = block_excl_scan<NT, true>(mine2, scratch, blk_total);
+    if (mine2 != 0 && pre2 <= rem && rem < pre2 + mine2) {
+      uint32_t f = first, at = kNoIndex, ql = 0;
+      uint64_t below = pre2;
+      auto find = [&]() {
 #pragma unroll
-      for (uint32_t e = 0; e < kKeepWeights; ++e) {
-        if (l == kNoLane && rem < run + t[e]) {
-          l = first + e + c;
-          ql = t[e];
+        for (uint32_t e = 0; e < kRunWeights; ++e) {
+          const bool hit = at == kNoIndex && rem < below + q[e];
+          at = hit ? e : at;
+          ql = hit ? q[e] : ql;
+          below += q[e];
         }
-        run += t[e];
+      };
+      find();
+      for (uint32_t c = kRunWeights; at == kNoIndex && c < per2; c += kRunWeights) {
+        f = first + c;
+        wsrc.load(f, idx, run);
+        weigh(f, run, q);
+        find();
       }
-    }
-    if (l != kNoLane) {
+      const uint32_t l = f + at;
+      picked = ql;
+      pick_pos[i] = l;
+      pick_valid[i] = wsrc.valid_of(l);
+      pick_raw[i] = wsrc.raw_at(run, at, l, idx);
       wsrc.remove(l);
+    }
+    lds_barrier();
+    const uint32_t ql = picked;
+    if (owner && ql != 0) {
+      mine -= ql;
+#pragma unroll
+      for (uint32_t k = 0; k < kChunk; ++k)
+        if (blk == b0 + k) run0[k] -= ql;
       bsum[blk] -= ql;
-      picked = 1;
-      if (prof_out) *prof_out = (uint32_t)wsrc.valid_of(l);
-      publish(res, wsrc.valid_of(l), wsrc.raw_of(l, idx), Q, r, seq);
     }
   }
-  __syncthreads();
-  // no pick although Q > 0: the block sums disagree with the weights
-  if (tid == 0 && !picked) {
-    if (prof_out) *prof_out = kNoProfile;
-    publish(res, kNoPick, kNoPick, Q, r, seq);
+  // The results leave together, one thread each.  (No pick although Q > 0:
+  // the block sums disagree with the weights.)
+  lds_barrier();
+  if (tid < (uint32_t)n) {
+    if (prof_out && tid == 0) *prof_out = pick_valid[0]; // kNoIndex == kNoProfile
+    publish(res + tid, pick_valid[tid], pick_raw[tid], pick_total[tid], seq0 + tid);
   }
 }
 
@@ -526,7 +611,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_scores(
     uint32_t *__restrict__ prof_out) {
   if (prof_dev) profile = *prof_dev;
   ScoreWeights w{s, explored, n_valid, profile, acc, gamma, w_min};
-  draw_body<kDrawThreads>(w, block_log2, bsum, n_blocks, u64, idx, res, seq, prof_out);
+  draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, 1, &u64, idx, res, seq, prof_out);
   __syncthreads();
   if (threadIdx.x == 0 && mark_profile && profile < n_valid)
     atomicOr(&explored[profile >> 5], 1u << (profile & 31u));
@@ -534,19 +619,14 @@ __global__ __launch_bounds__(kDrawThreads) void draw_scores(
 
 // Further draws of one step (after its first), made one after another by
 // one workgroup, each removing its pick before the next exactly as separate
-// launches of draw_scores would: draw i uses u64[i] and publishes into
-// res[i] under sequence number seq0 + i.
+// launches of draw_scores would.
 __global__ __launch_bounds__(kDrawThreads) void draw_many(
     const float *__restrict__ s, uint32_t *__restrict__ explored, uint32_t n_valid,
     const StepAcc *__restrict__ acc, float gamma, float w_min, int block_log2,
     uint64_t *__restrict__ bsum, uint32_t n_blocks, DrawSeries series,
     const uint32_t *__restrict__ idx, DrawResult *__restrict__ res, uint64_t seq0) {
-  for (int i = 0; i < series.n; ++i) {
-    ScoreWeights w{s, explored, n_valid, kNoProfile, acc, gamma, w_min};
-    draw_body<kDrawThreads>(w, block_log2, bsum, n_blocks, series.u64[i], idx, res + i,
-                            seq0 + (uint64_t)i);
-    __syncthreads(); // the pick's removal is seen by the next draw
-  }
+  ScoreWeights w{s, explored, n_valid, kNoProfile, acc, gamma, w_min};
+  draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, series.n, series.u64, idx, res, seq0);
 }
 
 // ------------------------------------------------------------ batched
@@ -609,7 +689,7 @@ __global__ __launch_bounds__(kDrawThreads) void batch_draw(const BatchSess *__re
   if (!st.draw) return;
   ScoreWeights w{d.s, d.explored, d.n_valid, st.profile, d.acc + st.parity * kAccSlots, d.gamma,
                  d.w_min};
-  draw_body<kDrawThreads>(w, d.block_log2, d.bsum, d.n_blocks, st.u64, d.idx, d.res, st.seq);
+  draw_series<kDrawThreads>(w, d.block_log2, d.bsum, d.n_blocks, 1, &st.u64, d.idx, d.res, st.seq);
   __syncthreads();
   if (threadIdx.x == 0 && st.profile < d.n_valid)
     atomicOr(&d.explored[st.profile >> 5], 1u << (st.profile & 31u));
@@ -760,8 +840,8 @@ __global__ __launch_bounds__(kDrawThreads) void nb_draw(
     uint64_t *__restrict__ bsum, uint32_t *__restrict__ explored, uint32_t profile,
     int mark_profile, uint32_t n_valid, uint64_t u64, const uint32_t *__restrict__ idx,
     DrawResult *__restrict__ res, uint64_t seq) {
-  NbWeights w{q, nb, explored, stats->count};
-  draw_body<kDrawThreads>(w, kNbBlockLog2, bsum, kNbBlocks, u64, idx, res, seq);
+  NbWeights w{{q, stats->count}, nb, explored};
+  draw_series<kDrawThreads>(w, kNbBlockLog2, bsum, kNbBlocks, 1, &u64, idx, res, seq);
   __syncthreads();
   if (threadIdx.x == 0 && mark_profile && profile < n_valid)
     atomicOr(&explored[profile >> 5], 1u << (profile & 31u));
@@ -779,7 +859,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_array(uint32_t *__restrict_
                                                            uint32_t n_blocks, uint64_t u64,
                                                            DrawResult *__restrict__ res) {
   ArrayWeights w{q, n};
-  draw_body<kDrawThreads>(w, block_log2, bsum, n_blocks, u64, nullptr, res, 1);
+  draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, 1, &u64, nullptr, res, 1);
 }
 
 __global__ __launch_bounds__(kWeightThreads) void array_block_sums(const uint32_t *__restrict__ q,
