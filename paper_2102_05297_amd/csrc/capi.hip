@@ -1093,42 +1093,45 @@ extern "C" void cgs_default_tuning_opts(cgs_tuning_opts *out) {
 
 namespace {
 
-hipError_t launch_pending(cgs_session s, bool do_draw, uint64_t u64);
+bool small_steps(const cgs_session_s *s);
+hipError_t launch_pending(cgs_session s, int n_draws, const uint64_t *u64, DrawResult *d_res);
 cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq, Pick *pick);
 
-// The next n draws of a full step (1 <= n <= kMaxDrawSeries + 1) with
-// uniforms u64[0..n): the first as cgs_sample_next makes it (launching a
-// recorded step), the others in one draw_many launch, all enqueued before
-// the host waits; each removes its pick before the next, so the picks are
-// those of n cgs_sample_next calls.  valid[0..*made) receives the picks;
+// The next n draws of a full step (1 <= n <= kMaxDrawSeries) with uniforms
+// u64[0..n): with the recorded step in one launch on a small space;
+// otherwise the first as cgs_sample_next makes it (launching a recorded
+// step) and the others in one draw_many launch, all enqueued before the host
+// waits.  Each removes its pick before the next, so the picks are those of n
+// cgs_sample_next calls.  valid[0..*made) receives the picks;
 // *made < n when a draw found nothing to draw (Q == 0; the later ones find
 // nothing either).
 cgs_status draw_series(cgs_session s, int n, const uint64_t *u64, uint64_t *valid, int *made) {
   cgs_space sp = s->space;
   *made = 0;
-  if (s->pending) {
-    HIP_TRY(launch_pending(s, true, u64[0]));
+  const uint64_t seq_first = s->seq + 1;
+  if (s->pending && small_steps(s)) {
+    HIP_TRY(launch_pending(s, n, u64, s->d_ring));
+  } else if (s->pending) {
+    HIP_TRY(launch_pending(s, 1, u64, s->d_ring));
   } else {
     HIP_TRY(launch_draw(s->d_s, s->d_explored, (uint32_t)sp->n_valid, kNoProfile, false,
                         s->d_acc + s->cur_acc * kAccSlots, s->params.gamma, s->params.w_min,
-                        s->block_log2, s->d_bsum, s->n_blocks, u64[0], sp->d_idx, s->d_res,
+                        s->block_log2, s->d_bsum, s->n_blocks, u64[0], sp->d_idx, s->d_ring,
                         ++s->seq, sp->stream));
   }
-  const uint64_t seq_first = s->seq;
-  if (n > 1) {
+  if (s->seq == seq_first && n > 1) { // the first draw was launched alone
     DrawSeries ser{};
     ser.n = n - 1;
     for (int i = 1; i < n; ++i) ser.u64[i - 1] = u64[i];
     HIP_TRY(launch_draw_many(s->d_s, s->d_explored, (uint32_t)sp->n_valid,
                              s->d_acc + s->cur_acc * kAccSlots, s->params.gamma, s->params.w_min,
-                             s->block_log2, s->d_bsum, s->n_blocks, ser, sp->d_idx, s->d_ring,
-                             seq_first + 1, sp->stream));
+                             s->block_log2, s->d_bsum, s->n_blocks, ser, sp->d_idx,
+                             s->d_ring + 1, seq_first + 1, sp->stream));
     s->seq += (uint64_t)(n - 1);
   }
   for (int i = 0; i < n; ++i) {
-    const DrawResult *slot = i == 0 ? s->h_res : s->h_ring + (i - 1);
     Pick r;
-    const cgs_status ws = wait_draw(s, slot, seq_first + (uint64_t)i, &r);
+    const cgs_status ws = wait_draw(s, s->h_ring + i, seq_first + (uint64_t)i, &r);
     if (ws != CGS_OK) return ws;
     s->last_total = r.total;
     if (r.total == 0) return CGS_OK;
@@ -1199,11 +1202,11 @@ extern "C" cgs_status cgs_tuning_run(cgs_session s, cgs_model m, const float *ru
       }
       return false;
     };
-    if (opts->draws <= kMaxDrawSeries + 1 && !s->pending_nb && (s->pending || !s->last_nb)) {
+    if (opts->draws <= kMaxDrawSeries && !s->pending_nb && (s->pending || !s->last_nb)) {
       // the step's draws in one go: they depend on its weights and the
       // uniforms only, the tests decide where the run stops
       const int want = (int)std::min<uint64_t>((uint64_t)opts->draws, n_uniforms - u);
-      uint64_t picks[kMaxDrawSeries + 1];
+      uint64_t picks[kMaxDrawSeries];
       int made = 0;
       if (want > 0) st = draw_series(s, want, uniforms + u, picks, &made);
       u += (uint64_t)std::max(want, 0);
@@ -1907,47 +1910,81 @@ hipError_t launch_pending_nb(cgs_session s, bool do_draw, uint64_t u64) {
   return hipSuccess;
 }
 
-// Enqueues one full step: score pass, weight pass, and either its first
-// draw (do_draw; result in d_res under sequence number seq) or just the
-// marking of its profiled configuration.  The profile is `prof` or, with
+// Whether the session's full steps run as one launch (launch_small_step):
+// small spaces, without timing (whose markers stand between the kernels).
+bool small_steps(const cgs_session_s *s) {
+  return s->space->n_valid <= kSmallMaxValid && s->params.timing == 0;
+}
+
+// Enqueues one full step: score pass, weight pass, and n_draws draws (one,
+// or up to kMaxDrawSeries where small_steps(s)) or just the marking of its
+// profiled configuration (none).  Draw i uses u64[i], its result goes to
+// d_res[i] under sequence number seq + i.  The profile is `prof` or, with
 // d_prof_in, the word the previous step's draw left in device memory
 // (`scored` then tells whether the step has counters to score); with
-// d_prof_out the draw leaves its pick there.  Advances the accumulator set.
+// d_prof_out the first draw leaves its pick there.  Advances the accumulator
+// set.
 hipError_t launch_full_step(cgs_session s, cgs_model m, const ActiveCounters &act, uint32_t prof,
                             const uint32_t *d_prof_in, uint32_t *d_prof_out, bool scored,
-                            bool do_draw, uint64_t u64, DrawResult *d_res, uint64_t seq) {
+                            int n_draws, const uint64_t *u64, DrawResult *d_res, uint64_t seq) {
   cgs_space sp = s->space;
   const uint32_t nv = (uint32_t)sp->n_valid;
   StepAcc *acc = s->d_acc + s->parity * kAccSlots;
   StepAcc *acc_next = s->d_acc + (s->parity ^ 1) * kAccSlots;
   const bool timed = s->params.timing > 0 && s->n_launched % (uint64_t)s->params.timing == 0;
   hipError_t e = hipSuccess;
-  TimedSpan *span = nullptr;
-  if (timed) {
-    // kind 5: a score pass that reads no prediction (no profile or no active
-    // counter, e.g. the uniform start), kept out of the score-pass totals
-    const int kinds[3] = {scored ? 0 : 5, 1, do_draw ? 2 : 3};
-    e = begin_span(s, 3, kinds, &span);
-    s->t_step = (int32_t)(s->t_spans.size() - 1);
+  if (small_steps(s)) {
+    SmallStep a{};
+    a.P = m->d_P;
+    a.stride = m->stride;
+    a.prof_dev = d_prof_in;
+    a.profile = prof;
+    a.n_valid = nv;
+    a.explored = s->d_explored;
+    a.s = s->d_s;
+    a.acc = acc;
+    a.acc_next = acc_next;
+    a.gamma = s->params.gamma;
+    a.w_min = s->params.w_min;
+    a.block_log2 = s->block_log2;
+    a.n_blocks = s->n_blocks;
+    a.bsum = s->d_bsum;
+    a.idx = sp->d_idx;
+    a.res = d_res;
+    a.seq0 = seq;
+    a.prof_out = d_prof_out;
+    a.act = act;
+    a.series.n = n_draws;
+    for (int i = 0; i < n_draws; ++i) a.series.u64[i] = u64[i];
+    e = launch_small_step(a, sp->stream);
+  } else {
+    TimedSpan *span = nullptr;
+    if (timed) {
+      // kind 5: a score pass that reads no prediction (no profile or no active
+      // counter, e.g. the uniform start), kept out of the score-pass totals
+      const int kinds[3] = {scored ? 0 : 5, 1, n_draws ? 2 : 3};
+      e = begin_span(s, 3, kinds, &span);
+      s->t_step = (int32_t)(s->t_spans.size() - 1);
+    }
+    if (e == hipSuccess)
+      e = launch_score_pass(m->d_P, m->stride, prof, act, s->d_explored, nv, s->d_s, acc,
+                            sp->stream, d_prof_in);
+    if (e == hipSuccess && timed) e = mark_span(s, span, 0);
+    if (e == hipSuccess)
+      e = launch_weight_pass(s->d_s, s->d_explored, nv, prof, acc, acc_next, s->params.gamma,
+                             s->params.w_min, s->block_log2, s->d_bsum, s->n_blocks, sp->stream,
+                             d_prof_in);
+    if (e == hipSuccess && timed) e = mark_span(s, span, 1);
+    if (e == hipSuccess) {
+      if (n_draws)
+        e = launch_draw(s->d_s, s->d_explored, nv, prof, true, acc, s->params.gamma,
+                        s->params.w_min, s->block_log2, s->d_bsum, s->n_blocks, u64[0], sp->d_idx,
+                        d_res, seq, sp->stream, d_prof_in, d_prof_out);
+      else
+        e = launch_mark_one(s->d_explored, prof, nv, sp->stream);
+    }
+    if (e == hipSuccess && timed) e = mark_span(s, span, 2);
   }
-  if (e == hipSuccess)
-    e = launch_score_pass(m->d_P, m->stride, prof, act, s->d_explored, nv, s->d_s, acc,
-                          sp->stream, d_prof_in);
-  if (e == hipSuccess && timed) e = mark_span(s, span, 0);
-  if (e == hipSuccess)
-    e = launch_weight_pass(s->d_s, s->d_explored, nv, prof, acc, acc_next, s->params.gamma,
-                           s->params.w_min, s->block_log2, s->d_bsum, s->n_blocks, sp->stream,
-                           d_prof_in);
-  if (e == hipSuccess && timed) e = mark_span(s, span, 1);
-  if (e == hipSuccess) {
-    if (do_draw)
-      e = launch_draw(s->d_s, s->d_explored, nv, prof, true, acc, s->params.gamma, s->params.w_min,
-                      s->block_log2, s->d_bsum, s->n_blocks, u64, sp->d_idx, d_res, seq,
-                      sp->stream, d_prof_in, d_prof_out);
-    else
-      e = launch_mark_one(s->d_explored, prof, nv, sp->stream);
-  }
-  if (e == hipSuccess && timed) e = mark_span(s, span, 2);
   if (e != hipSuccess) return e;
   ++s->n_launched;
   s->step_timed = timed;
@@ -1958,20 +1995,22 @@ hipError_t launch_full_step(cgs_session s, cgs_model m, const ActiveCounters &ac
   return hipSuccess;
 }
 
-hipError_t launch_pending(cgs_session s, bool do_draw, uint64_t u64) {
-  if (s->pending_nb) return launch_pending_nb(s, do_draw, u64);
+// Launches the recorded step with n_draws draws (more than one where
+// small_steps(s)) into d_res; the draws take the next sequence numbers.
+hipError_t launch_pending(cgs_session s, int n_draws, const uint64_t *u64, DrawResult *d_res) {
+  if (s->pending_nb) return launch_pending_nb(s, n_draws != 0, n_draws ? u64[0] : 0);
   const uint32_t prof = s->pending_profile;
   const bool scored = prof < (uint32_t)s->space->n_valid && s->pending_act.n > 0;
-  const uint64_t seq = do_draw ? ++s->seq : s->seq;
   const hipError_t e = launch_full_step(s, s->pending_model, s->pending_act, prof, nullptr,
-                                        nullptr, scored, do_draw, u64, s->d_res, seq);
+                                        nullptr, scored, n_draws, u64, d_res, s->seq + 1);
   if (e != hipSuccess) return e;
+  s->seq += (uint64_t)n_draws;
   s->pending = false;
   return hipSuccess;
 }
 
 cgs_status flush_pending(cgs_session s) {
-  if (s->pending) HIP_TRY(launch_pending(s, false, 0));
+  if (s->pending) HIP_TRY(launch_pending(s, 0, nullptr, nullptr));
   return CGS_OK;
 }
 
@@ -2232,7 +2271,7 @@ extern "C" cgs_status cgs_search_run(cgs_session s, cgs_model m, int n_steps,
   auto launch = [&](int k) {
     const uint32_t *in = k == 0 ? nullptr : s->d_prof + (k & 1);
     return launch_full_step(s, m, acts[k], kNoProfile, in, s->d_prof + ((k + 1) & 1),
-                            k > 0 && acts[k].n > 0, true, u64[k], s->d_ring + k % kResultRing,
+                            k > 0 && acts[k].n > 0, 1, u64 + k, s->d_ring + k % kResultRing,
                             seq0 + (uint64_t)k + 1);
   };
   // leaves the session as after the last launched step: no further draw
@@ -2563,7 +2602,7 @@ extern "C" cgs_status cgs_sample_next(cgs_session s, uint64_t u64, uint64_t *raw
   cgs_space sp = s->space;
   if (sp->n_valid == 0) return fail(CGS_EEMPTY, "the space has no valid configuration");
   if (s->pending) {
-    HIP_TRY(launch_pending(s, true, u64));
+    HIP_TRY(launch_pending(s, 1, &u64, s->d_res));
   } else {
     TimedSpan *span = nullptr;
     if (s->step_timed) {

@@ -18,6 +18,8 @@ struct FastDiv {
   uint32_t sh; // sh1 | sh2 << 8
 };
 
+FastDiv make_fastdiv(uint32_t d);
+
 // Space description, resident in device memory (one per space).
 // Parameter j's value for digit d is table[j * CGS_MAX_RADIX + d].
 struct SpaceDev {
@@ -192,12 +194,40 @@ hipError_t launch_weight_pass(const float *d_s, const uint32_t *d_explored, uint
 // The draw stores its result, then `seq` with a system-scope release; with
 // d_prof_out also the pick's valid index (kNoProfile without a pick).
 // Up to kMaxDrawSeries further draws of one step in one launch (draw_many).
-constexpr int kMaxDrawSeries = 32;
+constexpr int kMaxDrawSeries = 33;
 struct DrawSeries {
   int32_t n;
   int32_t pad;
   uint64_t u64[kMaxDrawSeries];
 };
+// A whole step (score, weights, series.n >= 0 draws, profile marked
+// explored) of a space of 1 .. kSmallMaxValid configurations in one launch;
+// the arguments of the separate launches, with acc_next[0].pad as the
+// workgroups' meeting counter (0 between launches).
+constexpr uint32_t kSmallMaxValid = 32768;
+struct SmallStep {
+  const float *P;
+  uint64_t stride;
+  const uint32_t *prof_dev;
+  uint32_t profile;
+  uint32_t n_valid;
+  uint32_t *explored;
+  float *s;
+  StepAcc *acc, *acc_next;
+  float gamma, w_min;
+  int32_t block_log2;
+  uint32_t n_blocks;
+  uint64_t *bsum;
+  const uint32_t *idx;
+  DrawResult *res;
+  uint64_t seq0;
+  uint32_t *prof_out;
+  uint32_t per;  // set by the launch: weights per thread, and their quads
+  FastDiv per4;  // as a divisor
+  ActiveCounters act;
+  DrawSeries series;
+};
+hipError_t launch_small_step(SmallStep &a, hipStream_t stream);
 hipError_t launch_draw_many(const float *d_s, uint32_t *d_explored, uint32_t n_valid,
                             const StepAcc *d_acc, float gamma, float w_min, int block_log2,
                             uint64_t *d_bsum, uint32_t n_blocks, const DrawSeries &series,

@@ -84,8 +84,6 @@ hipError_t launch_pack_weights(const MlpShape &sh, const float *theta, size_t n,
                                const MlpCopies &cp, hipStream_t stream);
 
 // ---- regression-tree fitting (Sect. 3.4.2)
-FastDiv make_fastdiv(uint32_t d);
-
 struct TreeFitIn {
   const SpaceDev *d_space;
   const uint32_t *d_idx;    // valid raw indices of the space

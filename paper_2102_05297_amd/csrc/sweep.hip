@@ -629,6 +629,228 @@ __global__ __launch_bounds__(kDrawThreads) void draw_many(
   draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, series.n, series.u64, idx, res, seq0);
 }
 
+// ------------------------------------------------------------ small spaces
+// A whole step of a space of at most kSmallMaxValid configurations in one
+// launch: 256 configurations a workgroup are scored, and the workgroup that
+// finishes last weighs all of them, keeps the weights in LDS and makes the
+// step's draws.
+// Bound: latency.  As separate launches (score, weight, draw, further draws)
+// such a step is four kernel starts, each with its own chain of dependent
+// round trips, and every draw weighs a block again; here the draws after the
+// weighing cost two LDS barriers and one LDS read each.
+// The workgroups meet on one counter: each adds 1 with release once its
+// scores and its min / max slot are written, the one that brings it to the
+// number of workgroups goes on after an acquire (no workgroup waits).
+// 512 threads: with 256 the last workgroup's single wave per SIMD leaves its
+// weighing waiting on its own latencies (2.6 against 1.5 us on 7,616
+// configurations), with 1,024 every barrier of a draw costs more (0.62 to
+// 1.2 us a draw).
+// Measured on 7,616 configurations, 9 to 13 active counters: 8.9 us with one
+// draw and 11.6 us with five, against 16.5 and 31 us for the separate
+// launches; of the 8.9 us, 2.3 to the scores, 1.4 for the handoff, 3.3 to
+// load and weigh, 0.6 the draw, 0.5 to publish, 0.4 the block sums.
+// kSmallMaxValid: one accumulator slot per workgroup, and the weights fit in
+// the last workgroup's LDS.  It is also where the two ways meet: steps
+// enqueued ahead take 10.5 against 16.7 us on 8,192 configurations, 12.9
+// against 16.6 us on 16,384, 16.5 against 16.8 us on 32,768.
+constexpr int kSmallThreads = 512;
+constexpr uint32_t kSmallPer = 64; // weights per thread of the last workgroup
+static_assert(kSmallMaxValid == kSmallThreads * kSmallPer, "one run per thread");
+static_assert(kSmallMaxValid <= kAccSlots * kSmallThreads, "one accumulator slot per workgroup");
+static_assert(kSmallPer <= kWave && kSmallPer % 4 == 0, "a wave searches a run at once");
+// Words between the runs of `per` weights in LDS: an odd number of 16-byte
+// units, so that threads reading their runs start in different banks.
+__host__ __device__ constexpr uint32_t small_ld(uint32_t per) { return per + (per & 4u ? 0u : 4u); }
+
+// Score of configuration l against the profiled one: counters ctr[0..n) with
+// changes delta[], the loads of RIF counters in flight together.
+template <int RIF>
+__device__ __forceinline__ float score_one(const float *__restrict__ P, uint64_t stride,
+                                           uint32_t profile, int n, const uint32_t *ctr,
+                                           const float *delta, uint32_t l) {
+  float s = 0.0f;
+  for (int j0 = 0; j0 < n; j0 += RIF) {
+    float x[RIF], a[RIF];
+#pragma unroll
+    for (int u = 0; u < RIF; ++u) {
+      const float *row = P + (size_t)ctr[min(j0 + u, n - 1)] * stride;
+      x[u] = row[l];
+      a[u] = row[profile];
+    }
+#pragma unroll
+    for (int u = 0; u < RIF; ++u) {
+      if (j0 + u < n && a[u] != 0.0f) { // a_p == 0: counter not in PC_used
+        const float t = (x[u] - a[u]) / (a[u] + x[u]);
+        s = (x[u] != 0.0f) ? s + delta[j0 + u] * t : s;
+      }
+    }
+  }
+  return s;
+}
+
+// The last workgroup's part: weighs the n_valid scores, makes the draws and
+// leaves the block sums.  Thread t owns the run of a.per consecutive weights
+// from t * per (LDS words q[t * ld ..]).
+__device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile, uint32_t *q) {
+  __shared__ uint64_t scratch[kSmallThreads / kWave];
+  __shared__ StepAccSums sums;
+  __shared__ uint32_t pick_pos[kMaxDrawSeries];
+  __shared__ uint64_t pick_total[kMaxDrawSeries];
+  constexpr uint32_t kBlocks = (kSmallMaxValid + 4095) >> 12; // blocks hold 4096 or more
+  __shared__ unsigned long long blk_sum[kBlocks];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_valid = a.n_valid;
+  const uint32_t per = a.per, ld = small_ld(per), first = tid * per;
+  const uint32_t n_quads = kSmallThreads * (per / 4);
+  StepAcc slot{};
+  if (tid < kWave) slot = a.acc[tid];
+  // scores four at a time, kInFlight loads per thread together; positions
+  // past the end weigh 0
+  constexpr uint32_t kInFlight = 4;
+  float4 v[kInFlight];
+  uint32_t ew[kInFlight];
+  auto load = [&](uint32_t q0) {
+#pragma unroll
+    for (uint32_t k = 0; k < kInFlight; ++k) {
+      const uint32_t f = 4u * (q0 + k * kSmallThreads + tid);
+      const uint32_t fc = f < n_valid ? f : 0u;
+      v[k] = *reinterpret_cast<const float4 *>(a.s + fc);
+      ew[k] = a.explored[fc >> 5] >> (fc & 31u);
+    }
+  };
+  load(0);
+  reduce_slot_values(slot, &sums);
+  if (tid < kBlocks) blk_sum[tid] = 0ull;
+  if (tid < (uint32_t)a.series.n) pick_pos[tid] = kNoIndex;
+  lds_barrier();
+  const StepNorm nm = step_norm(key_float(sums.min_key), key_float(sums.max_key), a.gamma, a.w_min);
+  auto weigh = [&](auto wide) {
+    for (uint32_t q0 = 0;;) {
+#pragma unroll
+      for (uint32_t k = 0; k < kInFlight; ++k) {
+        const uint32_t quad = q0 + k * kSmallThreads + tid, f = 4u * quad;
+        uint32_t ex4 = ew[k];
+        if (f >= n_valid) ex4 = 0xfu;
+        else if (n_valid - f < 4u) ex4 |= 0xfu << (n_valid - f);
+        if (profile - f < 4u) ex4 |= 1u << (profile - f);
+        const float sv[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+        uint32_t w[4];
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+          w[e] = quantized_weight_t<decltype(wide)::value>(sv[e], (ex4 >> e) & 1u, nm);
+        const uint32_t run = fastdiv(quad, a.per4); // its thread
+        if (quad < n_quads)
+          *reinterpret_cast<uint4 *>(q + f + run * (ld - per)) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+      q0 += kInFlight * kSmallThreads;
+      if (q0 >= n_quads) break;
+      load(q0);
+    }
+  };
+  if (nm.wide) weigh(std::true_type{});
+  else weigh(std::false_type{});
+  lds_barrier();
+  uint64_t mine = 0;
+  for (uint32_t e = 0; e < per; e += 4) {
+    const uint4 w = *reinterpret_cast<const uint4 *>(q + tid * ld + e);
+    mine += (uint64_t)w.x + w.y + w.z + w.w;
+  }
+  for (int i = 0; i < a.series.n; ++i) {
+    uint64_t Q;
+    const uint64_t pre = block_excl_scan<kSmallThreads, true>(mine, scratch, Q);
+    if (tid == 0) pick_total[i] = Q;
+    const uint64_t r = __umul64hi(a.series.u64[i], Q); // 0 when Q == 0: no owner
+    const bool owner = pre <= r && r < pre + mine;
+    const uint64_t own = __ballot(owner);
+    if (own != 0) { // the owner's wave looks through its run, one weight per lane
+      const int o = __ffsll((unsigned long long)own) - 1;
+      const uint32_t run = (tid & ~63u) + (uint32_t)o;
+      const uint64_t rem = (uint64_t)__shfl((long long)(r - pre), o);
+      const uint64_t w = lane < per ? q[run * ld + lane] : 0u;
+      const uint64_t incl = wave_incl_scan(w);
+      if (rem < incl && incl - w <= rem) { // one lane: prefix <= rem < prefix + w
+        const uint32_t l = run * per + lane;
+        q[run * ld + lane] = 0u;
+        pick_pos[i] = l;
+        atomicOr(&a.explored[l >> 5], 1u << (l & 31u));
+      }
+      const uint64_t hit = __ballot(rem < incl && incl - w <= rem);
+      const uint64_t ql = (uint64_t)__shfl((long long)w, __ffsll((unsigned long long)hit) - 1);
+      if (owner) mine -= ql;
+    }
+  }
+  lds_barrier();
+  if (tid < (uint32_t)a.series.n) {
+    const uint32_t l = pick_pos[tid];
+    const uint32_t raw = l != kNoIndex ? a.idx[l] : kNoIndex;
+    if (a.prof_out && tid == 0) *a.prof_out = l; // kNoIndex == kNoProfile
+    publish(a.res + tid, l, raw, pick_total[tid], a.seq0 + tid);
+  }
+  // the block sums as the draws left them, for further draws of this step
+  const uint32_t lg = (uint32_t)a.block_log2, b0 = first >> lg;
+  uint64_t lower = mine; // the run's part in its first block
+  if (first < n_valid && (first + per - 1) >> lg != b0) {
+    lower = 0;
+    for (uint32_t e = 0; e < per; e += 4) { // blocks start at multiples of 4
+      const uint4 w = *reinterpret_cast<const uint4 *>(q + tid * ld + e);
+      if ((first + e) >> lg == b0) lower += (uint64_t)w.x + w.y + w.z + w.w;
+    }
+  }
+  if (__all(lower == mine && b0 == __shfl(b0, 0))) { // one block: one addition per wave
+    const uint64_t sum = wave_sum(mine);
+    if (lane == 0 && sum != 0) atomicAdd(&blk_sum[b0], (unsigned long long)sum);
+  } else {
+    if (lower != 0) atomicAdd(&blk_sum[b0], (unsigned long long)lower);
+    if (mine != lower) atomicAdd(&blk_sum[b0 + 1], (unsigned long long)(mine - lower));
+  }
+  lds_barrier();
+  if (tid < a.n_blocks) a.bsum[tid] = blk_sum[tid];
+}
+
+__global__ __launch_bounds__(kSmallThreads) void small_step(SmallStep a) {
+  extern __shared__ uint32_t small_q[];
+  __shared__ uint32_t red[3][kSmallThreads / kWave];
+  __shared__ uint32_t arrived;
+  const uint32_t tid = threadIdx.x, n_valid = a.n_valid;
+  uint32_t profile = a.prof_dev ? *a.prof_dev : a.profile;
+  const int n = profile < n_valid ? a.act.n : 0;
+  const uint32_t l = blockIdx.x * kSmallThreads + tid, lc = min(l, n_valid - 1);
+  const uint32_t word = a.explored[lc >> 5];
+  const float s = score_one<16>(a.P, a.stride, profile, n, a.act.ctr, a.act.delta, lc);
+  const bool ex = l >= n_valid || l == profile || ((word >> (lc & 31u)) & 1u);
+  if (l < n_valid) a.s[l] = s;
+  const uint32_t key = float_key(s);
+  const uint32_t kmin = wave_umin(ex ? 0xffffffffu : key), kmax = wave_umax(ex ? 0u : key);
+  const uint32_t cnt = (uint32_t)__popcll(__ballot(!ex));
+  if ((tid & 63u) == 0) {
+    red[0][tid >> 6] = kmin;
+    red[1][tid >> 6] = kmax;
+    red[2][tid >> 6] = cnt;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    StepAcc slot{red[0][0], red[1][0], red[2][0], 0u};
+#pragma unroll
+    for (int w = 1; w < kSmallThreads / kWave; ++w) {
+      slot.min_key = min(slot.min_key, red[0][w]);
+      slot.max_key = max(slot.max_key, red[1][w]);
+      slot.n_unexplored += red[2][w];
+    }
+    a.acc[blockIdx.x].min_key = slot.min_key;
+    a.acc[blockIdx.x].max_key = slot.max_key;
+    a.acc[blockIdx.x].n_unexplored = slot.n_unexplored;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    arrived = atomicAdd(&a.acc_next[0].pad, 1u);
+  }
+  __syncthreads();
+  if (arrived != gridDim.x - 1) return; // uniform over the workgroup
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (tid == 0) a.acc_next[0].pad = 0u;
+  small_draws(a, profile, small_q);
+  clear_acc(a.acc_next); // the next step's accumulators
+  if (tid == 0 && profile < n_valid)
+    atomicOr(&a.explored[profile >> 5], 1u << (profile & 31u));
+}
+
 // ------------------------------------------------------------ batched
 // Score tiles of every session, grid-stride over the concatenated tile list;
 // a workgroup flushes its accumulators whenever the session changes.
@@ -950,6 +1172,23 @@ hipError_t launch_draw_many(const float *d_s, uint32_t *d_explored, uint32_t n_v
   hipLaunchKernelGGL(draw_many, dim3(1), dim3(kDrawThreads), 0, stream, d_s, d_explored, n_valid,
                      d_acc, gamma, w_min, block_log2, d_bsum, n_blocks, series, d_idx, d_res,
                      seq0);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_step(SmallStep &a, hipStream_t stream) {
+  if (a.n_valid == 0 || a.n_valid > kSmallMaxValid || a.series.n < 0 ||
+      a.series.n > kMaxDrawSeries || a.block_log2 < 12)
+    return hipErrorInvalidValue;
+  const uint32_t grid = (a.n_valid + kSmallThreads - 1) / kSmallThreads;
+  a.per = (grid + 3u) & ~3u; // grid configurations per thread, in whole quads
+  a.per4 = make_fastdiv(a.per / 4);
+  const size_t lds = small_ld(a.per) * kSmallThreads * sizeof(uint32_t);
+  if (lds > 62 * 1024) { // with the static part, past what needs no opt-in
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(small_step),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(small_step, dim3(grid), dim3(kSmallThreads), lds, stream, a);
   return hipGetLastError();
 }
 
