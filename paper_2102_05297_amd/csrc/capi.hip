@@ -500,6 +500,13 @@ void destroy_model(cgs_model m) {
   delete m;
 }
 
+// Columns of the predictions past n_valid hold zeros; the evaluations write
+// every other one.
+hipError_t clear_padding(cgs_model m) {
+  return launch_clear_columns(m->d_P, m->stride, m->n_counters, m->space->n_valid,
+                              m->space->stream);
+}
+
 MlpCopies mlp_copies(cgs_model m) {
   return MlpCopies{m->d_w1p, m->d_w2p, m->d_w3p, m->d_w2t, m->d_w3t,
                    m->d_w1n, m->d_w2n, m->d_w3n};
@@ -524,6 +531,25 @@ MlpFwdArgs mlp_args(cgs_model m) {
   a.P = m->d_P;
   a.stride = m->stride;
   return a;
+}
+
+// Where launch_check_floats leaves the first bad value of a model's inputs,
+// and its copy for the host.
+struct FloatCheck {
+  uint64_t *d_first = nullptr;
+  uint64_t first = kNoPick;
+  ~FloatCheck() { dfree(d_first); }
+};
+
+// Enqueues the check of x[0..n) on the stream; `c.first` is the first bad
+// position (kNoPick: none) once the stream has been synchronised.
+hipError_t check_floats(FloatCheck &c, const float *d_x, uint64_t n, bool nonneg,
+                        hipStream_t stream) {
+  hipError_t e = dalloc(&c.d_first, 1);
+  if (e == hipSuccess) e = launch_check_floats(d_x, n, nonneg, c.d_first, stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(&c.first, c.d_first, sizeof(uint64_t), hipMemcpyDeviceToHost, stream);
+  return e;
 }
 
 cgs_status evaluate_model(cgs_model m) {
@@ -581,10 +607,6 @@ extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth
     nodes[i] = (uint16_t)(f | ((uint16_t)thr[i] << 8));
   }
   const size_t n_leaf_vals = (size_t)n_trees * n_leaf * n_counters;
-  for (size_t i = 0; i < n_leaf_vals; ++i)
-    if (!(leaves[i] >= 0.0f) || !std::isfinite(leaves[i]))
-      return fail(CGS_EINVAL, "leaf value %zu is negative or not finite", i);
-
   cgs_model m = new (std::nothrow) cgs_model_s();
   if (!m) return fail(CGS_ENOMEM, "host allocation");
   m->space = sp;
@@ -603,15 +625,18 @@ extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth
   if (e == hipSuccess)
     e = hipMemcpyAsync(m->d_leaves, leaves, n_leaf_vals * sizeof(float), hipMemcpyHostToDevice,
                        sp->stream);
-  // padding columns of P (past n_valid) hold zeros
-  if (e == hipSuccess)
-    e = hipMemsetAsync(m->d_P, 0, (size_t)n_counters * m->stride * sizeof(float), sp->stream);
+  FloatCheck bad;
+  if (e == hipSuccess) e = check_floats(bad, m->d_leaves, n_leaf_vals, true, sp->stream);
+  if (e == hipSuccess) e = clear_padding(m);
   if (e != hipSuccess) {
     destroy_model(m);
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
                 hipGetErrorString(e));
   }
-  const cgs_status st = evaluate_model(m);
+  cgs_status st = evaluate_model(m); // synchronises
+  if (bad.first != kNoPick)
+    st = fail(CGS_EINVAL, "leaf value %llu is negative or not finite",
+              (unsigned long long)bad.first);
   if (st != CGS_OK) {
     destroy_model(m);
     return st;
@@ -706,8 +731,7 @@ extern "C" cgs_status cgs_model_fit_tree(cgs_space sp, uint64_t n, int n_counter
   if (e == hipSuccess) e = dalloc(&m->d_leaves, n_leaf_vals);
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
   if (e == hipSuccess) e = tree_fit_emit(work, depth, m->d_nodes, m->d_leaves, sp->stream);
-  if (e == hipSuccess)
-    e = hipMemsetAsync(m->d_P, 0, (size_t)n_counters * m->stride * sizeof(float), sp->stream);
+  if (e == hipSuccess) e = clear_padding(m);
   cleanup();
   if (e != hipSuccess) {
     destroy_model(m);
@@ -975,8 +999,7 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
     e = hipMemcpyAsync(d_pairs, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice,
                        sp->stream);
   if (e == hipSuccess) e = hipMemsetAsync(d_err, 0, 4, sp->stream);
-  if (e == hipSuccess)
-    e = hipMemsetAsync(m->d_P, 0, (size_t)C * m->stride * sizeof(float), sp->stream);
+  if (e == hipSuccess) e = clear_padding(m);
   hipEvent_t ev[2] = {nullptr, nullptr};
   if (e == hipSuccess) e = hipEventCreate(&ev[0]);
   if (e == hipSuccess) e = hipEventCreate(&ev[1]);
@@ -1052,9 +1075,6 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
     return fail(CGS_ERANGE, "n_counters %d outside 1..%d", n_counters, CGS_MAX_COUNTERS);
   const uint64_t nv = sp->n_valid;
   if (nv == 0) return fail(CGS_EEMPTY, "the space has no valid configuration");
-  for (uint64_t i = 0; i < nv * (uint64_t)n_counters; ++i)
-    if (!(pred_host[i] >= 0.0f) || !std::isfinite(pred_host[i]))
-      return fail(CGS_EINVAL, "prediction %llu is negative or not finite", (unsigned long long)i);
   cgs_model m = new (std::nothrow) cgs_model_s();
   if (!m) return fail(CGS_ENOMEM, "host allocation");
   m->space = sp;
@@ -1065,11 +1085,13 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
   float *d_src = nullptr;
   hipError_t e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
   if (e == hipSuccess) e = dalloc(&d_src, nv * (size_t)n_counters);
-  if (e == hipSuccess)
-    e = hipMemsetAsync(m->d_P, 0, (size_t)n_counters * m->stride * sizeof(float), sp->stream);
+  if (e == hipSuccess) e = clear_padding(m);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_src, pred_host, nv * (size_t)n_counters * sizeof(float),
                        hipMemcpyHostToDevice, sp->stream);
+  FloatCheck bad;
+  if (e == hipSuccess)
+    e = check_floats(bad, d_src, nv * (uint64_t)n_counters, true, sp->stream);
   if (e == hipSuccess)
     e = launch_rows_to_columns(d_src, (uint32_t)nv, n_counters, m->d_P, m->stride, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
@@ -1078,6 +1100,11 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
     destroy_model(m);
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "prediction table: %s",
                 hipGetErrorString(e));
+  }
+  if (bad.first != kNoPick) {
+    destroy_model(m);
+    return fail(CGS_EINVAL, "prediction %llu is negative or not finite",
+                (unsigned long long)bad.first);
   }
   *out = m;
   return CGS_OK;
@@ -1564,9 +1591,6 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
     return fail(CGS_EINVAL, "n_in %d must equal the space's %d parameters", desc->n_in,
                 sp->n_params);
   const uint64_t n = mlp_count(desc->n_in, desc->hidden, desc->n_out);
-  for (uint64_t i = 0; i < n; ++i)
-    if (!std::isfinite(params[i])) return fail(CGS_EINVAL, "parameter %llu not finite",
-                                               (unsigned long long)i);
   cgs_model m = new (std::nothrow) cgs_model_s();
   if (!m) return fail(CGS_ENOMEM, "host allocation");
   m->space = sp;
@@ -1614,7 +1638,9 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3t, 0, m->n_w3p * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w1n, 0, H * 32 * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3n, 0, m->n_w3p * sizeof(__bf16), st);
-  if (e == hipSuccess) e = hipMemsetAsync(m->d_P, 0, (size_t)C * m->stride * sizeof(float), st);
+  FloatCheck bad;
+  if (e == hipSuccess) e = check_floats(bad, m->d_theta, n, false, st);
+  if (e == hipSuccess) e = clear_padding(m);
   if (e == hipSuccess)
     e = launch_pack_weights(m->sh, m->d_theta, n, mlp_copies(m), st);
   if (e != hipSuccess) {
@@ -1622,7 +1648,9 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "perceptron buffers: %s",
                 hipGetErrorString(e));
   }
-  const cgs_status stt = evaluate_model(m);
+  cgs_status stt = evaluate_model(m); // synchronises
+  if (bad.first != kNoPick)
+    stt = fail(CGS_EINVAL, "parameter %llu not finite", (unsigned long long)bad.first);
   if (stt != CGS_OK) {
     destroy_model(m);
     return stt;

@@ -7,6 +7,13 @@
 
 namespace cgs {
 
+// *first = the lowest position of a value of x[0..n) that is not finite (or
+// negative, with nonneg), ~0 when there is none.
+hipError_t launch_check_floats(const float *x, uint64_t n, bool nonneg, uint64_t *first,
+                               hipStream_t stream);
+// Zeros columns from..stride-1 of P[c][stride], c < C.
+hipError_t launch_clear_columns(float *P, uint64_t stride, int C, uint64_t from,
+                                hipStream_t stream);
 // Predictions given per configuration, src[l][C], into the model layout
 // P[c][stride].
 hipError_t launch_rows_to_columns(const float *d_src, uint32_t n, int C, float *d_P,
