@@ -31,6 +31,7 @@ COMMON = [
 # source -> extra flags
 SOURCES = {
     "capi.hip": ["-ffp-contract=off"],
+    "pool.cpp": ["-x", "hip"],
     "expert.cpp": ["-ffp-contract=off", "-x", "hip"],
     "enumerate.hip": ["-ffp-contract=off"],
     "forest.hip": ["-ffp-contract=off"],

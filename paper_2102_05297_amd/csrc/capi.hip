@@ -17,6 +17,7 @@
 #include "cgs.h"
 #include "internal.h"
 #include "models.h"
+#include "pool.h"
 
 using namespace cgs;
 
@@ -44,12 +45,30 @@ cgs_status fail(cgs_status st, const char *fmt, ...) {
   } while (0)
 
 template <typename T> hipError_t dalloc(T **p, size_t n) {
-  *p = nullptr;
-  if (n == 0) n = 1;
-  return hipMalloc(reinterpret_cast<void **>(p), n * sizeof(T));
+  void *q = nullptr;
+  const hipError_t e = pool::device_get(&q, std::max<size_t>(n, 1) * sizeof(T));
+  *p = static_cast<T *>(q);
+  return e;
 }
+// The work that used the block has finished (see settle).
 template <typename T> void dfree(T *&p) {
-  if (p) (void)hipFree(p);
+  pool::device_put(p);
+  p = nullptr;
+}
+// Before temporary blocks are put back: after an error, work may still be
+// enqueued that uses them (without one, the caller has synchronised).
+void settle(hipError_t e, hipStream_t stream) {
+  if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+}
+template <typename T> hipError_t palloc(T **host, T **dev, size_t n) {
+  void *h = nullptr, *d = nullptr;
+  const hipError_t e = pool::pinned_get(&h, &d, n * sizeof(T));
+  *host = static_cast<T *>(h);
+  if (dev) *dev = static_cast<T *>(d);
+  return e;
+}
+template <typename T> void pfree(T *&p) {
+  pool::pinned_put(p);
   p = nullptr;
 }
 
@@ -262,9 +281,10 @@ void destroy_space(cgs_space sp) {
   dfree(sp->d_mask);
   dfree(sp->d_idx);
   dfree(sp->d_rank);
-  if (sp->h_res) (void)hipHostFree(sp->h_res);
-  if (sp->own_stream && sp->stream) (void)hipStreamDestroy(sp->stream);
+  pfree(sp->h_res);
+  if (sp->own_stream) pool::stream_put(sp->stream);
   delete sp;
+  pool::detach();
 }
 
 } // namespace
@@ -321,6 +341,7 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
 
   cgs_space sp = new (std::nothrow) cgs_space_s();
   if (!sp) return fail(CGS_ENOMEM, "host allocation");
+  pool::attach();
   sp->n_params = n_params;
   sp->radix.assign(radix, radix + n_params);
   sp->n_raw = n_raw;
@@ -341,27 +362,27 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
   if (hip_stream) {
     sp->stream = reinterpret_cast<hipStream_t>(hip_stream);
   } else {
-    SP_TRY(hipStreamCreateWithFlags(&sp->stream, hipStreamNonBlocking));
     sp->own_stream = true;
+    SP_TRY(pool::stream_get(&sp->stream));
   }
   SP_TRY(dalloc(&sp->d_desc, 1));
   SP_TRY(dalloc(&sp->d_mask, desc.n_words));
   SP_TRY(dalloc(&sp->d_rank, desc.n_words));
-  SP_TRY(hipHostMalloc(reinterpret_cast<void **>(&sp->h_res), sizeof(DrawResult),
-                       hipHostMallocMapped));
-  SP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&sp->d_res), sp->h_res, 0));
+  SP_TRY(palloc(&sp->h_res, &sp->d_res, 1));
   const uint32_t n_tiles = enumeration_tiles((uint32_t)n_raw);
   uint32_t *d_tile_count = nullptr, *d_tile_off = nullptr;
   uint64_t *d_total = nullptr;
-  SP_TRY(dalloc(&d_tile_count, n_tiles));
-  SP_TRY(dalloc(&d_tile_off, n_tiles));
-  SP_TRY(dalloc(&d_total, 1));
+  hipError_t e = dalloc(&d_tile_count, n_tiles);
+  if (e == hipSuccess) e = dalloc(&d_tile_off, n_tiles);
+  if (e == hipSuccess) e = dalloc(&d_total, 1);
   auto free_tmp = [&]() {
+    settle(e, sp->stream);
     dfree(d_tile_count);
     dfree(d_tile_off);
     dfree(d_total);
   };
-  hipError_t e = hipMemcpyAsync(sp->d_desc, &desc, sizeof(desc), hipMemcpyHostToDevice, sp->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sp->d_desc, &desc, sizeof(desc), hipMemcpyHostToDevice, sp->stream);
   if (e == hipSuccess)
     e = launch_enumeration(sp->d_desc, (uint32_t)n_raw, sp->d_mask, d_tile_count, d_tile_off,
                            d_total, nullptr, nullptr, 0, sp->stream);
@@ -378,6 +399,7 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
     try {
       sp->h_idx.resize(n_valid);
     } catch (...) {
+      (void)hipStreamSynchronize(sp->stream);
       free_tmp();
       return guard(fail(CGS_ENOMEM, "host copy of the valid list"));
     }
@@ -1095,6 +1117,7 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
   if (e == hipSuccess)
     e = launch_rows_to_columns(d_src, (uint32_t)nv, n_counters, m->d_P, m->stride, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_src);
   if (e != hipSuccess) {
     destroy_model(m);
@@ -1348,6 +1371,7 @@ extern "C" cgs_status cgs_model_gather_predictions(cgs_model m, const uint32_t *
     e = hipMemcpyAsync(dst, d_out, n * (uint64_t)m->n_counters * sizeof(float),
                        hipMemcpyDeviceToHost, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_idx);
   dfree(d_out);
   if (e != hipSuccess)
@@ -1381,6 +1405,7 @@ extern "C" cgs_status cgs_model_rmse(cgs_model a, cgs_model b, const uint32_t *s
     e = hipMemcpyAsync(part.data(), d_part, grid * sizeof(double), hipMemcpyDeviceToHost,
                        sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_s);
   dfree(d_part);
   if (e != hipSuccess) return fail(CGS_EDEVICE, "rmse: %s", hipGetErrorString(e));
@@ -1407,6 +1432,7 @@ extern "C" cgs_status cgs_model_copy_leaf_ids(cgs_model m, uint64_t first, uint6
     e = hipMemcpyAsync(dst, d_out, (size_t)m->n_trees * count * sizeof(uint16_t),
                        hipMemcpyDeviceToHost, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_out);
   if (e != hipSuccess) return fail(CGS_EDEVICE, "leaf ids: %s", hipGetErrorString(e));
   return CGS_OK;
@@ -1427,6 +1453,7 @@ uint64_t mlp_count(int F, int H, int C) {
 
 hipError_t ensure_mlp_scratch(cgs_model m, uint32_t rows) {
   if (m->scratch_rows >= rows) return hipSuccess;
+  if (m->scratch_rows) (void)hipStreamSynchronize(m->space->stream);
   free_mlp_scratch(m);
   const size_t H = m->sh.H, Cp = (size_t)32 * ((m->sh.C + 31) / 32);
   const size_t n_pad = ((size_t)rows + 31) / 32 * 32, nblk = n_pad / 16; // 16-row blocks
@@ -1704,6 +1731,7 @@ cgs_status mlp_train_run(cgs_model m, const uint32_t *cfg, const float *targets,
   if (e == hipSuccess && loss_host && o->steps > 0)
     e = hipMemcpyAsync(loss_host, d_loss, o->steps * sizeof(float), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
+  settle(e, st);
   dfree(d_cfg);
   dfree(d_t);
   dfree(d_batch);
@@ -1743,6 +1771,7 @@ extern "C" cgs_status cgs_mlp_gradients(cgs_model m, const uint32_t *cfg, const 
     e = hipMemcpyAsync(grads, m->d_grad, m->n_theta * sizeof(float), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipMemcpyAsync(&loss, d_loss, sizeof(float), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
+  settle(e, st);
   dfree(d_cfg);
   dfree(d_t);
   dfree(d_loss);
@@ -1768,6 +1797,7 @@ extern "C" cgs_status cgs_mlp_forward(cgs_model m, const uint32_t *cfg, uint32_t
   if (e == hipSuccess)
     e = hipMemcpyAsync(rows.data(), m->d_y, rows.size() * sizeof(float), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
+  settle(e, st);
   dfree(d_cfg);
   if (e != hipSuccess) return fail(CGS_EDEVICE, "forward: %s", hipGetErrorString(e));
   for (uint32_t i = 0; i < n; ++i)
@@ -1809,9 +1839,7 @@ void destroy_session(cgs_session s) {
   dfree(s->d_nb_stats);
   dfree(s->d_nb_acc);
   dfree(s->d_prof);
-  if (s->h_res) (void)hipHostFree(s->h_res);
-  if (s->h_acc) (void)hipHostFree(s->h_acc);
-  if (s->h_ring) (void)hipHostFree(s->h_ring);
+  pfree(s->h_ring); // h_res and h_acc are parts of its block
   for (hipEvent_t ev : s->t_ev)
     if (ev) (void)hipEventDestroy(ev);
   destroy_space(s->space);
@@ -2084,22 +2112,16 @@ extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params,
   if (e == hipSuccess) e = dalloc(&s->d_s, stride);
   if (e == hipSuccess) e = dalloc(&s->d_bsum, s->n_blocks);
   if (e == hipSuccess) e = dalloc(&s->d_acc, 2 * kAccSlots);
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void **>(&s->h_res), sizeof(DrawResult),
-                      hipHostMallocMapped | hipHostMallocCoherent);
-  if (e == hipSuccess) {
-    std::memset(s->h_res, 0, sizeof(DrawResult));
-    e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->d_res), s->h_res, 0);
-  }
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void **>(&s->h_acc), kAccSlots * sizeof(StepAcc), 0);
   if (e == hipSuccess) e = dalloc(&s->d_prof, 2);
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void **>(&s->h_ring), kResultRing * sizeof(DrawResult),
-                      hipHostMallocMapped | hipHostMallocCoherent);
+  // one pinned block: the ring, the single result, the accumulators' copy
+  static_assert(alignof(StepAcc) <= sizeof(DrawResult), "the copy follows the results");
+  constexpr size_t kAccUnits = (kAccSlots * sizeof(StepAcc) + sizeof(DrawResult) - 1) / sizeof(DrawResult);
+  if (e == hipSuccess) e = palloc(&s->h_ring, &s->d_ring, kResultRing + 1 + kAccUnits);
   if (e == hipSuccess) {
-    std::memset(s->h_ring, 0, kResultRing * sizeof(DrawResult));
-    e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->d_ring), s->h_ring, 0);
+    std::memset(s->h_ring, 0, (kResultRing + 1) * sizeof(DrawResult));
+    s->h_res = s->h_ring + kResultRing;
+    s->d_res = s->d_ring + kResultRing;
+    s->h_acc = reinterpret_cast<StepAcc *>(s->h_ring + kResultRing + 1);
   }
   if (e == hipSuccess && p.timing > 0) {
     s->t_ev.assign(kTimeEvents, nullptr);
@@ -2107,12 +2129,11 @@ extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params,
     for (uint32_t i = 0; i < kTimeEvents && e == hipSuccess; ++i)
       e = hipEventCreateWithFlags(&s->t_ev[i], hipEventDisableSystemFence);
   }
+  // nothing explored, no scores, neutral accumulators: every use of the
+  // session follows on this stream (a batch waits for it first)
   if (e == hipSuccess)
-    e = hipMemsetAsync(s->d_explored, 0, std::max<uint64_t>(n_words, 1) * sizeof(uint32_t),
-                       sp->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(s->d_s, 0, stride * sizeof(float), sp->stream);
-  if (e == hipSuccess) e = launch_reset_acc(s->d_acc, 2 * kAccSlots, sp->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+    e = launch_session_init(s->d_explored, std::max<uint64_t>(n_words, 1), s->d_s, stride, s->d_acc,
+                            2 * kAccSlots, sp->stream);
   if (e != hipSuccess) {
     destroy_session(s);
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "session buffers: %s",
@@ -2189,6 +2210,7 @@ cgs_status build_subsets(cgs_session s, int radius, uint32_t *n_subsets, uint32_
                 (unsigned long long)run, kNbMaxCandidates);
   if (run == 0) return fail(CGS_EEMPTY, "the neighbourhood of radius %d is empty", radius);
   const uint32_t n = (uint32_t)code.size();
+  if (s->d_sub_off) (void)hipStreamSynchronize(s->space->stream); // the last table's steps
   dfree(s->d_sub_off);
   dfree(s->d_sub_code);
   s->nb_radius = 0;
@@ -2398,6 +2420,7 @@ cgs_status mlp_sample_rmse(cgs_model mlp, cgs_model tree, const uint32_t *sample
     e = hipMemcpyAsync(part.data(), d_part, grid * sizeof(double), hipMemcpyDeviceToHost,
                        sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_s);
   dfree(d_raw);
   dfree(d_p);
@@ -2761,6 +2784,7 @@ extern "C" cgs_status cgs_session_copy_weights(cgs_session s, uint64_t first, ui
   if (e == hipSuccess)
     e = hipMemcpyAsync(dst, d_q, count * sizeof(uint32_t), hipMemcpyDeviceToHost, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+  settle(e, sp->stream);
   dfree(d_q);
   if (e != hipSuccess) return fail(CGS_EDEVICE, "weights: %s", hipGetErrorString(e));
   return CGS_OK;
@@ -2821,11 +2845,11 @@ void destroy_batch(cgs_batch b) {
   dfree(b->d_step);
   dfree(b->d_tile_sess);
   dfree(b->d_blk_sess);
-  if (b->h_step) (void)hipHostFree(b->h_step);
-  if (b->h_res) (void)hipHostFree(b->h_res);
+  pfree(b->h_step);
+  pfree(b->h_res);
   if (b->e0) (void)hipEventDestroy(b->e0);
   if (b->e1) (void)hipEventDestroy(b->e1);
-  if (b->stream) (void)hipStreamDestroy(b->stream);
+  pool::stream_put(b->stream);
   delete b;
 }
 
@@ -2924,17 +2948,13 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     for (uint32_t t = 0; t < nt; ++t) tile_sess[desc[i].tile0 + t] = (uint16_t)i;
     for (uint32_t t = 0; t < desc[i].n_blocks; ++t) blk_sess[desc[i].blk0 + t] = (uint16_t)i;
   }
-  hipError_t e = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking);
+  hipError_t e = pool::stream_get(&b->stream);
   if (e == hipSuccess) e = dalloc(&b->d_sess, n);
   if (e == hipSuccess) e = dalloc(&b->d_step, n);
   if (e == hipSuccess) e = dalloc(&b->d_tile_sess, tile_sess.size());
   if (e == hipSuccess) e = dalloc(&b->d_blk_sess, blk_sess.size());
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void **>(&b->h_step), (size_t)n * sizeof(BatchStep), 0);
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void **>(&b->h_res), (size_t)n * sizeof(DrawResult),
-                      hipHostMallocMapped);
-  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&b->d_res), b->h_res, 0);
+  if (e == hipSuccess) e = palloc<BatchStep>(&b->h_step, nullptr, (size_t)n);
+  if (e == hipSuccess) e = palloc(&b->h_res, &b->d_res, (size_t)n);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->e0, hipEventDisableSystemFence);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->e1, hipEventDisableSystemFence);
   if (e == hipSuccess) {
@@ -3475,12 +3495,13 @@ extern "C" cgs_status cgs_sample_weights(cgs_space sp, const uint32_t *q, uint64
   const uint32_t n_blocks = (uint32_t)((n + (1ull << lg) - 1) >> lg);
   uint32_t *d_q = nullptr;
   uint64_t *d_bsum = nullptr;
-  HIP_TRY(dalloc(&d_q, (n + 63) & ~(uint64_t)63)); // whole runs of draw weights
-  hipError_t e = dalloc(&d_bsum, n_blocks);
+  hipError_t e = dalloc(&d_q, (n + 63) & ~(uint64_t)63); // whole runs of draw weights
+  if (e == hipSuccess) e = dalloc(&d_bsum, n_blocks);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_q, q, n * sizeof(uint32_t), hipMemcpyHostToDevice, sp->stream);
   cgs_status r = e == hipSuccess ? sample_resident(sp, d_q, n, lg, d_bsum, n_blocks, u64, n_draws, picks)
                                  : fail(CGS_EDEVICE, "sampler: %s", hipGetErrorString(e));
+  if (r != CGS_OK) (void)hipStreamSynchronize(sp->stream);
   dfree(d_q);
   dfree(d_bsum);
   return r;

@@ -177,6 +177,8 @@ hipError_t launch_gather_rows(const float *P, uint64_t stride, int n_counters,
 hipError_t launch_sq_diff(const float *Pa, const float *Pb, uint64_t stride_a, uint64_t stride_b,
                           int n_counters, const uint32_t *sample, uint32_t n, double *partial,
                           uint32_t grid, hipStream_t stream);
+hipError_t launch_session_init(uint32_t *d_explored, uint64_t n_words, float *d_s,
+                               uint64_t stride, StepAcc *d_acc, int n_acc, hipStream_t stream);
 hipError_t launch_reset_acc(StepAcc *d_acc, int n, hipStream_t stream);
 // The step's kernels take the profiled configuration's valid index either
 // as `profile` or, when d_prof is given, from device memory (the previous

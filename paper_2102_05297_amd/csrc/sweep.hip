@@ -1122,7 +1122,29 @@ __global__ __launch_bounds__(64) void reset_acc(StepAcc *__restrict__ acc, int n
   }
 }
 
+// A new session: nothing explored, scores 0, neutral accumulators.
+__global__ __launch_bounds__(256) void session_init(uint32_t *__restrict__ explored,
+                                                    uint64_t n_words, float *__restrict__ s,
+                                                    uint64_t stride, StepAcc *__restrict__ acc,
+                                                    int n_acc) {
+  const uint64_t i0 = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+  for (uint64_t i = i0; i < stride / 4; i += step) // stride is a multiple of 64
+    reinterpret_cast<float4 *>(s)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (uint64_t i = i0; i < n_words; i += step) explored[i] = 0u;
+  for (uint64_t i = i0; i < (uint64_t)n_acc; i += step)
+    acc[i] = StepAcc{0xffffffffu, 0u, 0u, 0u};
+}
+
 } // namespace
+
+hipError_t launch_session_init(uint32_t *d_explored, uint64_t n_words, float *d_s,
+                               uint64_t stride, StepAcc *d_acc, int n_acc, hipStream_t stream) {
+  const uint64_t items = std::max<uint64_t>({stride / 4, n_words, (uint64_t)n_acc});
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(2048, (items + 255) / 256);
+  hipLaunchKernelGGL(session_init, dim3(grid), dim3(256), 0, stream, d_explored, n_words, d_s,
+                     stride, d_acc, n_acc);
+  return hipGetLastError();
+}
 
 hipError_t launch_reset_acc(StepAcc *d_acc, int n, hipStream_t stream) {
   hipLaunchKernelGGL(reset_acc, dim3(1), dim3(64), 0, stream, d_acc, n);

@@ -46,6 +46,7 @@
 
 #include "device_common.h"
 #include "models.h"
+#include "pool.h"
 
 namespace cgs {
 
@@ -1271,11 +1272,13 @@ hipError_t tree_fit_run(const TreeFitIn &in, TreeFitOut &out, TreeFitWork **work
     o_slot[s] = take(level_cap * 4);
   }
   char *base = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&base), off);
+  void *block = nullptr;
+  hipError_t e = pool::device_get(&block, off);
+  base = static_cast<char *>(block);
   if (e != hipSuccess) return e;
   TreeFitWork *w = new (std::nothrow) TreeFitWork();
   if (!w) {
-    (void)hipFree(base);
+    pool::device_put(base);
     return hipErrorOutOfMemory;
   }
   w->base = base;
@@ -1434,7 +1437,7 @@ hipError_t tree_fit_emit(const TreeFitWork *w, int depth, uint16_t *d_nodes, flo
 
 void tree_fit_release(TreeFitWork *w) {
   if (!w) return;
-  if (w->base) (void)hipFree(w->base);
+  pool::device_put(w->base); // its stream has been synchronised
   delete w;
 }
 
