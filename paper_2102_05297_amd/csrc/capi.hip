@@ -1933,6 +1933,45 @@ hipError_t launch_pending_nb(cgs_session s, bool do_draw, uint64_t u64) {
   const uint32_t nv = (uint32_t)sp->n_valid;
   const bool timed = s->params.timing > 0 && s->n_launched % (uint64_t)s->params.timing == 0;
   hipError_t e = hipSuccess;
+  // one launch for the neighbourhoods it takes, without timing (whose markers
+  // stand between the kernels)
+  if (s->params.timing == 0 && st.total <= kNbFusedMax) {
+    NbFused a{};
+    a.st = st;
+    a.sub_off = s->d_sub_off;
+    a.sub_code = s->d_sub_code;
+    a.mask = sp->d_mask;
+    a.rank = sp->d_rank;
+    a.idx = sp->d_idx;
+    a.explored = s->d_explored;
+    a.P = m->d_P;
+    a.stride = m->stride;
+    a.n_valid = nv;
+    a.draw = do_draw ? 1 : 0;
+    a.tmp_idx = s->d_nb_tmp_idx;
+    a.tmp_s = s->d_nb_tmp_s;
+    a.acc = s->d_nb_acc;
+    a.gamma = s->params.gamma;
+    a.w_min = s->params.w_min;
+    a.nb_idx = s->d_nb_idx;
+    a.nb_q = s->d_nb_q;
+    a.nb_s = s->d_nb_s;
+    a.bsum = s->d_nb_bsum;
+    a.stats = s->d_nb_stats;
+    a.u64 = u64;
+    a.res = s->d_res;
+    a.seq = s->seq + 1;
+    e = launch_nb_step(a, sp->stream);
+    if (e != hipSuccess) return e;
+    if (do_draw) ++s->seq;
+    ++s->n_launched;
+    s->step_timed = false;
+    s->ran_in_batch = false;
+    s->last_nb = true;
+    s->pending = false;
+    s->pending_nb = false;
+    return hipSuccess;
+  }
   TimedSpan *span = nullptr;
   if (timed) {
     const int kinds[2] = {4, do_draw ? 2 : 3};

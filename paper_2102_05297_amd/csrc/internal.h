@@ -95,6 +95,34 @@ struct NbStats {
   uint32_t min_key, max_key;
 };
 
+// A whole restricted step (score, compaction, weights, one draw with `draw`,
+// the profile marked explored) of 1 .. kNbFusedMax neighbours in one launch.
+// acc: kAccSlots neutral slots, acc[0].pad the workgroups' meeting counter (0
+// between launches).
+constexpr uint32_t kNbFusedMax = 8192;
+constexpr uint32_t kNbFusedBlocks = kNbFusedMax >> kNbBlockLog2;
+struct NbFused {
+  NbStep st;
+  const uint32_t *sub_off, *sub_code, *mask, *rank, *idx;
+  uint32_t *explored;
+  const float *P;
+  uint64_t stride;
+  uint32_t n_valid;
+  int32_t draw;
+  uint32_t *tmp_idx;
+  float *tmp_s;
+  StepAcc *acc;
+  float gamma, w_min;
+  uint32_t *nb_idx, *nb_q;
+  float *nb_s;
+  uint64_t *bsum;
+  NbStats *stats;
+  uint64_t u64;
+  DrawResult *res;
+  uint64_t seq;
+};
+hipError_t launch_nb_step(const NbFused &a, hipStream_t stream);
+
 // ---- batched sessions: one descriptor per session (device memory) and one
 // step record per session (refreshed from pinned memory before each step)
 struct BatchSess {

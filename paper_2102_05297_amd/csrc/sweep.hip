@@ -926,6 +926,43 @@ __global__ __launch_bounds__(kDrawThreads) void batch_draw(const BatchSess *__re
 constexpr int kNbThreads = 256;
 constexpr uint32_t kNbMaxSubsets = 32 + 32 * 31 / 2 + 32 * 31 * 30 / 6; // radius <= 3
 
+// Raw index of candidate f: its subset of changed parameters (the last one
+// whose first candidate <= f) by binary search of off, then the new digits.
+__device__ __forceinline__ uint32_t nb_unrank(const NbStep &st, const uint32_t *off,
+                                              const uint32_t *__restrict__ sub_code, uint32_t f) {
+  uint32_t lo = 0, hi = st.n_subsets;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (off[mid] <= f) lo = mid;
+    else hi = mid;
+  }
+  const uint32_t code = sub_code[lo];
+  uint32_t u = f - off[lo];
+  int64_t raw = st.profile_raw;
+  // new digits of the changed parameters, the last one fastest; the
+  // profile's own digit is skipped
+  for (int k = (int)(code >> 24) - 1; k >= 0; --k) {
+    const uint32_t j = (code >> (8 * k)) & 0xffu;
+    const uint32_t alt = st.radix[j] - 1u;
+    const uint32_t a = u % alt;
+    u /= alt;
+    const uint32_t pd = st.pdig[j];
+    const uint32_t v = a < pd ? a : a + 1u;
+    raw += ((int64_t)v - (int64_t)pd) * (int64_t)st.stride[j];
+  }
+  return (uint32_t)raw;
+}
+// Whether raw index rw is valid and unexplored; l receives its valid index
+// when it is valid.
+__device__ __forceinline__ bool nb_keep(uint32_t rw, const uint32_t *__restrict__ mask,
+                                        const uint32_t *__restrict__ rank,
+                                        const uint32_t *__restrict__ explored, uint32_t &l) {
+  const uint32_t word = mask[rw >> 5], rk = rank[rw >> 5];
+  if (!((word >> (rw & 31u)) & 1u)) return false;
+  l = rk + (uint32_t)__popc(word & ((1u << (rw & 31u)) - 1u));
+  return !((explored[l >> 5] >> (l & 31u)) & 1u);
+}
+
 __global__ __launch_bounds__(kNbThreads) void nb_score(
     NbStep st, const uint32_t *__restrict__ sub_off, const uint32_t *__restrict__ sub_code,
     const uint32_t *__restrict__ mask, const uint32_t *__restrict__ rank,
@@ -940,35 +977,9 @@ __global__ __launch_bounds__(kNbThreads) void nb_score(
   uint32_t kmin = 0xffffffffu, kmax = 0u, cnt = 0u;
   const uint32_t f = blockIdx.x * kNbThreads + threadIdx.x;
   if (f < st.total) {
-    // subset holding candidate f: the last one whose first candidate <= f
-    uint32_t lo = 0, hi = st.n_subsets;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (off_lds[mid] <= f) lo = mid;
-      else hi = mid;
-    }
-    const uint32_t code = sub_code[lo];
-    uint32_t u = f - off_lds[lo];
-    int64_t raw = st.profile_raw;
-    // new digits of the changed parameters, the last one fastest; the
-    // profile's own digit is skipped
-    for (int k = (int)(code >> 24) - 1; k >= 0; --k) {
-      const uint32_t j = (code >> (8 * k)) & 0xffu;
-      const uint32_t alt = st.radix[j] - 1u;
-      const uint32_t a = u % alt;
-      u /= alt;
-      const uint32_t pd = st.pdig[j];
-      const uint32_t v = a < pd ? a : a + 1u;
-      raw += ((int64_t)v - (int64_t)pd) * (int64_t)st.stride[j];
-    }
-    const uint32_t rw = (uint32_t)raw;
-    const uint32_t word = mask[rw >> 5], rk = rank[rw >> 5];
-    bool keep = (word >> (rw & 31u)) & 1u;
+    const uint32_t rw = nb_unrank(st, off_lds, sub_code, f);
     uint32_t l = 0;
-    if (keep) {
-      l = rk + (uint32_t)__popc(word & ((1u << (rw & 31u)) - 1u));
-      keep = !((explored[l >> 5] >> (l & 31u)) & 1u);
-    }
+    const bool keep = nb_keep(rw, mask, rank, explored, l);
     float s = 0.0f;
     if (keep) {
       for (int j0 = 0; j0 < st.act.n; j0 += kRowsInFlight) {
@@ -1067,6 +1078,208 @@ __global__ __launch_bounds__(kDrawThreads) void nb_draw(
   __syncthreads();
   if (threadIdx.x == 0 && mark_profile && profile < n_valid)
     atomicOr(&explored[profile >> 5], 1u << (profile & 31u));
+}
+
+// A whole restricted step of at most kNbFusedMax neighbours in one launch:
+// the candidates are scored, and the workgroup that finishes last compacts
+// and weighs the kept ones and makes the step's first draw.
+// Bound: latency.  The separate launches are three kernel starts with their
+// chains of dependent round trips; and the gather of a candidate's counters
+// touches one page of the predictions per counter and candidate, so two
+// workgroups (476 candidates of radius 2 in a space of 16 parameters) wait on
+// address translation in two of the eight dies.  Here LP threads share a
+// candidate's counters (their terms meet in LDS and are added in counter
+// order), which spreads the gather over LP times as many workgroups.
+// The workgroups meet as those of small_step do.
+// Measured (32 active counters, 27.7M configurations): 476 neighbours 13.1 us
+// with 16 threads a candidate, 14.2 us with 8, 25.9 us as three launches
+// (18.5 of them the scores on two workgroups); a step with its draw 21.8
+// against 35.7 us, 19.8 against 28.1 us at radius 1, 39.9 against 42.0 us
+// with 5,134 candidates (the one workgroup's compaction grows with them,
+// hence the limit).
+template <int LP>
+__global__ __launch_bounds__(kNbThreads) void nb_step(NbFused a) {
+  constexpr uint32_t kCands = kNbThreads / LP; // candidates per workgroup
+  constexpr int kMine = CGS_MAX_COUNTERS / LP < 16 ? CGS_MAX_COUNTERS / LP : 16;
+  extern __shared__ uint32_t nb_lds[];
+  __shared__ float a_lds[CGS_MAX_COUNTERS];
+  __shared__ uint32_t red[3][kNbThreads / kWave];
+  __shared__ uint32_t arrived;
+  __shared__ uint64_t scratch[kNbThreads / kWave];
+  __shared__ StepAccSums sums;
+  __shared__ unsigned long long blk_sum[kNbFusedBlocks];
+  const NbStep &st = a.st;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const int n = st.act.n;
+  // scoring: the subset tables, then one row of terms per candidate
+  uint32_t *off = nb_lds, *code = off + st.n_subsets + 1;
+  float *terms = reinterpret_cast<float *>(code + st.n_subsets);
+  for (uint32_t i = tid; i <= st.n_subsets; i += kNbThreads) off[i] = a.sub_off[i];
+  for (uint32_t i = tid; i < st.n_subsets; i += kNbThreads) code[i] = a.sub_code[i];
+  if (tid < (uint32_t)n) a_lds[tid] = a.P[(size_t)st.act.ctr[tid] * a.stride + st.profile];
+  __syncthreads();
+  const uint32_t cand = tid / LP, part = tid % LP;
+  const uint32_t f = blockIdx.x * kCands + cand;
+  uint32_t l = 0;
+  bool keep = false;
+  if (f < st.total) keep = nb_keep(nb_unrank(st, off, code, f), a.mask, a.rank, a.explored, l);
+  if (keep) {
+    for (int j0 = (int)part; j0 < n; j0 += LP * kMine) {
+      float x[kMine];
+#pragma unroll
+      for (int u = 0; u < kMine; ++u) {
+        const int j = min(j0 + u * LP, n - 1);
+        x[u] = a.P[(size_t)st.act.ctr[j] * a.stride + l];
+      }
+#pragma unroll
+      for (int u = 0; u < kMine; ++u) {
+        const int j = j0 + u * LP;
+        if (j < n) {
+          // a term outside PC_used is 0: the running sum is never -0, so
+          // adding it changes nothing
+          const float ap = a_lds[j];
+          const float t = (x[u] - ap) / (ap + x[u]);
+          terms[cand * (uint32_t)(n | 1) + j] =
+              (ap != 0.0f && x[u] != 0.0f) ? st.act.delta[j] * t : 0.0f;
+        }
+      }
+    }
+  }
+  lds_barrier();
+  uint32_t kmin = 0xffffffffu, kmax = 0u;
+  const bool scored = keep && part == 0;
+  float s = 0.0f;
+  if (scored) {
+    for (int j = 0; j < n; ++j) s = s + terms[cand * (uint32_t)(n | 1) + j];
+    kmin = kmax = float_key(s);
+  }
+  if (part == 0 && f < st.total) {
+    a.tmp_idx[f] = keep ? l : kNoIndex;
+    a.tmp_s[f] = s;
+  }
+  kmin = wave_umin(kmin);
+  kmax = wave_umax(kmax);
+  const uint32_t cnt = (uint32_t)__popcll(__ballot(scored));
+  if (lane == 0) {
+    red[0][tid >> 6] = kmin;
+    red[1][tid >> 6] = kmax;
+    red[2][tid >> 6] = cnt;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    StepAcc slot{red[0][0], red[1][0], red[2][0], 0u};
+#pragma unroll
+    for (int w = 1; w < kNbThreads / kWave; ++w) {
+      slot.min_key = min(slot.min_key, red[0][w]);
+      slot.max_key = max(slot.max_key, red[1][w]);
+      slot.n_unexplored += red[2][w];
+    }
+    a.acc[blockIdx.x].min_key = slot.min_key;
+    a.acc[blockIdx.x].max_key = slot.max_key;
+    a.acc[blockIdx.x].n_unexplored = slot.n_unexplored;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    arrived = atomicAdd(&a.acc[0].pad, 1u);
+  }
+  __syncthreads();
+  if (arrived != gridDim.x - 1) return; // uniform over the workgroup
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+
+  // compaction: thread t takes the run of `per` candidates from t * per
+  const uint32_t per = (st.total + kNbThreads - 1) / kNbThreads, ld = per | 1u;
+  uint32_t *cq = nb_lds, *ci = cq + kNbThreads * ld; // the runs' weights and valid indices
+  const uint32_t f0 = min(st.total, tid * per), f1 = min(st.total, f0 + per);
+  StepAcc slot{};
+  if (tid < kWave) slot = a.acc[tid];
+  constexpr uint32_t kChunk = 8;
+  uint32_t kept = 0;
+  for (uint32_t c = 0; c < per; c += kChunk) {
+    uint32_t v[kChunk];
+    float sv[kChunk];
+#pragma unroll
+    for (uint32_t k = 0; k < kChunk; ++k) {
+      const uint32_t at = min(f0 + c + k, st.total - 1);
+      v[k] = a.tmp_idx[at];
+      sv[k] = a.tmp_s[at];
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kChunk; ++k) {
+      if (c + k >= per) break;
+      const bool in = f0 + c + k < f1 && v[k] != kNoIndex;
+      ci[tid * ld + c + k] = in ? v[k] : kNoIndex;
+      cq[tid * ld + c + k] = __float_as_uint(sv[k]); // its weight below
+      kept += in;
+    }
+  }
+  reduce_slot_values(slot, &sums);
+  if (tid < kNbFusedBlocks) blk_sum[tid] = 0ull;
+  uint64_t count;
+  const uint32_t pos0 =
+      (uint32_t)block_excl_scan<kNbThreads, true>(kept, scratch, count); // publishes sums
+  const StepNorm nm =
+      step_norm(key_float(sums.min_key), key_float(sums.max_key), a.gamma, a.w_min);
+  uint64_t mine = 0;
+  uint32_t pos = pos0;
+  for (uint32_t k = 0; k < per; ++k) {
+    const uint32_t v = ci[tid * ld + k];
+    const float sv = __uint_as_float(cq[tid * ld + k]);
+    const uint32_t q = quantized_weight(sv, v == kNoIndex, nm);
+    cq[tid * ld + k] = q;
+    if (v != kNoIndex) {
+      a.nb_idx[pos] = v;
+      a.nb_s[pos] = sv;
+      mine += q;
+      ++pos;
+    }
+  }
+  uint64_t Q;
+  const uint64_t pre = block_excl_scan<kNbThreads, true>(mine, scratch, Q);
+  if (tid == 0) {
+    a.stats->count = (uint32_t)count;
+    a.stats->total = Q;
+    a.stats->min_key = sums.min_key;
+    a.stats->max_key = sums.max_key;
+    a.acc[0].pad = 0u;
+    if (a.draw && Q == 0) publish(a.res, kNoIndex, kNoIndex, 0, a.seq);
+  }
+  const uint64_t r = __umul64hi(a.u64, Q);
+  const bool owner = a.draw && pre <= r && r < pre + mine;
+  const uint64_t own = __ballot(owner);
+  if (own != 0) { // the owner's wave looks through its run, one candidate per lane
+    const int o = __ffsll((unsigned long long)own) - 1;
+    const uint32_t run = (tid & ~63u) + (uint32_t)o;
+    const uint64_t rem = (uint64_t)__shfl((long long)(r - pre), o);
+    const uint64_t w = lane < per ? cq[run * ld + lane] : 0u;
+    const uint32_t v = lane < per ? ci[run * ld + lane] : kNoIndex;
+    const uint64_t incl = wave_incl_scan(w);
+    const bool hit = rem < incl && incl - w <= rem; // one lane
+    if (hit) {
+      publish(a.res, v, a.idx[v], Q, a.seq);
+      cq[run * ld + lane] = 0u;
+      atomicOr(&a.explored[v >> 5], 1u << (v & 31u));
+    }
+    const uint64_t who = __ballot(hit);
+    const uint64_t ql = (uint64_t)__shfl((long long)w, __ffsll((unsigned long long)who) - 1);
+    if (owner) mine -= ql;
+  }
+  // the weights the draw left and their block sums, by position among the
+  // kept
+  const uint32_t b0 = pos0 >> kNbBlockLog2;
+  uint64_t lower = 0;
+  pos = pos0;
+  for (uint32_t k = 0; k < per; ++k) {
+    if (ci[tid * ld + k] == kNoIndex) continue;
+    const uint32_t q = cq[tid * ld + k];
+    a.nb_q[pos] = q;
+    if (pos >> kNbBlockLog2 == b0) lower += q;
+    ++pos;
+  }
+  if (lower) atomicAdd(&blk_sum[b0], (unsigned long long)lower);
+  if (mine != lower) atomicAdd(&blk_sum[b0 + 1], (unsigned long long)(mine - lower));
+  lds_barrier();
+  if (tid < kNbBlocks) a.bsum[tid] = tid < kNbFusedBlocks ? blk_sum[tid] : 0ull;
+  clear_acc(a.acc);
+  if (tid == 0 && st.profile < a.n_valid)
+    atomicOr(&a.explored[st.profile >> 5], 1u << (st.profile & 31u));
 }
 
 // Marks the profiled configuration explored (a step read without a draw).
@@ -1251,6 +1464,28 @@ hipError_t launch_batch_draw(const BatchSess *d_sess, const BatchStep *d_step, u
 hipError_t launch_mark_one(uint32_t *d_explored, uint32_t l, uint32_t n_valid,
                            hipStream_t stream) {
   hipLaunchKernelGGL(mark_one, dim3(1), dim3(64), 0, stream, d_explored, l, n_valid);
+  return hipGetLastError();
+}
+
+hipError_t launch_nb_step(const NbFused &a, hipStream_t stream) {
+  const NbStep &st = a.st;
+  if (st.total == 0 || st.total > kNbFusedMax || st.n_subsets > kNbMaxSubsets)
+    return hipErrorInvalidValue;
+  // as many threads per candidate as leave at most 64 workgroups (one
+  // accumulator slot each)
+  constexpr uint32_t kAll = kAccSlots * kNbThreads; // threads of 64 workgroups
+  const int lp = st.total * 16 <= kAll ? 16 : st.total * 8 <= kAll ? 8 : 2;
+  const uint32_t cands = kNbThreads / lp, grid = (st.total + cands - 1) / cands;
+  const uint32_t per = (st.total + kNbThreads - 1) / kNbThreads;
+  const size_t score = (2 * st.n_subsets + 1 + (size_t)cands * (st.act.n | 1)) * 4;
+  const size_t lds = std::max(score, (size_t)2 * kNbThreads * (per | 1) * 4);
+  auto kernel = lp == 16 ? nb_step<16> : lp == 8 ? nb_step<8> : nb_step<2>;
+  if (lds > 62 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNbThreads), lds, stream, a);
   return hipGetLastError();
 }
 
