@@ -2865,6 +2865,12 @@ struct cgs_batch_s {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   float last_ms = 0.0f;
   uint64_t seq = 0; // sequence number of the last batch step's draws
+  // whole steps of small spaces in one launch (cgs_tuning_run_batch), where
+  // every session's space is small
+  bool small = false;
+  uint32_t max_tiles = 0, max_per = 0;
+  SmallJob *d_jobs = nullptr, *h_jobs = nullptr; // h_jobs pinned
+  DrawResult *h_series = nullptr, *d_series = nullptr; // [n][kMaxDrawSeries]
 };
 
 namespace {
@@ -2884,8 +2890,11 @@ void destroy_batch(cgs_batch b) {
   dfree(b->d_step);
   dfree(b->d_tile_sess);
   dfree(b->d_blk_sess);
+  dfree(b->d_jobs);
   pfree(b->h_step);
   pfree(b->h_res);
+  pfree(b->h_jobs);
+  pfree(b->h_series);
   if (b->e0) (void)hipEventDestroy(b->e0);
   if (b->e1) (void)hipEventDestroy(b->e1);
   pool::stream_put(b->stream);
@@ -2941,6 +2950,8 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   if (n < 1 || n > 65535 || !sessions || !models) return fail(CGS_EINVAL, "need 1..65535 sessions");
   std::vector<BatchSess> desc(n);
   uint64_t tiles = 0, blocks = 0, valid = 0;
+  uint32_t max_tiles = 0, max_per = 0;
+  bool small = true;
   int counters = 0;
   for (int i = 0; i < n; ++i) {
     cgs_session s = sessions[i];
@@ -2965,6 +2976,11 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     d.blk0 = (uint32_t)blocks;
     d.gamma = s->params.gamma;
     d.w_min = s->params.w_min;
+    small = small && d.n_valid >= 1 && d.n_valid <= kSmallMaxValid;
+    uint32_t st_tiles = 0;
+    small_shape(d.n_valid, &st_tiles, &d.per, &d.per4);
+    max_tiles = std::max(max_tiles, st_tiles);
+    max_per = std::max(max_per, d.per);
     tiles += (d.n_valid + kBatchTile - 1) / kBatchTile;
     blocks += d.n_blocks;
     valid += d.n_valid;
@@ -2981,6 +2997,9 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   b->total_blocks = (uint32_t)blocks;
   b->total_valid = valid;
   b->total_counters = counters;
+  b->small = small;
+  b->max_tiles = max_tiles;
+  b->max_per = max_per;
   std::vector<uint16_t> tile_sess(std::max<uint64_t>(tiles, 1)), blk_sess(std::max<uint64_t>(blocks, 1));
   for (int i = 0; i < n; ++i) {
     const uint32_t nt = (desc[i].n_valid + kBatchTile - 1) / kBatchTile;
@@ -3299,10 +3318,81 @@ extern "C" cgs_status cgs_batch_draw(cgs_batch b, const uint64_t *u64, uint64_t 
   return CGS_OK;
 }
 
+namespace {
+
+// Buffers of the one-launch steps of a small batch, on first use.
+cgs_status ensure_small_jobs(cgs_batch b) {
+  if (b->h_series) return CGS_OK;
+  hipError_t e = dalloc(&b->d_jobs, b->n);
+  if (e == hipSuccess) e = palloc<SmallJob>(&b->h_jobs, nullptr, (size_t)b->n);
+  if (e == hipSuccess) e = palloc(&b->h_series, &b->d_series, (size_t)b->n * kMaxDrawSeries);
+  if (e != hipSuccess) {
+    dfree(b->d_jobs);
+    pfree(b->h_jobs);
+    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "batch buffers: %s",
+                hipGetErrorString(e));
+  }
+  std::memset(b->h_series, 0, (size_t)b->n * kMaxDrawSeries * sizeof(DrawResult));
+  return CGS_OK;
+}
+
+// One step of every session with a job (n_draws > 0), the draws' results in
+// picks[i * kMaxDrawSeries + k]; the sessions then look as after a step and
+// draws of their own in the batch.
+cgs_status small_batch_step(cgs_batch b, Pick *picks) {
+  for (int i = 0; i < b->n; ++i) {
+    if (b->sess[i]->pending) { // recorded outside the batch
+      const cgs_status st = flush_pending(b->sess[i]);
+      if (st != CGS_OK) return st;
+      HIP_TRY(hipStreamSynchronize(b->sess[i]->space->stream));
+    }
+    b->h_jobs[i].parity = b->sess[i]->parity;
+    b->h_jobs[i].seq0 = b->seq + 1;
+  }
+  HIP_TRY(hipEventRecord(b->e0, b->stream));
+  HIP_TRY(hipMemcpyAsync(b->d_jobs, b->h_jobs, (size_t)b->n * sizeof(SmallJob),
+                         hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(launch_batch_small(b->d_sess, b->d_jobs, (uint32_t)b->n, b->max_tiles, b->max_per,
+                             b->d_series, b->stream));
+  HIP_TRY(hipEventRecord(b->e1, b->stream));
+  HIP_TRY(hipStreamSynchronize(b->stream));
+  HIP_TRY(hipEventElapsedTime(&b->last_ms, b->e0, b->e1));
+  const uint64_t seq0 = b->seq + 1;
+  b->seq += kMaxDrawSeries;
+  for (int i = 0; i < b->n; ++i) {
+    const SmallJob &j = b->h_jobs[i];
+    if (j.n_draws == 0) continue;
+    cgs_session s = b->sess[i];
+    s->cur_acc = s->parity;
+    s->parity ^= 1;
+    s->stepped = true;
+    s->pending = false;
+    s->last_nb = false;
+    s->ran_in_batch = true;
+    s->batch_ms = b->last_ms;
+    s->n_active = j.n_act;
+    b->h_step[i].parity = s->cur_acc; // cgs_batch_draw may go on from this step
+    b->h_step[i].profile = j.profile;
+    for (int k = 0; k < j.n_draws; ++k) {
+      Pick &r = picks[(size_t)i * kMaxDrawSeries + k];
+      if (!read_pick(b->h_series + (size_t)i * kMaxDrawSeries + k, seq0 + (uint64_t)k, &r))
+        return fail(CGS_EDEVICE, "session %d: draw %d did not publish its result", i, k);
+      if (r.total != 0 && r.valid == kNoPick)
+        return fail(CGS_EDEVICE, "session %d: no pick although Q > 0", i);
+      s->last_total = r.total;
+    }
+  }
+  return CGS_OK;
+}
+
+} // namespace
+
 // Alg. 1 for every session of a batch at once.  Each run follows exactly the
 // steps of cgs_tuning_run with its own random numbers; the runs advance in
-// lockstep (one batch step, then batched draws), and a run that has ended
-// keeps stepping with no profile while its results are ignored.
+// lockstep.  On small spaces an iteration is one launch and a run that has
+// ended rests; otherwise it is one batch step, then batched draws, and a run
+// that has ended keeps stepping with no profile while its results are
+// ignored.
 extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
                                            const double *counters,
                                            const cgs_expert_params *expert,
@@ -3382,8 +3472,27 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
     const cgs_status st = take_uniform(i, &u64[i]);
     if (st != CGS_OK) return st;
   }
-  cgs_status st = cgs_batch_step(b, prof.data(), nullptr, u64.data(), nullptr, valid.data(),
-                                 status.data());
+  const bool series = b->small && opts->draws <= kMaxDrawSeries;
+  std::vector<Pick> picks(series ? (size_t)n * kMaxDrawSeries : 0);
+  cgs_status st = CGS_OK;
+  if (series) {
+    st = ensure_small_jobs(b);
+    for (int i = 0; i < n && st == CGS_OK; ++i) {
+      SmallJob &job = b->h_jobs[i];
+      job.profile = kNoProfile;
+      job.n_act = 0;
+      job.n_draws = 1;
+      job.u64[0] = u64[i];
+    }
+    if (st == CGS_OK) st = small_batch_step(b, picks.data());
+    for (int i = 0; i < n && st == CGS_OK; ++i) {
+      const Pick &p = picks[(size_t)i * kMaxDrawSeries];
+      status[i] = p.total == 0 ? CGS_EEMPTY : CGS_OK;
+      valid[i] = p.valid;
+    }
+  } else {
+    st = cgs_batch_step(b, prof.data(), nullptr, u64.data(), nullptr, valid.data(), status.data());
+  }
   if (st != CGS_OK) return st;
   int n_active = 0;
   for (int i = 0; i < n; ++i) {
@@ -3391,6 +3500,19 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
     run[i].c = valid[i];
     n_active += run[i].active;
   }
+  // after an iteration: which runs go on, and from where
+  auto settle_runs = [&](int m) {
+    for (int j = 0; j < m; ++j) {
+      Run &r = run[map[j]];
+      if (!r.active) continue;
+      if (r.stop || !r.next) {
+        r.active = false;
+        --n_active;
+      } else {
+        r.c = r.next_c;
+      }
+    }
+  };
   while (n_active > 0) {
     const int m = cur->n;
     // profile the current configurations
@@ -3419,6 +3541,56 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
       r.drawing = true;
     }
     if (n_active == 0) break;
+    if (series) {
+      // the scored step and its draws in one launch: the draws depend on its
+      // weights and the uniforms only, the tests decide where a run stops
+      for (int j = 0; j < m; ++j) {
+        const int i = map[j];
+        SmallJob &job = cur->h_jobs[j];
+        job.profile = kNoProfile;
+        job.n_act = job.n_draws = 0;
+        if (!run[i].active) continue;
+        const int64_t l = (int64_t)run[i].c;
+        job.profile = (uint32_t)l;
+        for (int c = 0; c < 24; ++c) {
+          const float dc = deltas[(size_t)j * 24 + c];
+          if (dc == 0.0f) continue;
+          job.ctr[job.n_act] = (uint32_t)c;
+          job.delta[job.n_act++] = dc;
+        }
+        job.u64[0] = u64[j];
+        job.n_draws = 1;
+        for (; job.n_draws < opts->draws && run[i].u < n_uniforms; ++job.n_draws)
+          job.u64[job.n_draws] = uniforms[(uint64_t)i * n_uniforms + run[i].u++];
+      }
+      st = small_batch_step(cur, picks.data());
+      if (st != CGS_OK) return release(st);
+      for (int j = 0; j < m; ++j) {
+        Run &r = run[map[j]];
+        if (!r.active) continue;
+        const int made = cur->h_jobs[j].n_draws;
+        for (int k = 0; k < made && !r.stop; ++k) {
+          const Pick &p = picks[(size_t)j * kMaxDrawSeries + k];
+          if (p.total == 0) break; // no configuration left
+          if (test(map[j], p.valid, false)) {
+            r.stop = true;
+          } else {
+            if (runtime[p.valid] <= r.best) {
+              r.best = runtime[p.valid];
+              r.next_c = p.valid;
+              r.next = true;
+            }
+            if (k + 1 == made && made < opts->draws) {
+              st = fail(CGS_ERANGE, "run %d needs more than %llu random numbers", map[j],
+                        (unsigned long long)n_uniforms);
+              return release(st);
+            }
+          }
+        }
+      }
+      settle_runs(m);
+      continue;
+    }
     // the scored step and its first draw, then the further draws
     st = cgs_batch_step(cur, prof.data(), deltas.data(), u64.data(), nullptr, valid.data(),
                         status.data());
@@ -3457,16 +3629,7 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
       st = cgs_batch_draw(cur, u64.data(), nullptr, valid.data(), status.data());
     }
     if (st != CGS_OK) return release(st);
-    for (int j = 0; j < m; ++j) {
-      Run &r = run[map[j]];
-      if (!r.active) continue;
-      if (r.stop || !r.next) {
-        r.active = false;
-        --n_active;
-      } else {
-        r.c = r.next_c;
-      }
-    }
+    settle_runs(m);
     if (n_active > 0 && 2 * n_active <= m && m >= 4) {
       std::vector<cgs_session> ss;
       std::vector<cgs_model> ms;

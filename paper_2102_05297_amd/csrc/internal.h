@@ -139,6 +139,8 @@ struct BatchSess {
   uint32_t tile0, blk0; // first global score tile / weight block of the session
   float gamma, w_min;
   uint32_t pad;
+  uint32_t per;   // split of a small space (small_shape)
+  FastDiv per4;
 };
 struct BatchStep {
   uint32_t profile; // valid index, kNoProfile for none
@@ -258,6 +260,25 @@ struct SmallStep {
   DrawSeries series;
 };
 hipError_t launch_small_step(SmallStep &a, hipStream_t stream);
+// Tiles of a small space, and the weights per thread of its last workgroup
+// with their quads as a divisor.
+void small_shape(uint32_t n_valid, uint32_t *tiles, uint32_t *per, FastDiv *per4);
+// One step (score, weights, n_draws draws, profile marked explored) in every
+// session of a batch of small spaces, one launch: job i of session i (0
+// draws: the session rests), draw k of session i into d_res[i *
+// kMaxDrawSeries + k] under sequence number seq0 + k.  max_tiles, max_per:
+// the largest of small_shape over the sessions.
+struct SmallJob {
+  uint32_t profile;
+  int32_t n_act, parity, n_draws;
+  uint64_t seq0;
+  uint64_t u64[kMaxDrawSeries];
+  uint32_t ctr[CGS_MAX_COUNTERS];
+  float delta[CGS_MAX_COUNTERS];
+};
+hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, uint32_t n,
+                              uint32_t max_tiles, uint32_t max_per, DrawResult *d_res,
+                              hipStream_t stream);
 hipError_t launch_draw_many(const float *d_s, uint32_t *d_explored, uint32_t n_valid,
                             const StepAcc *d_acc, float gamma, float w_min, int block_log2,
                             uint64_t *d_bsum, uint32_t n_blocks, const DrawSeries &series,

@@ -655,6 +655,11 @@ __global__ __launch_bounds__(kDrawThreads) void draw_many(
 // against 16.6 us on 16,384, 16.5 against 16.8 us on 32,768.
 constexpr int kSmallThreads = 512;
 constexpr uint32_t kSmallPer = 64; // weights per thread of the last workgroup
+// Workgroups of a step of a batch, split evenly over its sessions: the release
+// of each writes back the L2 of its die, one after another.  64 sessions of
+// 7,616 configurations, five draws: 28.7 us with one or two workgroups a
+// session, 31.7 us with four, 43.6 us with eight, 50 us with fifteen.
+constexpr uint32_t kBatchSmallGroups = 128;
 static_assert(kSmallMaxValid == kSmallThreads * kSmallPer, "one run per thread");
 static_assert(kSmallMaxValid <= kAccSlots * kSmallThreads, "one accumulator slot per workgroup");
 static_assert(kSmallPer <= kWave && kSmallPer % 4 == 0, "a wave searches a run at once");
@@ -688,17 +693,73 @@ __device__ __forceinline__ float score_one(const float *__restrict__ P, uint64_t
   return s;
 }
 
+// The same for configurations l .. l + 3 (l a multiple of 4, the rows padded):
+// 16-byte loads, for workgroups that score many configurations each.
+template <int RIF>
+__device__ __forceinline__ float4 score_four(const float *__restrict__ P, uint64_t stride,
+                                             uint32_t profile, int n, const uint32_t *ctr,
+                                             const float *delta, uint32_t l) {
+  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j0 = 0; j0 < n; j0 += RIF) {
+    float4 x[RIF];
+    float a[RIF];
+#pragma unroll
+    for (int u = 0; u < RIF; ++u) {
+      const float *row = P + (size_t)ctr[min(j0 + u, n - 1)] * stride;
+      x[u] = *reinterpret_cast<const float4 *>(row + l);
+      a[u] = row[profile];
+    }
+#pragma unroll
+    for (int u = 0; u < RIF; ++u) {
+      if (j0 + u < n && a[u] != 0.0f) {
+        const float d = delta[j0 + u], v[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float t = (v[e] - a[u]) / (a[u] + v[e]);
+          s[e] = (v[e] != 0.0f) ? s[e] + d * t : s[e];
+        }
+      }
+    }
+  }
+  return make_float4(s[0], s[1], s[2], s[3]);
+}
+
+// One session's step as its workgroups see it; the counters and the uniforms
+// stay where the launch put them.
+struct SmallView {
+  const float *P;
+  uint64_t stride;
+  uint32_t profile, n_valid;
+  uint32_t *explored;
+  float *s;
+  StepAcc *acc, *acc_next;
+  float gamma, w_min;
+  int32_t block_log2;
+  uint32_t n_blocks;
+  uint64_t *bsum;
+  const uint32_t *idx;
+  DrawResult *res;
+  uint64_t seq0;
+  uint32_t *prof_out;
+  uint32_t per;
+  FastDiv per4;
+  int n_act, n_draws;
+  const uint32_t *ctr;
+  const float *delta;
+  const uint64_t *u64;
+};
+
 // The last workgroup's part: weighs the n_valid scores, makes the draws and
 // leaves the block sums.  Thread t owns the run of a.per consecutive weights
 // from t * per (LDS words q[t * ld ..]).
-__device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile, uint32_t *q) {
+__device__ __forceinline__ void small_draws(const SmallView &a, uint32_t *q) {
   __shared__ uint64_t scratch[kSmallThreads / kWave];
   __shared__ StepAccSums sums;
   __shared__ uint32_t pick_pos[kMaxDrawSeries];
   __shared__ uint64_t pick_total[kMaxDrawSeries];
   constexpr uint32_t kBlocks = (kSmallMaxValid + 4095) >> 12; // blocks hold 4096 or more
   __shared__ unsigned long long blk_sum[kBlocks];
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_valid = a.n_valid;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, n_valid = a.n_valid, profile = a.profile;
   const uint32_t per = a.per, ld = small_ld(per), first = tid * per;
   const uint32_t n_quads = kSmallThreads * (per / 4);
   StepAcc slot{};
@@ -720,7 +781,7 @@ __device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile
   load(0);
   reduce_slot_values(slot, &sums);
   if (tid < kBlocks) blk_sum[tid] = 0ull;
-  if (tid < (uint32_t)a.series.n) pick_pos[tid] = kNoIndex;
+  if (tid < (uint32_t)a.n_draws) pick_pos[tid] = kNoIndex;
   lds_barrier();
   const StepNorm nm = step_norm(key_float(sums.min_key), key_float(sums.max_key), a.gamma, a.w_min);
   auto weigh = [&](auto wide) {
@@ -754,11 +815,11 @@ __device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile
     const uint4 w = *reinterpret_cast<const uint4 *>(q + tid * ld + e);
     mine += (uint64_t)w.x + w.y + w.z + w.w;
   }
-  for (int i = 0; i < a.series.n; ++i) {
+  for (int i = 0; i < a.n_draws; ++i) {
     uint64_t Q;
     const uint64_t pre = block_excl_scan<kSmallThreads, true>(mine, scratch, Q);
     if (tid == 0) pick_total[i] = Q;
-    const uint64_t r = __umul64hi(a.series.u64[i], Q); // 0 when Q == 0: no owner
+    const uint64_t r = __umul64hi(a.u64[i], Q); // 0 when Q == 0: no owner
     const bool owner = pre <= r && r < pre + mine;
     const uint64_t own = __ballot(owner);
     if (own != 0) { // the owner's wave looks through its run, one weight per lane
@@ -779,7 +840,7 @@ __device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile
     }
   }
   lds_barrier();
-  if (tid < (uint32_t)a.series.n) {
+  if (tid < (uint32_t)a.n_draws) {
     const uint32_t l = pick_pos[tid];
     const uint32_t raw = l != kNoIndex ? a.idx[l] : kNoIndex;
     if (a.prof_out && tid == 0) *a.prof_out = l; // kNoIndex == kNoProfile
@@ -806,21 +867,43 @@ __device__ __forceinline__ void small_draws(const SmallStep &a, uint32_t profile
   if (tid < a.n_blocks) a.bsum[tid] = blk_sum[tid];
 }
 
-__global__ __launch_bounds__(kSmallThreads) void small_step(SmallStep a) {
-  extern __shared__ uint32_t small_q[];
+// One workgroup's part of the step: group `group` of n_groups takes every
+// n_groups-th tile of 512 configurations (2,048 where groups take several),
+// and the rest of the step when it arrives last.  A single group needs no meeting.
+__device__ __forceinline__ void small_body(const SmallView &a, uint32_t group, uint32_t n_groups,
+                                           uint32_t *small_q) {
   __shared__ uint32_t red[3][kSmallThreads / kWave];
   __shared__ uint32_t arrived;
-  const uint32_t tid = threadIdx.x, n_valid = a.n_valid;
-  uint32_t profile = a.prof_dev ? *a.prof_dev : a.profile;
-  const int n = profile < n_valid ? a.act.n : 0;
-  const uint32_t l = blockIdx.x * kSmallThreads + tid, lc = min(l, n_valid - 1);
-  const uint32_t word = a.explored[lc >> 5];
-  const float s = score_one<16>(a.P, a.stride, profile, n, a.act.ctr, a.act.delta, lc);
-  const bool ex = l >= n_valid || l == profile || ((word >> (lc & 31u)) & 1u);
-  if (l < n_valid) a.s[l] = s;
-  const uint32_t key = float_key(s);
-  const uint32_t kmin = wave_umin(ex ? 0xffffffffu : key), kmax = wave_umax(ex ? 0u : key);
-  const uint32_t cnt = (uint32_t)__popcll(__ballot(!ex));
+  const uint32_t tid = threadIdx.x, n_valid = a.n_valid, profile = a.profile;
+  const int n = profile < n_valid ? a.n_act : 0;
+  uint32_t kmin = 0xffffffffu, kmax = 0u, cnt = 0u;
+  auto fold = [&](float s, bool ex) {
+    const uint32_t key = float_key(s);
+    kmin = min(kmin, ex ? 0xffffffffu : key);
+    kmax = max(kmax, ex ? 0u : key);
+    cnt += (uint32_t)__popcll(__ballot(!ex));
+  };
+  if (n_groups * kSmallThreads >= n_valid) { // one configuration per thread
+    const uint32_t l = group * kSmallThreads + tid, lc = min(l, n_valid - 1);
+    const uint32_t word = a.explored[lc >> 5];
+    const float s = score_one<16>(a.P, a.stride, profile, n, a.ctr, a.delta, lc);
+    if (l < n_valid) a.s[l] = s;
+    fold(s, l >= n_valid || l == profile || ((word >> (lc & 31u)) & 1u));
+  } else {
+    for (uint32_t l0 = 4 * group * kSmallThreads; l0 < n_valid;
+         l0 += 4 * n_groups * kSmallThreads) {
+      const uint32_t l = l0 + 4 * tid, lc = l < n_valid ? l : 0u;
+      const uint32_t word = a.explored[lc >> 5] >> (lc & 31u);
+      const float4 s = score_four<8>(a.P, a.stride, profile, n, a.ctr, a.delta, lc);
+      if (l < n_valid) *reinterpret_cast<float4 *>(a.s + l) = s;
+      const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e)
+        fold(v[e], l + e >= n_valid || l + e == profile || ((word >> e) & 1u));
+    }
+  }
+  kmin = wave_umin(kmin);
+  kmax = wave_umax(kmax);
   if ((tid & 63u) == 0) {
     red[0][tid >> 6] = kmin;
     red[1][tid >> 6] = kmax;
@@ -835,20 +918,52 @@ __global__ __launch_bounds__(kSmallThreads) void small_step(SmallStep a) {
       slot.max_key = max(slot.max_key, red[1][w]);
       slot.n_unexplored += red[2][w];
     }
-    a.acc[blockIdx.x].min_key = slot.min_key;
-    a.acc[blockIdx.x].max_key = slot.max_key;
-    a.acc[blockIdx.x].n_unexplored = slot.n_unexplored;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    arrived = atomicAdd(&a.acc_next[0].pad, 1u);
+    a.acc[group].min_key = slot.min_key;
+    a.acc[group].max_key = slot.max_key;
+    a.acc[group].n_unexplored = slot.n_unexplored;
+    if (n_groups > 1) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      arrived = atomicAdd(&a.acc_next[0].pad, 1u);
+    }
   }
-  __syncthreads();
-  if (arrived != gridDim.x - 1) return; // uniform over the workgroup
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (tid == 0) a.acc_next[0].pad = 0u;
-  small_draws(a, profile, small_q);
+  __syncthreads(); // also publishes a single group's scores within the workgroup
+  if (n_groups > 1) {
+    if (arrived != n_groups - 1) return; // uniform over the workgroup
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (tid == 0) a.acc_next[0].pad = 0u;
+  }
+  small_draws(a, small_q);
   clear_acc(a.acc_next); // the next step's accumulators
   if (tid == 0 && profile < n_valid)
     atomicOr(&a.explored[profile >> 5], 1u << (profile & 31u));
+}
+
+__global__ __launch_bounds__(kSmallThreads) void small_step(SmallStep a) {
+  extern __shared__ uint32_t small_q[];
+  const uint32_t profile = a.prof_dev ? *a.prof_dev : a.profile;
+  const SmallView v{a.P,    a.stride, profile,      a.n_valid,  a.explored, a.s,
+                    a.acc,  a.acc_next, a.gamma,    a.w_min,    a.block_log2, a.n_blocks,
+                    a.bsum, a.idx,    a.res,        a.seq0,     a.prof_out, a.per,
+                    a.per4, a.act.n,  a.series.n,   a.act.ctr,  a.act.delta, a.series.u64};
+  small_body(v, blockIdx.x, gridDim.x, small_q);
+}
+
+// The same step in every session of a batch of small spaces, `groups`
+// workgroups a session; a session with no draws to make rests.
+__global__ __launch_bounds__(kSmallThreads) void batch_small(
+    const BatchSess *__restrict__ sess, const SmallJob *__restrict__ jobs, uint32_t groups,
+    DrawResult *__restrict__ res) {
+  extern __shared__ uint32_t small_q[];
+  const uint32_t si = blockIdx.x / groups;
+  const BatchSess &d = sess[si];
+  const SmallJob &j = jobs[si];
+  if (j.n_draws == 0) return; // uniform over the session's workgroups
+  const SmallView v{d.P, d.stride, j.profile, d.n_valid, d.explored, d.s,
+                    d.acc + j.parity * kAccSlots, d.acc + (j.parity ^ 1) * kAccSlots,
+                    d.gamma, d.w_min, d.block_log2, d.n_blocks, d.bsum, d.idx,
+                    res + (size_t)si * kMaxDrawSeries, j.seq0, nullptr, d.per, d.per4,
+                    j.n_act, j.n_draws, j.ctr, j.delta, j.u64};
+  small_body(v, blockIdx.x - si * groups, groups, small_q);
 }
 
 // ------------------------------------------------------------ batched
@@ -1410,20 +1525,45 @@ hipError_t launch_draw_many(const float *d_s, uint32_t *d_explored, uint32_t n_v
   return hipGetLastError();
 }
 
+void small_shape(uint32_t n_valid, uint32_t *tiles, uint32_t *per, FastDiv *per4) {
+  *tiles = (n_valid + kSmallThreads - 1) / kSmallThreads;
+  *per = std::max<uint32_t>(4, (*tiles + 3u) & ~3u); // `tiles` weights per thread, in quads
+  *per4 = make_fastdiv(*per / 4);
+}
+
+namespace {
+template <typename K> hipError_t allow_small_lds(K kernel, size_t lds) {
+  if (lds <= 62 * 1024) return hipSuccess; // with the static part, no opt-in needed
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+} // namespace
+
 hipError_t launch_small_step(SmallStep &a, hipStream_t stream) {
   if (a.n_valid == 0 || a.n_valid > kSmallMaxValid || a.series.n < 0 ||
       a.series.n > kMaxDrawSeries || a.block_log2 < 12)
     return hipErrorInvalidValue;
-  const uint32_t grid = (a.n_valid + kSmallThreads - 1) / kSmallThreads;
-  a.per = (grid + 3u) & ~3u; // grid configurations per thread, in whole quads
-  a.per4 = make_fastdiv(a.per / 4);
+  uint32_t grid;
+  small_shape(a.n_valid, &grid, &a.per, &a.per4);
   const size_t lds = small_ld(a.per) * kSmallThreads * sizeof(uint32_t);
-  if (lds > 62 * 1024) { // with the static part, past what needs no opt-in
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(small_step),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = allow_small_lds(small_step, lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(small_step, dim3(grid), dim3(kSmallThreads), lds, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, uint32_t n,
+                              uint32_t max_tiles, uint32_t max_per, DrawResult *d_res,
+                              hipStream_t stream) {
+  if (n == 0) return hipSuccess;
+  if (max_per > kSmallPer) return hipErrorInvalidValue;
+  const uint32_t groups =
+      std::max<uint32_t>(1, std::min<uint32_t>(std::min<uint32_t>(max_tiles, kAccSlots), kBatchSmallGroups / n));
+  const size_t lds = small_ld(max_per) * kSmallThreads * sizeof(uint32_t);
+  const hipError_t e = allow_small_lds(batch_small, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(batch_small, dim3(n * groups), dim3(kSmallThreads), lds, stream, d_sess,
+                     d_jobs, groups, d_res);
   return hipGetLastError();
 }
 

@@ -64,3 +64,35 @@ def test_draw_series_equal_the_oracle(radix, draws):
     ref = TU.run(prep, table.runtime, P, U, draws=draws, max_tests=n, stop_at_well=False,
                  cores=1.0, threads=1e9)
     assert got[0].tolist() == ref.tested and got[1].tolist() == ref.profiled
+
+
+# one workgroup a session (more sessions than workgroups, a space of one
+# tile), several, and one per tile
+@pytest.mark.parametrize("radix,runs,draws", [((15, 7, 5), 3, 2), ((15, 13, 7, 3), 130, 5),
+                                              ((15, 14, 13, 12), 9, 5), ((16, 16, 16), 1, 33)])
+def test_batched_runs_equal_the_oracle(radix, runs, draws):
+    m = cgs()
+    spec = synth.Space(list(radix), [list(range(1, r + 1)) for r in radix])
+    valid = SP.enumerate_valid(spec.radix, spec.values, spec.constraints)
+    digits = SP.digits_of(valid, spec.radix)
+    table = synth.kernel_table(synth.rng(64, *radix), digits, spec.radix)
+    P = table.counters
+    prep = SR.Prepared(valid, digits, None, P, P.astype(np.float32))
+    sp = m.Space.from_spec(spec)
+    model = m.TableModel(sp, P.astype(np.float32))
+    sessions = [m.Session(sp) for _ in range(runs)]
+    U = np.stack([synth.uniforms_u64(synth.rng(65, i), 200) for i in range(runs)])
+    ep = m.cgs_expert_params(inst_reaction=0.7, volta=0, reserved=0, cores=1.0, threads=1e9)
+    n = 2 * (draws + 1) + 2
+    batch = m.Batch(sessions, [model] * runs)
+    got = batch.tuning_run(table.runtime, P, U, draws=draws, max_tests=n, stop_at_well=False,
+                           expert=ep)
+    for i in sorted({0, runs // 2, runs - 1}):
+        ref = TU.run(prep, table.runtime, P, U[i], draws=draws, max_tests=n, stop_at_well=False,
+                     cores=1.0, threads=1e9)
+        assert got[i][0].tolist() == ref.tested and got[i][1].tolist() == ref.profiled
+    # the sessions go on from the batch's last step, one draw each
+    more = batch.draw(U[:, -1])
+    assert (more[2] == 0).all()
+    for i in range(runs):
+        assert more[1][i] not in set(got[i][0].tolist())
