@@ -593,7 +593,8 @@ typedef struct {
  * keeps pointers to both: destroy the batch first.  While stepping through
  * the batch, the sessions may still be read (copy_scores, step_info, ...) and
  * drawn from between batch steps.  sched NULL: defaults (grids capped at
- * 2048 workgroups, graph on). */
+ * 2048 workgroups, or one workgroup per tile and block when the sessions'
+ * predictions are too large for the caches; graph on). */
 cgs_status cgs_batch_create(int n, const cgs_session *sessions, const cgs_model *models,
                             const cgs_batch_schedule *sched, cgs_batch *out);
 /* One step in every session: profile_raw_host[n] (CGS_NO_PROFILE allowed),

@@ -158,9 +158,23 @@ constexpr uint32_t kBatchTile = 1024; // configurations per score tile
 // (0: 8 rows, unconstrained; 1: 4 rows, 4 waves; 2: 16 rows, 2 waves;
 // 3: 8 rows, 4 waves; 4: 4 rows, 8 waves)
 constexpr int kBatchScoreVariants = 5;
+// Scored steps that read more prediction bytes than this stream them past the
+// caches (non-temporal loads) with one workgroup per tile; below it, the next
+// step finds much of the same rows in the 256 MB last-level cache, which
+// plain loads from a grid-stride pass use.  Per step of 4.0M configurations:
+// 144 MB (9 counters) 51 us plain against 56 us streamed, 256 MB 71 to 76
+// against 73, 320 MB 84 to 90 against 83, 513 MB 127 against 117, 1,026 MB
+// 225 against 206; the pass over 27.7M configurations and 32 counters 731 us
+// plain, 676 us with non-temporal loads, 628 us (5.8 TB/s) with one tile per
+// workgroup as well.
+constexpr uint64_t kStreamBytes = 288000000;
+// A batch whose sessions' predictions (every counter) take row_bytes: its
+// steps score with about half of the counters or more.
+inline bool batch_streams(uint64_t row_bytes) { return row_bytes / 2 > kStreamBytes; }
+// row_bytes: the predictions of every counter of every session.
 hipError_t launch_batch_score(const BatchSess *d_sess, const BatchStep *d_step,
                               const uint16_t *d_tile_sess, uint32_t total_tiles, uint32_t grid,
-                              int variant, hipStream_t stream);
+                              int variant, uint64_t row_bytes, hipStream_t stream);
 hipError_t launch_batch_weight(const BatchSess *d_sess, const BatchStep *d_step,
                                const uint16_t *d_blk_sess, uint32_t total_blocks, uint32_t grid,
                                hipStream_t stream);

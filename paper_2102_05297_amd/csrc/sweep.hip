@@ -65,10 +65,21 @@ __device__ __forceinline__ StepAccSums reduce_slots(const StepAcc *__restrict__ 
   return shared_sums;
 }
 
+template <bool kStream> __device__ __forceinline__ float4 load_row(const float *p) {
+  if constexpr (kStream) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+  } else {
+    return *reinterpret_cast<const float4 *>(p);
+  }
+}
+
 // Scores the 4 configurations of this thread in `tile` (4 * kScoreThreads
 // configurations per tile) and folds the unexplored ones into the running
 // min / max keys and count.  Counters ctr[0..n) with changes delta[].
-template <int RIF = kRowsInFlight>
+// kStream: the rows are loaded past the caches.
+template <int RIF = kRowsInFlight, bool kStream = false>
 __device__ __forceinline__ void score_tile(const float *__restrict__ P, uint64_t stride,
                                            uint32_t profile, int n, const uint32_t *ctr,
                                            const float *delta,
@@ -93,7 +104,7 @@ __device__ __forceinline__ void score_tile(const float *__restrict__ P, uint64_t
     for (int u = 0; u < RIF; ++u) {
       if (j0 + u < n) {
         const size_t row = (size_t)ctr[j0 + u] * stride;
-        x[u] = *reinterpret_cast<const float4 *>(col + row);
+        x[u] = load_row<kStream>(col + row);
         av[u] = P[row + profile];
       }
     }
@@ -168,6 +179,7 @@ __device__ __forceinline__ void flush_acc(uint32_t kmin, uint32_t kmax, uint32_t
 // configurations, grid-stride, so few workgroups update the accumulators.
 // With prof_dev, the profiled configuration is read from device memory
 // (written there by the previous step's draw) instead of `profile`.
+template <bool kStream>
 __global__ __launch_bounds__(kScoreThreads) void score_pass(
     const float *__restrict__ P, uint64_t stride, uint32_t profile,
     const uint32_t *__restrict__ prof_dev, ActiveCounters act,
@@ -178,8 +190,8 @@ __global__ __launch_bounds__(kScoreThreads) void score_pass(
   const int n = profile < n_valid ? act.n : 0;
   const uint32_t n_tiles = (n_valid + 4u * kScoreThreads - 1) / (4u * kScoreThreads);
   for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
-    score_tile(P, stride, profile, n, act.ctr, act.delta, explored, n_valid, s_out, tile, kmin,
-               kmax, cnt);
+    score_tile<kRowsInFlight, kStream>(P, stride, profile, n, act.ctr, act.delta, explored, n_valid,
+                                       s_out, tile, kmin, kmax, cnt);
   flush_acc(kmin, kmax, cnt, acc + (blockIdx.x & (kAccSlots - 1)));
 }
 
@@ -971,7 +983,8 @@ __global__ __launch_bounds__(kSmallThreads) void batch_small(
 // a workgroup flushes its accumulators whenever the session changes.
 // RIF: counter rows in flight per thread; WPE: waves per SIMD the compiler
 // plans registers for (the autotuner's variants).
-template <int RIF, int WPE>
+// kStream as in score_pass, chosen for the batch as a whole.
+template <int RIF, int WPE, bool kStream>
 __global__ __launch_bounds__(kScoreThreads)
 __attribute__((amdgpu_waves_per_eu(WPE, 8))) void batch_score(const BatchSess *__restrict__ sess,
                                                               const BatchStep *__restrict__ step,
@@ -993,7 +1006,7 @@ __attribute__((amdgpu_waves_per_eu(WPE, 8))) void batch_score(const BatchSess *_
     const BatchSess &d = sess[si];
     const BatchStep &st = step[si];
     const int n = st.profile < d.n_valid ? st.n_act : 0;
-    score_tile<RIF>(d.P, d.stride, st.profile, n, st.ctr, st.delta, d.explored, d.n_valid, d.s,
+    score_tile<RIF, kStream>(d.P, d.stride, st.profile, n, st.ctr, st.delta, d.explored, d.n_valid, d.s,
                t - d.tile0, kmin, kmax, cnt);
   }
   if (cur != 0xffffffffu)
@@ -1484,10 +1497,14 @@ hipError_t launch_score_pass(const float *d_P, uint64_t stride, uint32_t profile
                              uint32_t n_valid, float *d_s, StepAcc *d_acc, hipStream_t stream,
                              const uint32_t *d_prof) {
   const uint32_t n_tiles = (n_valid + 4u * kScoreThreads - 1) / (4u * kScoreThreads);
-  const uint32_t grid = std::min<uint32_t>(n_tiles, kScoreGrid);
-  if (grid == 0) return hipSuccess;
-  hipLaunchKernelGGL(score_pass, dim3(grid), dim3(kScoreThreads), 0, stream, d_P, stride, profile,
-                     d_prof, act, d_explored, n_valid, d_s, d_acc);
+  if (n_tiles == 0) return hipSuccess;
+  if (4ull * (uint64_t)act.n * n_valid > kStreamBytes)
+    hipLaunchKernelGGL(score_pass<true>, dim3(n_tiles), dim3(kScoreThreads), 0, stream, d_P,
+                       stride, profile, d_prof, act, d_explored, n_valid, d_s, d_acc);
+  else
+    hipLaunchKernelGGL(score_pass<false>, dim3(std::min<uint32_t>(n_tiles, kScoreGrid)),
+                       dim3(kScoreThreads), 0, stream, d_P, stride, profile, d_prof, act,
+                       d_explored, n_valid, d_s, d_acc);
   return hipGetLastError();
 }
 
@@ -1569,11 +1586,18 @@ hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, u
 
 hipError_t launch_batch_score(const BatchSess *d_sess, const BatchStep *d_step,
                               const uint16_t *d_tile_sess, uint32_t total_tiles, uint32_t grid,
-                              int variant, hipStream_t stream) {
+                              int variant, uint64_t row_bytes, hipStream_t stream) {
   if (total_tiles == 0 || grid == 0) return hipSuccess;
+  const bool streamed = batch_streams(row_bytes);
 #define CGS_BATCH_SCORE(RIF, WPE)                                                               \
-  hipLaunchKernelGGL((batch_score<RIF, WPE>), dim3(grid), dim3(kScoreThreads), 0, stream,      \
-                     d_sess, d_step, d_tile_sess, total_tiles)
+  do {                                                                                          \
+    if (streamed)                                                                               \
+      hipLaunchKernelGGL((batch_score<RIF, WPE, true>), dim3(grid), dim3(kScoreThreads), 0,     \
+                         stream, d_sess, d_step, d_tile_sess, total_tiles);                     \
+    else                                                                                        \
+      hipLaunchKernelGGL((batch_score<RIF, WPE, false>), dim3(grid), dim3(kScoreThreads), 0,    \
+                         stream, d_sess, d_step, d_tile_sess, total_tiles);                     \
+  } while (0)
   switch (variant) {
   case 1: CGS_BATCH_SCORE(4, 4); break;
   case 2: CGS_BATCH_SCORE(16, 2); break;
