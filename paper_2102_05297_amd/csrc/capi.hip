@@ -162,6 +162,8 @@ struct cgs_model_s {
   // least-squares polynomials: descriptor and coefficients [S][T][C]
   PolyDev poly{};
   PolyDev *d_poly = nullptr;
+  PolyNest nest{};
+  PolyNest *d_nest = nullptr;
   double *d_beta64 = nullptr;
   float *d_beta32 = nullptr;
 };
@@ -515,6 +517,7 @@ void destroy_model(cgs_model m) {
   dfree(m->d_w2n);
   dfree(m->d_w3n);
   dfree(m->d_poly);
+  dfree(m->d_nest);
   dfree(m->d_beta64);
   dfree(m->d_beta32);
   free_mlp_scratch(m);
@@ -588,7 +591,8 @@ cgs_status evaluate_model(cgs_model m) {
   } else if (m->kind == 3) {
     // predictions given by the caller: nothing to evaluate
   } else if (m->kind == 2) {
-    e = launch_poly_eval(m->d_poly, m->poly.T, m->poly.C, m->poly.S, sp->d_desc, sp->d_idx,
+    e = launch_poly_eval(m->d_poly, m->poly.T, m->poly.C, m->poly.S, m->nest, m->d_nest,
+                         sp->d_desc, (uint32_t)sp->n_raw, sp->d_idx, sp->d_mask, sp->d_rank,
                          (uint32_t)sp->n_valid, m->d_beta32, m->d_P, m->stride, sp->stream);
   } else {
     MlpFwdArgs a = mlp_args(m);
@@ -863,6 +867,70 @@ cgs_status poly_describe(const cgs_space_s *sp, int order, int n_counters, PolyD
   return CGS_OK;
 }
 
+// The nested form (models.h): as many of the last parameters as keep r_in
+// within kNestMaxInner are inner, up to the last binary one.
+void poly_nest(const cgs_space_s *sp, const PolyDev &pd, PolyNest &n) {
+  std::memset(&n, 0, sizeof(n));
+  int first = sp->n_params;
+  uint32_t r_in = 1;
+  while (first > 0 && sp->radix[first - 1] != 2 &&
+         r_in * (uint32_t)sp->radix[first - 1] <= kNestMaxInner)
+    r_in *= (uint32_t)sp->radix[--first];
+  if (r_in < 8) return; // too few configurations share an outer part
+  uint32_t M = 0, of[kPolyMaxTerms], slots[kPolyMaxTerms], n_slot = 1;
+  for (int i = 0; i < pd.T; ++i) {
+    const uint32_t d = pd.terms[i];
+    uint32_t in = 0, k_in = 0, out = 0, k_out = 0;
+    for (uint32_t q = 0; q < (d & 7u); ++q) {
+      const uint32_t j = (d >> (3 + 5 * q)) & 31u;
+      if ((int)j >= first)
+        in |= j << (3 + 5 * k_in++);
+      else
+        out |= j << (8 * k_out++);
+    }
+    n_slot = std::max(n_slot, k_out);
+    while (k_out < 4) out |= 32u << (8 * k_out++);
+    in |= k_in;
+    uint32_t m = 0;
+    while (m < M && n.inner[m] != in) ++m;
+    if (m == M) {
+      if (M == (uint32_t)kNestMaxMonomials) return;
+      n.inner[M++] = in;
+    }
+    of[i] = m;
+    slots[i] = out;
+  }
+  uint32_t K = 0, start[kNestMaxMonomials + 1]; // in eights
+  for (uint32_t m = 0; m < M; ++m) {
+    start[m] = K / 8;
+    for (int i = 0; i < pd.T; ++i) {
+      if (of[i] != m) continue;
+      if (K == kNestMaxPadded) return;
+      n.order[K] = i;
+      n.slots[K++] = slots[i];
+    }
+    for (; K % 8; ++K) { // kNestMaxPadded is a multiple of eight
+      n.order[K] = INT32_MIN;
+      n.slots[K] = 33u | 32u << 8 | 32u << 16 | 32u << 24;
+    }
+    n.ends |= 1ull << (K / 8 - 1);
+  }
+  start[M] = K / 8;
+  uint32_t split = 1; // two shares, as even as the monomials allow
+  auto larger = [&](uint32_t v) { return std::max(start[v], K / 8 - start[v]); };
+  for (uint32_t m = 1; m <= M; ++m)
+    if (larger(m) < larger(split)) split = m;
+  if (larger(split) > (uint32_t)kNestPairs) return;
+  n.split_m = split;
+  n.split = start[split];
+  n.first = (uint32_t)first;
+  n.K = K;
+  n.n_slot = n_slot;
+  n.r_in = r_in;
+  n.div_in = make_fastdiv(r_in);
+  n.M = M;
+}
+
 } // namespace
 
 extern "C" cgs_status cgs_poly_design(cgs_space sp, uint64_t capacity, uint32_t *valid_idx,
@@ -946,6 +1014,7 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
   m->kind = 2;
   m->n_counters = C;
   m->poly = pd;
+  poly_nest(sp, pd, m->nest);
   m->stride = (sp->n_valid + 63) & ~(uint64_t)63;
   // each subspace's points in input order (a stable counting sort on the
   // host: digits of the points' raw indices, parameter 0 most significant)
@@ -994,6 +1063,9 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
     dfree(d_Gp);
   };
   hipError_t e = dalloc(&m->d_poly, 1);
+  if (e == hipSuccess) e = dalloc(&m->d_nest, 1);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(m->d_nest, &m->nest, sizeof(PolyNest), hipMemcpyHostToDevice, sp->stream);
   if (e == hipSuccess) e = dalloc(&m->d_beta64, (size_t)S * T * C);
   if (e == hipSuccess) e = dalloc(&m->d_beta32, (size_t)S * T * C);
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)C * m->stride);

@@ -153,8 +153,31 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
                            const uint32_t *d_pairs, uint32_t n_pairs, double *d_G, double *d_Gp,
                            double *d_beta64, float *d_beta32, uint32_t *d_err,
                            hipStream_t stream);
-hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const SpaceDev *d_space,
-                            const uint32_t *d_idx, uint32_t nv, const float *d_beta32, float *d_P,
-                            uint64_t stride, hipStream_t stream);
+// The nested form of the basis: the parameters from `first` on (none of them
+// binary, r_in combinations) are inner.  The terms with inner monomial m
+// (descriptor inner[m]) are consecutive and filled up to eights: position t of
+// K holds term order[t] (bit 31: none), whose outer part is the
+// product of the features slots[t] names, one byte each (32: the value 1, 33:
+// the value 0), n_slot of them.  Bit u of `ends`: positions 8 u .. 8 u + 7 are
+// a monomial's last.  Monomials from split_m on start at position 8 split.
+// M = 0: the space has no inner parameters worth it.
+constexpr int kNestMaxMonomials = 32;
+constexpr uint32_t kNestMaxInner = 128;
+constexpr uint32_t kNestMaxPadded = 320;
+constexpr int kNestPairs = 20;           // eights before, and from, position 8 split
+constexpr uint32_t kNestSlack = 32;      // floats read past the last combination's parts
+struct PolyNest {
+  uint32_t M, r_in, first, K, n_slot, split_m, split;
+  FastDiv div_in;
+  uint64_t ends;
+  uint32_t inner[kNestMaxMonomials];
+  int32_t order[kNestMaxPadded];
+  uint32_t slots[kNestMaxPadded];
+};
+hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const PolyNest &nest,
+                            const PolyNest *d_nest, const SpaceDev *d_space, uint32_t n_raw,
+                            const uint32_t *d_idx, const uint32_t *d_mask,
+                            const uint32_t *d_rank, uint32_t nv, const float *d_beta32,
+                            float *d_P, uint64_t stride, hipStream_t stream);
 
 } // namespace cgs

@@ -215,23 +215,43 @@ __device__ __forceinline__ uint32_t pk(uint32_t i, uint32_t j) { return i * (i +
 
 // One workgroup per subspace: (G + lam I) beta = R by Cholesky in LDS
 // (packed lower triangle), then the two triangular solves for CC counters at
-// a time, each elimination step spread over (row, counter) pairs.
-__global__ __launch_bounds__(kPolyThreads) void poly_solve(const PolyDev *__restrict__ pd,
-                                                           const double *__restrict__ G,
-                                                           uint32_t CC,
-                                                           double *__restrict__ beta64,
-                                                           float *__restrict__ beta32,
-                                                           uint32_t *__restrict__ err) {
+// a time, in panels of 16 terms: a panel's columns are factored with a row
+// per lane in registers, then taken off the rest of the triangle at once; the
+// solves take a block of 16 rows per counter in one thread's registers, then
+// take it off the other rows.  Every element has the same multiply-adds in
+// the same order as column by column.
+// Bound: the chains of square roots and divisions (one of each per term, and
+// a division per term in each solve).  Column by column, with three barriers
+// per column and four per row of the solves, it took 502 us on 139 terms and
+// 24 counters; in panels 248 us, of which a third was
+// saved by keeping the loops over a panel's columns rolled (unrolled: 300 us).
+constexpr int kSolveThreads = 512;
+constexpr uint32_t kSolveNB = 16; // columns per panel
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+__global__ __launch_bounds__(kSolveThreads) void poly_solve(const PolyDev *__restrict__ pd,
+                                                            const double *__restrict__ G,
+                                                            uint32_t CC,
+                                                            double *__restrict__ beta64,
+                                                            float *__restrict__ beta32,
+                                                            uint32_t *__restrict__ err) {
   extern __shared__ double L[]; // packed lower triangle, then z[T][CC]
   __shared__ double s_lam;
+  constexpr uint32_t NB = kSolveNB;
   const uint32_t T = pd->T, C = pd->C, Ta = T + C, s = blockIdx.x, t = threadIdx.x;
-  const uint32_t tx = t % 16, ty = t / 16;
+  const uint32_t lane = t & 63u, wave = t >> 6;
   const double *Gs = G + (uint64_t)s * Ta * Ta;
   double *z = L + (uint64_t)T * (T + 1) / 2;
   double *b64 = beta64 + (uint64_t)s * T * C;
   float *b32 = beta32 + (uint64_t)s * T * C;
   if (Gs[0] == 0.0) { // no point in this subspace (the constant column sums to n_s)
-    for (uint32_t e = t; e < T * C; e += kPolyThreads) {
+    for (uint32_t e = t; e < T * C; e += kSolveThreads) {
       b64[e] = 0.0;
       b32[e] = 0.0f;
     }
@@ -241,85 +261,157 @@ __global__ __launch_bounds__(kPolyThreads) void poly_solve(const PolyDev *__rest
   // flight (one thread per row would wait for up to T loads in turn)
   constexpr int kB = 8;
   const uint32_t nt = T * T;
-  for (uint32_t e0 = t; e0 < nt; e0 += kB * kPolyThreads) {
+  for (uint32_t e0 = t; e0 < nt; e0 += kB * kSolveThreads) {
     double v[kB];
 #pragma unroll
     for (int u = 0; u < kB; ++u) {
-      const uint32_t e = min(e0 + u * kPolyThreads, nt - 1);
+      const uint32_t e = min(e0 + u * kSolveThreads, nt - 1);
       v[u] = Gs[(uint64_t)(e / T) * Ta + e % T];
     }
 #pragma unroll
     for (int u = 0; u < kB; ++u) {
-      const uint32_t e = e0 + u * kPolyThreads, i = e / T, j = e % T;
+      const uint32_t e = e0 + u * kSolveThreads, i = e / T, j = e % T;
       if (e < nt && j <= i) L[pk(i, j)] = v[u];
     }
   }
   __syncthreads();
   if (t == 0) { // the trace in index order
     double tr = 0.0;
+#pragma unroll 8
     for (uint32_t i = 0; i < T; ++i) tr += L[pk(i, i)];
     s_lam = kRidge * tr / (double)T;
   }
   __syncthreads();
-  for (uint32_t i = t; i < T; i += kPolyThreads) L[pk(i, i)] += s_lam;
-  // right-looking Cholesky, column by column; the trailing update is tiled
-  // 16 x 16 over (row, column) pairs of the remaining lower triangle
-  for (uint32_t j = 0; j < T; ++j) {
+  for (uint32_t i = t; i < T; i += kSolveThreads) L[pk(i, i)] += s_lam;
+  for (uint32_t j0 = 0; j0 < T; j0 += NB) {
+    const uint32_t nb = min(NB, T - j0), j1 = j0 + nb;
     __syncthreads();
-    if (t == 0) {
-      double d = L[pk(j, j)];
-      if (!(d > 0.0)) {
-        atomicOr(err, 4u);
-        d = s_lam;
+    // the panel, one row per lane: the diagonal block in lanes 0 .. 15 of every
+    // wave that has rows, 48 of the rows below it in the others
+    const uint32_t row = lane < NB ? (lane < nb ? j0 + lane : T) : j1 + 48 * wave + lane - NB;
+    const bool work = wave == 0 || j1 + 48 * wave < T;
+    double a[NB];
+    if (work) {
+#pragma unroll
+      for (uint32_t c = 0; c < NB; ++c) {
+        const uint32_t j = j0 + c;
+        a[c] = c < nb && row < T && j <= row ? L[pk(row, j)] : 0.0;
       }
-      L[pk(j, j)] = sqrt(d);
+    }
+    __syncthreads(); // every wave has the diagonal block
+    if (work) {
+      // rolled, with the columns moving down by one: unrolled sixteen times the
+      // code is longer than its first pass through the instruction cache allows
+      const bool mine = row < T && (lane >= NB || wave == 0);
+#pragma unroll 1
+      for (uint32_t c = 0; c < nb; ++c) {
+        double d = lane_value(a[0], c);
+        if (!(d > 0.0)) {
+          if (t == 0) atomicOr(err, 4u);
+          d = s_lam;
+        }
+        d = sqrt(d);
+        const double x = lane == c ? d : a[0] / d;
+        if (mine && j0 + c <= row) L[pk(row, j0 + c)] = x;
+        // columns past the panel take rows below it, and are never reached
+#pragma unroll
+        for (uint32_t k = 1; k < NB; ++k) a[k - 1] = a[k] - x * lane_value(x, c + k);
+      }
     }
     __syncthreads();
-    const double djj = L[pk(j, j)];
-    for (uint32_t i = j + 1 + t; i < T; i += kPolyThreads) L[pk(i, j)] /= djj;
-    __syncthreads();
-    for (uint32_t i = j + 1 + ty; i < T; i += 16) {
-      const double lij = L[pk(i, j)];
-      for (uint32_t k = j + 1 + tx; k <= i; k += 16) L[pk(i, k)] -= lij * L[pk(k, j)];
+    // the panel's columns off the rest of the triangle (nb == NB wherever there is any)
+    for (uint32_t i = j1 + t / 16; i < T; i += kSolveThreads / 16) {
+      double li[NB];
+#pragma unroll
+      for (uint32_t c = 0; c < NB; ++c) li[c] = L[pk(i, j0) + c];
+      for (uint32_t k = j1 + t % 16; k <= i; k += 16) {
+        double v = L[pk(i, k)];
+        const double *lk = L + pk(k, j0);
+#pragma unroll
+        for (uint32_t c = 0; c < NB; ++c) v -= li[c] * lk[c];
+        L[pk(i, k)] = v;
+      }
     }
   }
-  // L z = R, then L^T beta = z, CC counters at a time
+  // L z = R, then L^T beta = z, CC counters at a time: a block of rows by one
+  // thread per counter, then off the other rows by all
+  const uint32_t last = (T - 1) / NB * NB;
   for (uint32_t c0 = 0; c0 < C; c0 += CC) {
     const uint32_t cc = min(CC, C - c0);
     __syncthreads();
-    for (uint32_t e0 = t; e0 < T * cc; e0 += kB * kPolyThreads) {
+    for (uint32_t e0 = t; e0 < T * cc; e0 += kB * kSolveThreads) {
       double v[kB];
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
-        const uint32_t e = min(e0 + u * kPolyThreads, T * cc - 1);
+        const uint32_t e = min(e0 + u * kSolveThreads, T * cc - 1);
         v[u] = Gs[(uint64_t)(e / cc) * Ta + T + c0 + e % cc];
       }
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
-        const uint32_t e = e0 + u * kPolyThreads;
+        const uint32_t e = e0 + u * kSolveThreads;
         if (e < T * cc) z[(e / cc) * CC + e % cc] = v[u];
       }
     }
-    for (uint32_t i = 0; i < T; ++i) {
+    double x[NB];
+    for (uint32_t j0 = 0; j0 < T; j0 += NB) {
+      const uint32_t nb = min(NB, T - j0), j1 = j0 + nb;
       __syncthreads();
-      if (t < cc) z[i * CC + t] /= L[pk(i, i)];
+      if (t < cc) {
+#pragma unroll
+        for (uint32_t k = 0; k < NB; ++k) x[k] = k < nb ? z[(j0 + k) * CC + t] : 0.0;
+#pragma unroll 1
+        for (uint32_t i = 0; i < nb; ++i) {
+          const double v = x[0] / L[pk(j0 + i, j0 + i)];
+          z[(j0 + i) * CC + t] = v;
+          // rows past the block are never reached
+#pragma unroll
+          for (uint32_t k = 1; k < NB; ++k) x[k - 1] = x[k] - L[pk(min(j0 + i + k, j1 - 1), j0 + i)] * v;
+        }
+      }
       __syncthreads();
-      for (uint32_t e = t; e < (T - 1 - i) * cc; e += kPolyThreads) {
-        const uint32_t k = i + 1 + e / cc, c = e % cc;
-        z[k * CC + c] -= L[pk(k, i)] * z[i * CC + c];
+      for (uint32_t e = t; e < (T - j1) * cc; e += kSolveThreads) {
+        const uint32_t k = j1 + e / cc, c = e % cc;
+        const double *lk = L + pk(k, j0), *zi = z + j0 * CC + c; // nb == NB here
+        double v = z[k * CC + c];
+#pragma unroll
+        for (uint32_t i = 0; i < NB; ++i) v -= lk[i] * zi[i * CC];
+        z[k * CC + c] = v;
       }
     }
-    for (uint32_t i = T; i-- > 0;) {
+    for (uint32_t j0 = last + NB; j0 > 0;) {
+      j0 -= NB;
+      const uint32_t nb = min(NB, T - j0);
       __syncthreads();
-      if (t < cc) z[i * CC + t] /= L[pk(i, i)];
+      if (t < cc) {
+#pragma unroll
+        for (uint32_t k = 0; k < NB; ++k) x[k] = k < nb ? z[(j0 + nb - 1 - k) * CC + t] : 0.0;
+#pragma unroll 1
+        for (uint32_t i = j0 + nb; i-- > j0;) {
+          const double v = x[0] / L[pk(i, i)];
+          z[i * CC + t] = v;
+#pragma unroll
+          for (uint32_t k = 1; k < NB; ++k) x[k - 1] = x[k] - L[pk(i, i >= j0 + k ? i - k : j0)] * v;
+        }
+      }
       __syncthreads();
-      for (uint32_t e = t; e < i * cc; e += kPolyThreads) {
+      for (uint32_t e = t; e < j0 * cc; e += kSolveThreads) {
         const uint32_t k = e / cc, c = e % cc;
-        z[k * CC + c] -= L[pk(i, k)] * z[i * CC + c];
+        const double *lk = L + pk(j0, k), *zi = z + j0 * CC + c;
+        double l[NB], x1[NB], v = z[k * CC + c];
+#pragma unroll
+        for (uint32_t i = 0; i < NB; ++i) { // row j0 + i starts i j0 + i (i + 1) / 2 further on
+          const uint32_t u = min(i, nb - 1);
+          l[i] = lk[u * j0 + u * (u + 1) / 2];
+          x1[i] = zi[u * CC];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < NB; ++u)
+          if (NB - 1 - u < nb) v -= l[NB - 1 - u] * x1[NB - 1 - u];
+        z[k * CC + c] = v;
       }
     }
     __syncthreads();
-    for (uint32_t e = t; e < T * cc; e += kPolyThreads) {
+    for (uint32_t e = t; e < T * cc; e += kSolveThreads) {
       const uint32_t i = e / cc, c = e % cc;
       const double v = z[i * CC + c];
       b64[(uint64_t)i * C + c0 + c] = v;
@@ -456,6 +548,242 @@ __global__ __launch_bounds__(kEvalThreads) void poly_eval(const PolyDev *__restr
   }
 }
 
+// Nested evaluation.  Consecutive configurations share the digits of all but
+// the last parameters.  With the last (non-binary) parameters of a space as
+// the inner ones, a polynomial is, for fixed outer digits, a polynomial in
+// the inner features alone: its coefficient of inner monomial m is
+//   g_m = sum over the terms t with inner part m of beta_t * outer part of t,
+// formed once per combination of outer digits, and a configuration costs M
+// multiply-adds per counter instead of T (139 terms in 11 inner monomials
+// for the last three parameters of four values of the 12-parameter space).
+// A workgroup takes runs of consecutive tiles of consecutive combinations.
+// Per tile it forms the outer parts of the terms, then g as float32 matrix
+// products on the matrix cores: rows are combinations of one subspace (the
+// tile's, put in order of subspace), columns counters, and each inner
+// monomial has its own run of terms, filled up to eights.  A wave keeps its
+// share of the coefficients in registers from tile to tile while its subspace
+// stays the same.  Then each thread evaluates one of the tile's valid
+// configurations.  Three barriers per tile; two workgroups per CU fill each
+// other's waits.
+// Measured on the 4.0M configurations of the 12-parameter space, 139 terms, 24
+// counters: 276 us; every configuration by itself (poly_eval) 982 us.  g takes
+// a third of it; writing the 385 MB alone takes 77 us.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kNestThreads = 512;
+constexpr uint32_t kNestTile = 32; // combinations per tile at most
+constexpr uint32_t kNestRows = 16; // combinations per matrix product
+constexpr uint32_t kNestRun = 4;   // consecutive tiles of one workgroup
+constexpr uint32_t kNestLdx = 35;  // features of a combination, then 1 and 0
+
+template <int CB>
+__global__ __launch_bounds__(kNestThreads, CB <= 32 ? 4 : 2) void poly_eval_nested(
+    const PolyDev *__restrict__ pd, const PolyNest *__restrict__ pn,
+    const SpaceDev *__restrict__ sp, const uint32_t *__restrict__ idx,
+    const uint32_t *__restrict__ mask, const uint32_t *__restrict__ rank, uint32_t nv,
+    const float *__restrict__ beta32, uint32_t tile_n, float *__restrict__ P, uint64_t stride) {
+  extern __shared__ float4 nest_lds[]; // g [tile_n + 1][M][CB], then the parts below
+  __shared__ float xf[kNestTile * kNestLdx];
+  __shared__ float xv[CGS_MAX_PARAMS * CGS_MAX_RADIX];
+  __shared__ uint32_t slots[kNestMaxPadded];
+  __shared__ uint32_t sub[kNestTile], perm[kNestTile], group[kNestTile + 1], n_group;
+  const uint32_t T = pd->T, C = pd->C, B = pd->B, tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t M = pn->M, r_in = pn->r_in, ldv = M | 1u, K = pn->K, ldp = K | 1u;
+  const uint32_t n_slot = pn->n_slot, n_par = pn->first;
+  float *g = reinterpret_cast<float *>(nest_lds);
+  const uint32_t spare = tile_n * M * CB;
+  float *part = g + (size_t)(tile_n + 1) * M * CB;          // [tile_n][ldp] outer parts
+  float *inner = part + (size_t)tile_n * ldp + kNestSlack;  // [r_in][ldv] inner monomials
+  for (uint32_t e = tid; e < CGS_MAX_PARAMS * CGS_MAX_RADIX; e += kNestThreads) xv[e] = pd->xv32[e];
+  for (uint32_t e = tid; e < K; e += kNestThreads) slots[e] = pn->slots[e];
+  for (uint32_t e = tid; e < kNestSlack; e += kNestThreads) part[(size_t)tile_n * ldp + e] = 0.0f;
+  for (uint32_t e = tid; e < kNestTile; e += kNestThreads) {
+    xf[e * kNestLdx + 32] = 1.0f;
+    xf[e * kNestLdx + 33] = 0.0f;
+  }
+  __syncthreads();
+  for (uint32_t e = tid; e < r_in * M; e += kNestThreads) {
+    const uint32_t i = e / M, m = e - i * M, d = pn->inner[m];
+    uint64_t lo, hi;
+    decode_packed(i, sp, lo, hi); // raw index i: outer digits 0, inner digits those of i
+    float f = 1.0f;
+    for (uint32_t q = 0; q < term_count(d); ++q) {
+      const uint32_t j = term_var(d, q);
+      f *= xv[j * CGS_MAX_RADIX + digit_of(lo, hi, j)];
+    }
+    inner[i * ldv + m] = f;
+  }
+  // valid configurations before raw index k
+  const uint32_t n_raw = sp->n_raw;
+  auto rank_of = [&](uint32_t k) -> uint32_t {
+    const uint32_t w = min(k, n_raw - 1) >> 5;
+    const uint32_t r = rank[w], b = mask[w];
+    return k >= n_raw ? nv : r + (uint32_t)__popc(b & ((1u << (k & 31u)) - 1u));
+  };
+  const uint32_t n_outer = n_raw / r_in;
+  // the matrix products of this wave: half h of the steps, counters 16 n ..
+  constexpr int kN = (CB + 15) / 16;
+  constexpr bool kKeep = CB <= 32; // room for the coefficients beside the accumulators
+  const uint32_t row = lane & 15u, k4 = lane >> 4;
+  float bv[2 * kNestPairs];
+  uint32_t have = ~0u; // (subspace, n, h) of bv
+#pragma unroll
+  for (int u = 0; u < 2 * kNestPairs; ++u) bv[u] = 0.0f;
+
+  uint32_t bit[2] = {32u, 32u}; // subspace bits of parameters tid % 16 and that + 16
+  for (uint32_t b = 0; b < B; ++b)
+    for (uint32_t u = 0; u < 2; ++u)
+      if (pd->bin_params[b] == tid % 16 + 16 * u) bit[u] = b;
+  const uint32_t span = kNestRun * tile_n;
+  for (uint32_t s0 = blockIdx.x * span; s0 < n_outer; s0 += gridDim.x * span) {
+    const uint32_t s1 = min(n_outer, s0 + span);
+    uint32_t l0 = rank_of(s0 * r_in);
+    uint32_t l1 = rank_of(min(s0 + tile_n, s1) * r_in);
+    uint32_t raw = l0 < l1 ? idx[min(l0 + tid, l1 - 1)] : 0u;
+    for (uint32_t p0 = s0; p0 < s1; p0 += tile_n) {
+      const uint32_t np = min(tile_n, s1 - p0);
+      // the next tile's range (its first index is loaded once this is here)
+      const uint32_t l2 = p0 + tile_n < s1 ? rank_of(min(p0 + 2 * tile_n, s1) * r_in) : l1;
+      uint32_t raw_next = 0;
+      if (l0 < l1) { // uniform: the tile has valid configurations
+        // 16 threads per combination: the features of its outer digits
+        for (uint32_t i = tid / 16; i < np; i += kNestThreads / 16) {
+          uint64_t lo, hi;
+          decode_packed((p0 + i) * r_in, sp, lo, hi);
+          uint32_t s = 0;
+#pragma unroll
+          for (uint32_t u = 0; u < 2; ++u) {
+            const uint32_t j = tid % 16 + 16 * u, digit = digit_of(lo, hi, j);
+            if (j < n_par) xf[i * kNestLdx + j] = xv[j * CGS_MAX_RADIX + digit];
+            s |= bit[u] < 32u ? digit << bit[u] : 0u;
+          }
+#pragma unroll
+          for (int o = 1; o < 16; o <<= 1) s |= (uint32_t)__shfl_xor((int)s, o, 16);
+          if (tid % 16 == 0) sub[i] = s;
+        }
+        lds_barrier();
+        if (tid < 64) { // in order of subspace, in groups of up to kNestRows of one
+          const uint32_t mine = lane < np ? sub[lane] : ~0u;
+          uint32_t pos = 0, same = 0; // same: earlier ones of the same subspace
+#pragma unroll
+          for (uint32_t k = 0; k < kNestTile; ++k) {
+            const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, k);
+            const uint32_t before = other == mine && k < lane;
+            same += before;
+            pos += other < mine ? 1u : before;
+          }
+          if (lane < np) perm[pos] = lane;
+          // positions that start a group, as bits
+          uint32_t starts = lane < np && same % kNestRows == 0 ? 1u << pos : 0u;
+#pragma unroll
+          for (int o = 1; o < 64; o <<= 1) starts |= (uint32_t)__shfl_xor((int)starts, o, 64);
+          if (lane < np && (starts >> lane & 1u))
+            group[__popc(starts & ((1u << lane) - 1u))] = lane;
+          if (lane == 0) {
+            const uint32_t n = (uint32_t)__popc(starts);
+            group[n] = np;
+            n_group = n;
+          }
+        }
+        for (uint32_t i = tid / 16; i < np; i += kNestThreads / 16) {
+          const float *x = xf + i * kNestLdx;
+#pragma unroll 4
+          for (uint32_t t = tid % 16; t < K; t += 16) {
+            const uint32_t d = slots[t];
+            float f = x[d & 255u];
+            for (uint32_t q = 1; q < n_slot; ++q) f *= x[d >> (8 * q) & 255u];
+            part[i * ldp + t] = f;
+          }
+        }
+        lds_barrier();
+        const uint32_t n_role = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_group) * kN * 2;
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / 64));
+        for (uint32_t role = wave; role < n_role; role += kNestThreads / 64) {
+          const uint32_t h = role & 1u, n = (role >> 1) % kN, q = (role >> 1) / kN;
+          const uint32_t r0 = group[q], rows = group[q + 1] - r0;
+          const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)sub[perm[r0]]);
+          const uint32_t pair0 = h ? pn->split : 0u;
+          const uint32_t pairs = (h ? K / 8 : pn->split) - pair0;
+          const uint32_t key = (s * kN + n) * 2 + h, c = 16 * n + row;
+          if (!kKeep || key != have) {
+            have = key;
+            const float *b = beta32 + (size_t)s * T * C + min(c, C - 1);
+#pragma unroll
+            for (int u = 0; u < 2 * kNestPairs; ++u) {
+              // the term in the low byte, or bit 31: none (a zero, whatever the value read)
+              const int32_t t = pn->order[min(8 * pair0 + 4 * u + k4, K - 1)];
+              bv[u] = __int_as_float(__float_as_int(b[(t & 255) * C]) & ~(t >> 31));
+            }
+          }
+          const float *a = part + perm[r0 + min(row, rows - 1)] * ldp + 8 * pair0 + k4;
+          float *out[4]; // rows that do not exist are written to the spare row
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const uint32_t i = 4 * k4 + r;
+            out[r] = g + (i < rows && c < CB ? perm[r0 + i] * M * CB + c : spare) +
+                     (h ? pn->split_m : 0u) * CB;
+          }
+          const uint32_t ends = (uint32_t)__builtin_amdgcn_readfirstlane(
+              (int)(uint32_t)(pn->ends >> pair0)); // last pairs of the monomials
+          v4f acc0 = v4f{0.0f, 0.0f, 0.0f, 0.0f}, acc1 = acc0;
+#pragma unroll
+          for (int u0 = 0; u0 < kNestPairs; u0 += 4) {
+            if ((uint32_t)u0 >= pairs) break;
+            float av[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) av[u] = a[8 * u0 + 4 * u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[2 * u], bv[2 * (u0 + u)], acc0, 0, 0, 0);
+              acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[2 * u + 1], bv[2 * (u0 + u) + 1], acc1,
+                                                          0, 0, 0);
+              if (ends >> (u0 + u) & 1u) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  *out[r] = acc0[r] + acc1[r];
+                  out[r] += CB;
+                }
+                acc0 = acc1 = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+              }
+            }
+          }
+        }
+        if (l1 < l2) raw_next = idx[min(l1 + tid, l2 - 1)];
+        lds_barrier();
+        for (uint32_t l = l0 + tid; l < l1; l += kNestThreads) {
+          const uint32_t q = fastdiv(raw, pn->div_in);
+          const float *v = inner + (raw - q * r_in) * ldv;
+          const float4 *gp = reinterpret_cast<const float4 *>(g + (size_t)(q - p0) * M * CB);
+          if (l + kNestThreads < l1) raw = idx[l + kNestThreads];
+          float acc[CB];
+#pragma unroll
+          for (int c = 0; c < CB; ++c) acc[c] = 0.0f;
+          for (uint32_t m = 0; m < M; ++m) {
+            const float f = v[m];
+#pragma unroll
+            for (int c4 = 0; c4 < CB / 4; ++c4) {
+              const float4 b = gp[m * (CB / 4) + c4];
+              acc[4 * c4] += f * b.x;
+              acc[4 * c4 + 1] += f * b.y;
+              acc[4 * c4 + 2] += f * b.z;
+              acc[4 * c4 + 3] += f * b.w;
+            }
+          }
+          // the loads in flight are waited for here, so that no wait falls behind the stores
+          asm volatile("" ::"v"(raw), "v"(raw_next));
+#pragma unroll
+          for (int c = 0; c < CB; ++c)
+            if ((uint32_t)c < C) P[(uint64_t)c * stride + l] = fmaxf(acc[c], 0.0f); // counters >= 0
+        }
+      } else if (l1 < l2) {
+        raw_next = idx[min(l1 + tid, l2 - 1)];
+      }
+      l0 = l1;
+      l1 = l2;
+      raw = raw_next;
+    }
+  }
+}
+
 template <typename K> hipError_t allow_lds(K kernel, size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
   return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
@@ -521,22 +849,70 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
   const size_t lds = poly_solve_lds(T, C);
   e = allow_lds(poly_solve, lds);
   if (e != hipSuccess) return e;
-  poly_solve<<<S, kPolyThreads, lds, stream>>>(d_pd, d_G, poly_solve_cc(T, C), d_beta64,
+  poly_solve<<<S, kSolveThreads, lds, stream>>>(d_pd, d_G, poly_solve_cc(T, C), d_beta64,
                                                d_beta32, d_err);
   return hipGetLastError();
 }
 
-hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const SpaceDev *d_space,
-                            const uint32_t *d_idx, uint32_t nv, const float *d_beta32, float *d_P,
-                            uint64_t stride, hipStream_t stream) {
+namespace {
+
+// Outer combinations per tile of the nested evaluation: the most that leave
+// room for two workgroups in a CU's LDS, or for one (0: not even eight).
+uint32_t nest_tile(int CB, const PolyNest &n, size_t *lds) {
+  if (n.M == 0) return 0;
+  const size_t fixed = ((size_t)n.r_in * (n.M | 1) + kNestSlack + (size_t)n.M * CB) * 4;
+  const size_t per = ((size_t)n.M * CB + (n.K | 1)) * 4;
+  constexpr size_t kStatic = 10 * 1024; // the kernel's own arrays
+  for (size_t room : {80 * 1024 - kStatic, 160 * 1024 - kStatic})
+    for (uint32_t tile = kNestTile; tile >= 8; tile /= 2)
+      if (fixed + tile * per <= room) {
+        *lds = fixed + tile * per;
+        return tile;
+      }
+  return 0;
+}
+
+} // namespace
+
+// Nested wherever the space has inner parameters (poly_nest: eight or more
+// combinations, so that forming g pays: 276 against 982 us above) and a tile
+// of combinations fits in LDS; otherwise every configuration by itself.
+hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const PolyNest &nest,
+                            const PolyNest *d_nest, const SpaceDev *d_space, uint32_t n_raw,
+                            const uint32_t *d_idx, const uint32_t *d_mask,
+                            const uint32_t *d_rank, uint32_t nv, const float *d_beta32,
+                            float *d_P, uint64_t stride, hipStream_t stream) {
   const int CB = C <= 8 ? 8 : C <= 16 ? 16 : C <= 24 ? 24 : C <= 32 ? 32 : C <= 48 ? 48 : 64;
+  hipError_t e = hipSuccess;
+  size_t nest_lds = 0;
+  if (const uint32_t tile = nest_tile(CB, nest, &nest_lds)) {
+    const uint32_t n_outer = n_raw / nest.r_in;
+    const uint32_t span = kNestRun * tile;
+    const uint32_t grid = std::min<uint32_t>((n_outer + span - 1) / span, 1u << 20);
+#define CGS_POLY_NEST(CBV)                                                                      \
+  do {                                                                                          \
+    e = allow_lds(poly_eval_nested<CBV>, nest_lds);                                             \
+    if (e == hipSuccess)                                                                        \
+      poly_eval_nested<CBV><<<grid, kNestThreads, nest_lds, stream>>>(                          \
+          d_pd, d_nest, d_space, d_idx, d_mask, d_rank, nv, d_beta32, tile, d_P, stride);       \
+  } while (0)
+    switch (CB) {
+    case 8: CGS_POLY_NEST(8); break;
+    case 16: CGS_POLY_NEST(16); break;
+    case 24: CGS_POLY_NEST(24); break;
+    case 32: CGS_POLY_NEST(32); break;
+    case 48: CGS_POLY_NEST(48); break;
+    default: CGS_POLY_NEST(64); break;
+    }
+#undef CGS_POLY_NEST
+    return e != hipSuccess ? e : hipGetLastError();
+  }
   const size_t per = (size_t)T * CB * 4;
   const uint32_t SG = (uint32_t)std::max<size_t>(1, std::min<size_t>(S, kEvalLds / per));
   const uint32_t groups = (S + SG - 1) / SG;
   const size_t lds = SG * per;
   const uint32_t grid = std::max<uint32_t>(
       1, std::min<uint32_t>(1024, (nv + kEvalThreads - 1) / kEvalThreads));
-  hipError_t e = hipSuccess;
 #define CGS_POLY_EVAL(CBV)                                                                      \
   do {                                                                                          \
     e = allow_lds(poly_eval<CBV>, lds);                                                         \
