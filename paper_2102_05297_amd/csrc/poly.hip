@@ -97,13 +97,28 @@ __global__ __launch_bounds__(kPolyThreads) void poly_design_write(
 }
 
 // ---------------------------------------------------------------- fit
-// F[i][t]: basis term t of point i for t < T, its counter t - T for t >= T;
-// sub[i]: its subspace.  err bit 0: a point outside the valid list, bit 1: a
-// non-finite target.
+// sub[i]: the subspace of point i, S where it is outside the valid list.  Here
+// and not on the host, where the divisions of the points' indices by the
+// radices took 0.65 ms for 20,736 points of 12 parameters.
+__global__ __launch_bounds__(kPolyThreads) void poly_subspaces(
+    const PolyDev *__restrict__ pd, const SpaceDev *__restrict__ sp,
+    const uint32_t *__restrict__ idx, uint32_t nv, const uint32_t *__restrict__ pts, uint32_t n,
+    uint32_t *__restrict__ sub) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (uint64_t)gridDim.x * blockDim.x) {
+    const uint32_t p = pts[i];
+    uint64_t lo = 0, hi = 0;
+    if (p < nv) decode_packed(idx[p], sp, lo, hi);
+    sub[i] = p < nv ? subspace_of(pd, lo, hi) : (uint32_t)pd->S;
+  }
+}
+
+// F[i][t]: basis term t of point i for t < T, its counter t - T for t >= T.
+// err bit 0: a point outside the valid list, bit 1: a non-finite target.
 __global__ __launch_bounds__(kPolyThreads) void poly_features(
     const PolyDev *__restrict__ pd, const SpaceDev *__restrict__ sp,
     const uint32_t *__restrict__ idx, uint32_t nv, const uint32_t *__restrict__ pts,
-    const float *__restrict__ Y, uint32_t n, double *__restrict__ F, uint32_t *__restrict__ sub,
+    const float *__restrict__ Y, uint32_t n, double *__restrict__ F,
     uint32_t *__restrict__ err) {
   const uint32_t T = pd->T, C = pd->C, Ta = T + C;
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < (uint64_t)n * Ta;
@@ -127,7 +142,6 @@ __global__ __launch_bounds__(kPolyThreads) void poly_features(
       v = isfinite(y) ? (double)y : 0.0;
     }
     F[e] = v;
-    if (t == 0) sub[i] = subspace_of(pd, lo, hi);
   }
 }
 
@@ -823,9 +837,17 @@ uint32_t poly_gram_parts(int S, uint32_t n_pairs) {
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(8, 1024 / std::max<uint64_t>(wgs, 1)));
 }
 
+hipError_t launch_poly_subspaces(const PolyDev *d_pd, const SpaceDev *d_space,
+                                 const uint32_t *d_idx, uint32_t nv, const uint32_t *d_pts,
+                                 uint32_t n, uint32_t *d_sub, hipStream_t stream) {
+  const uint32_t grid = std::min<uint32_t>(4096, (n + kPolyThreads - 1) / kPolyThreads);
+  poly_subspaces<<<grid, kPolyThreads, 0, stream>>>(d_pd, d_space, d_idx, nv, d_pts, n, d_sub);
+  return hipGetLastError();
+}
+
 hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const SpaceDev *d_space,
                            const uint32_t *d_idx, uint32_t nv, const uint32_t *d_pts,
-                           const float *d_Y, uint32_t n, double *d_F, uint32_t *d_sub,
+                           const float *d_Y, uint32_t n, double *d_F,
                            const uint32_t *d_list, const uint32_t *d_off,
                            const uint32_t *d_pairs, uint32_t n_pairs, double *d_G, double *d_Gp,
                            double *d_beta64, float *d_beta32, uint32_t *d_err,
@@ -833,7 +855,7 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
   const uint64_t fe = (uint64_t)n * (T + C);
   const uint32_t gf = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(8192, (fe + 255) / 256));
   poly_features<<<gf, kPolyThreads, 0, stream>>>(d_pd, d_space, d_idx, nv, d_pts, d_Y, n, d_F,
-                                                 d_sub, d_err);
+                                                 d_err);
   const size_t gram_lds = (size_t)2 * kGramChunk * (kGB + 1) * sizeof(double);
   hipError_t e = allow_lds(poly_gram, gram_lds);
   if (e != hipSuccess) return e;
