@@ -116,7 +116,31 @@ struct cgs_space_s {
   uint32_t *d_mask = nullptr;
   uint32_t *d_idx = nullptr;
   uint32_t *d_rank = nullptr;  // valid configurations before each mask word
-  std::vector<uint32_t> h_idx; // valid raw indices, for raw -> valid lookups
+  // raw <-> valid on the host: the validity mask and the valid configurations
+  // before each tile of kEnumTile raw indices (pinned, pooled), which is a
+  // quarter to a hundredth of the list of raw indices
+  uint32_t *h_mask = nullptr, *h_tile_off = nullptr;
+  // valid configurations below raw index k < n_raw
+  uint64_t valid_below(uint64_t k) const {
+    uint64_t w = k / kEnumTile * (kEnumTile / 32), r = h_tile_off[k / kEnumTile];
+    for (; w < k / 32; ++w) r += (uint64_t)__builtin_popcount(h_mask[w]);
+    return r + (uint64_t)__builtin_popcount(h_mask[w] & ((1u << (k % 32)) - 1u));
+  }
+  bool is_valid(uint64_t k) const { return k < n_raw && (h_mask[k / 32] >> (k % 32) & 1u); }
+  // raw index of valid configuration l < n_valid
+  uint64_t raw_of(uint64_t l) const {
+    const uint32_t n_tiles = (uint32_t)((n_raw + kEnumTile - 1) / kEnumTile);
+    uint64_t w = (uint64_t)(std::upper_bound(h_tile_off, h_tile_off + n_tiles, l) - h_tile_off - 1);
+    uint64_t left = l - h_tile_off[w];
+    for (w *= kEnumTile / 32;; ++w) {
+      const uint64_t n = (uint64_t)__builtin_popcount(h_mask[w]);
+      if (left < n) break;
+      left -= n;
+    }
+    uint32_t bits = h_mask[w];
+    for (; left > 0; --left) bits &= bits - 1u;
+    return 32 * w + (uint64_t)__builtin_ctz(bits);
+  }
   // scratch for the standalone sampler
   DrawResult *d_res = nullptr;
   DrawResult *h_res = nullptr;
@@ -284,6 +308,8 @@ void destroy_space(cgs_space sp) {
   dfree(sp->d_idx);
   dfree(sp->d_rank);
   pfree(sp->h_res);
+  pfree(sp->h_mask);
+  pfree(sp->h_tile_off);
   if (sp->own_stream) pool::stream_put(sp->stream);
   delete sp;
   pool::detach();
@@ -374,19 +400,24 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
   const uint32_t n_tiles = enumeration_tiles((uint32_t)n_raw);
   uint32_t *d_tile_count = nullptr, *d_tile_off = nullptr;
   uint64_t *d_total = nullptr;
+  uint8_t *d_tables = nullptr;
   hipError_t e = dalloc(&d_tile_count, n_tiles);
   if (e == hipSuccess) e = dalloc(&d_tile_off, n_tiles);
   if (e == hipSuccess) e = dalloc(&d_total, 1);
+  if (e == hipSuccess) e = dalloc(&d_tables, enumeration_table_bytes());
+  if (e == hipSuccess) e = palloc(&sp->h_mask, (uint32_t **)nullptr, desc.n_words);
+  if (e == hipSuccess) e = palloc(&sp->h_tile_off, (uint32_t **)nullptr, n_tiles);
   auto free_tmp = [&]() {
     settle(e, sp->stream);
     dfree(d_tile_count);
     dfree(d_tile_off);
     dfree(d_total);
+    dfree(d_tables);
   };
   if (e == hipSuccess)
     e = hipMemcpyAsync(sp->d_desc, &desc, sizeof(desc), hipMemcpyHostToDevice, sp->stream);
   if (e == hipSuccess)
-    e = launch_enumeration(sp->d_desc, (uint32_t)n_raw, sp->d_mask, d_tile_count, d_tile_off,
+    e = launch_enumeration(desc, sp->d_desc, d_tables, sp->d_mask, d_tile_count, d_tile_off,
                            d_total, nullptr, nullptr, 0, sp->stream);
   uint64_t n_valid = 0;
   if (e == hipSuccess)
@@ -395,19 +426,14 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
   // whole runs of draw weights (draws load the raw indices with the scores)
   if (e == hipSuccess) e = dalloc(&sp->d_idx, (n_valid + 63) & ~(uint64_t)63);
   if (e == hipSuccess && n_valid > 0)
-    e = launch_enumeration(sp->d_desc, (uint32_t)n_raw, sp->d_mask, d_tile_count, d_tile_off,
+    e = launch_enumeration(desc, sp->d_desc, d_tables, sp->d_mask, d_tile_count, d_tile_off,
                            d_total, sp->d_idx, sp->d_rank, 1, sp->stream);
-  if (e == hipSuccess && n_valid > 0) {
-    try {
-      sp->h_idx.resize(n_valid);
-    } catch (...) {
-      (void)hipStreamSynchronize(sp->stream);
-      free_tmp();
-      return guard(fail(CGS_ENOMEM, "host copy of the valid list"));
-    }
-    e = hipMemcpyAsync(sp->h_idx.data(), sp->d_idx, n_valid * sizeof(uint32_t),
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sp->h_mask, sp->d_mask, desc.n_words * sizeof(uint32_t),
                        hipMemcpyDeviceToHost, sp->stream);
-  }
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(sp->h_tile_off, d_tile_off, n_tiles * sizeof(uint32_t),
+                       hipMemcpyDeviceToHost, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
   free_tmp();
   if (e != hipSuccess)
@@ -439,10 +465,7 @@ extern "C" cgs_status cgs_space_decode(cgs_space sp, uint64_t k, int32_t *digits
 
 namespace {
 int64_t valid_index_of(cgs_space sp, uint64_t k) {
-  if (k >= sp->n_raw) return -1;
-  auto it = std::lower_bound(sp->h_idx.begin(), sp->h_idx.end(), (uint32_t)k);
-  if (it == sp->h_idx.end() || *it != (uint32_t)k) return -1;
-  return (int64_t)(it - sp->h_idx.begin());
+  return sp->is_valid(k) ? (int64_t)sp->valid_below(k) : -1;
 }
 } // namespace
 
@@ -1310,7 +1333,7 @@ extern "C" cgs_status cgs_tuning_run(cgs_session s, cgs_model m, const float *ru
   if (st == CGS_EEMPTY) st = CGS_OK;
   while (st == CGS_OK && have) {
     if (test(c, true)) break;
-    st = cgs_search_step(s, m, sp->h_idx[c], nullptr, counters + c * 24, expert);
+    st = cgs_search_step(s, m, sp->raw_of(c), nullptr, counters + c * 24, expert);
     if (st != CGS_OK) break;
     float best = INFINITY;
     bool next = false, stop = false;
@@ -2494,12 +2517,9 @@ cgs_status mlp_sample_rmse(cgs_model mlp, cgs_model tree, const uint32_t *sample
                            double *rmse) {
   cgs_space sp = mlp->space;
   if (n == 0 || n > 0xffffffffull) return fail(CGS_ERANGE, "need 1 .. 2^32-1 samples");
-  std::vector<uint32_t> raw(n);
-  for (uint64_t i = 0; i < n; ++i) {
+  for (uint64_t i = 0; i < n; ++i)
     if (sample[i] >= sp->n_valid)
       return fail(CGS_EINVAL, "sample %llu outside the valid list", (unsigned long long)i);
-    raw[i] = sp->h_idx[sample[i]];
-  }
   const int C = mlp->n_counters;
   const uint64_t stride = (n + 63) & ~(uint64_t)63;
   const uint32_t grid = (uint32_t)std::min<uint64_t>((n + 255) / 256, 1024);
@@ -2513,8 +2533,7 @@ cgs_status mlp_sample_rmse(cgs_model mlp, cgs_model tree, const uint32_t *sample
   if (e == hipSuccess) e = dalloc(&d_part, grid);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_s, sample, n * sizeof(uint32_t), hipMemcpyHostToDevice, sp->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_raw, raw.data(), n * sizeof(uint32_t), hipMemcpyHostToDevice, sp->stream);
+  if (e == hipSuccess) e = launch_gather_idx(sp->d_idx, d_s, (uint32_t)n, d_raw, sp->stream);
   if (e == hipSuccess) {
     MlpFwdArgs a = mlp_args(mlp);
     a.idx = d_raw;
@@ -3612,7 +3631,7 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
       st = cgs_expert_system(counters + r.c * 24, expert, bn, d, nullptr);
       if (st != CGS_OK) return release(fail(st, "run %d: expert system rejected the counters", i));
       for (int c = 0; c < 24; ++c) deltas[(size_t)j * 24 + c] = (float)d[c];
-      prof[j] = sp->h_idx[r.c];
+      prof[j] = sp->raw_of(r.c);
       st = take_uniform(i, &u64[j]);
       if (st != CGS_OK) return release(st);
       r.best = INFINITY;

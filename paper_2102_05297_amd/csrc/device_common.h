@@ -44,43 +44,26 @@ __device__ __forceinline__ uint32_t uabs32(int32_t v) {
   return v < 0 ? (uint32_t)(-(int64_t)v) : (uint32_t)v;
 }
 
-// AND of all constraints for one configuration.  `table` is the space's value
-// table staged in LDS.
-__device__ __forceinline__ bool satisfies_all(const SpaceDev *__restrict__ sp,
-                                              const int32_t *table, uint64_t lo, uint64_t hi) {
-  bool ok = true;
-  const int nc = sp->n_cons;
-  for (int c = 0; c < nc; ++c) {
-    const uint32_t code = sp->cons_code[c];
-    const uint32_t kind = code & 0xffu, a = (code >> 8) & 0xffu, b = (code >> 16) & 0xffu,
-                   cc = code >> 24;
-    const int64_t bound = sp->cons_bound[c];
-    const int32_t va = table[a * CGS_MAX_RADIX + digit_of(lo, hi, a)];
-    const int32_t vb = table[b * CGS_MAX_RADIX + digit_of(lo, hi, b)];
-    const int32_t vc = table[cc * CGS_MAX_RADIX + digit_of(lo, hi, cc)];
-    bool r;
-    switch (kind) {
-    case CGS_DIV: {
-      const uint32_t d = uabs32(vb);
-      r = d != 0 && (uabs32(va) % d) == 0;
-      break;
-    }
-    case CGS_DIV2: {
-      // |v| < 2^20, so |vb * vc| < 2^40; a divisor larger than |va| divides
-      // only va == 0.
-      const uint64_t d = (uint64_t)uabs32(vb) * (uint64_t)uabs32(vc);
-      const uint32_t n = uabs32(va);
-      r = d != 0 && (d > n ? n == 0 : (n % (uint32_t)d) == 0);
-      break;
-    }
-    case CGS_PROD_LE: r = (int64_t)va * vb <= bound; break;
-    case CGS_PROD3_LE: r = (int64_t)va * vb * vc <= bound; break;
-    case CGS_PROD_GE: r = (int64_t)va * vb >= bound; break;
-    default: r = va <= vb; break; // CGS_LE
-    }
-    ok = ok && r;
+// One constraint of kind `kind` for the values of its parameters.
+__device__ __forceinline__ bool satisfies(uint32_t kind, int64_t bound, int32_t va, int32_t vb,
+                                          int32_t vc) {
+  switch (kind) {
+  case CGS_DIV: {
+    const uint32_t d = uabs32(vb);
+    return d != 0 && (uabs32(va) % d) == 0;
   }
-  return ok;
+  case CGS_DIV2: {
+    // |v| < 2^20, so |vb * vc| < 2^40; a divisor larger than |va| divides
+    // only va == 0.
+    const uint64_t d = (uint64_t)uabs32(vb) * (uint64_t)uabs32(vc);
+    const uint32_t n = uabs32(va);
+    return d != 0 && (d > n ? n == 0 : (n % (uint32_t)d) == 0);
+  }
+  case CGS_PROD_LE: return (int64_t)va * vb <= bound;
+  case CGS_PROD3_LE: return (int64_t)va * vb * vc <= bound;
+  case CGS_PROD_GE: return (int64_t)va * vb >= bound;
+  default: return va <= vb; // CGS_LE
+  }
 }
 
 // Order-preserving map float -> uint32 (a < b  <=>  key(a) < key(b) for

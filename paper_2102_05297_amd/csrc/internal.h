@@ -204,10 +204,18 @@ struct MlpFwdArgs {
 hipError_t launch_mlp_forward(const MlpFwdArgs &a, bool train, hipStream_t stream);
 
 // ---- launchers (each enqueues on `stream`; return hipSuccess or an error)
-hipError_t launch_enumeration(const SpaceDev *d_space, uint32_t n_raw, uint32_t *d_mask,
-                              uint32_t *d_tile_count, uint32_t *d_tile_off, uint64_t *d_total,
-                              uint32_t *d_idx, uint32_t *d_rank, int phase, hipStream_t stream);
+constexpr uint32_t kEnumTile = 2048; // raw indices per tile of the enumeration
+// d_tables: enumeration_table_bytes(), read until phase 0 is done; d_tile_off
+// [enumeration_tiles]: valid configurations before each tile.
+size_t enumeration_table_bytes();
+hipError_t launch_enumeration(const SpaceDev &space, const SpaceDev *d_space, void *d_tables,
+                              uint32_t *d_mask, uint32_t *d_tile_count, uint32_t *d_tile_off,
+                              uint64_t *d_total, uint32_t *d_idx, uint32_t *d_rank, int phase,
+                              hipStream_t stream);
 uint32_t enumeration_tiles(uint32_t n_raw);
+// d_raw[i] = d_idx[d_pos[i]], positions checked by the caller.
+hipError_t launch_gather_idx(const uint32_t *d_idx, const uint32_t *d_pos, uint32_t n,
+                             uint32_t *d_raw, hipStream_t stream);
 
 hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, uint32_t n_valid,
                               const uint16_t *d_nodes, const float *d_leaves, int n_trees,
