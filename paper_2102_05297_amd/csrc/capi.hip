@@ -120,6 +120,12 @@ struct cgs_space_s {
   // before each tile of kEnumTile raw indices (pinned, pooled), which is a
   // quarter to a hundredth of the list of raw indices
   uint32_t *h_mask = nullptr, *h_tile_off = nullptr;
+  // tests digit > threshold there are: r - 1 per parameter
+  int n_bits() const {
+    int b = 0;
+    for (int32_t r : radix) b += r - 1;
+    return b;
+  }
   // valid configurations below raw index k < n_raw
   uint64_t valid_below(uint64_t k) const {
     uint64_t w = k / kEnumTile * (kEnumTile / 32), r = h_tile_off[k / kEnumTile];
@@ -609,8 +615,8 @@ cgs_status evaluate_model(cgs_model m) {
   hipError_t e = hipSuccess;
   if (m->kind == 0) {
     e = launch_forest_eval(sp->d_desc, sp->d_idx, (uint32_t)sp->n_valid, m->d_nodes, m->d_leaves,
-                           m->n_trees, m->depth, m->n_counters, m->d_P, m->stride, nullptr, 0, 0,
-                           sp->stream);
+                           m->n_trees, m->depth, m->n_counters, sp->n_bits(), m->d_P, m->stride,
+                           nullptr, 0, 0, sp->stream);
   } else if (m->kind == 3) {
     // predictions given by the caller: nothing to evaluate
   } else if (m->kind == 2) {
@@ -1520,7 +1526,7 @@ extern "C" cgs_status cgs_model_copy_leaf_ids(cgs_model m, uint64_t first, uint6
   uint16_t *d_out = nullptr;
   HIP_TRY(dalloc(&d_out, (size_t)m->n_trees * count));
   hipError_t e = launch_forest_eval(sp->d_desc, sp->d_idx, (uint32_t)sp->n_valid, m->d_nodes,
-                                    m->d_leaves, m->n_trees, m->depth, m->n_counters, m->d_P,
+                                    m->d_leaves, m->n_trees, m->depth, m->n_counters, sp->n_bits(), m->d_P,
                                     m->stride, d_out, (uint32_t)first, (uint32_t)count, sp->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(dst, d_out, (size_t)m->n_trees * count * sizeof(uint16_t),

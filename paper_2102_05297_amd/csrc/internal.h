@@ -217,9 +217,10 @@ uint32_t enumeration_tiles(uint32_t n_raw);
 hipError_t launch_gather_idx(const uint32_t *d_idx, const uint32_t *d_pos, uint32_t n,
                              uint32_t *d_raw, hipStream_t stream);
 
+// n_bits: the sum of the radices less one of each parameter (the space's tests).
 hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, uint32_t n_valid,
                               const uint16_t *d_nodes, const float *d_leaves, int n_trees,
-                              int depth, int n_counters, float *d_P, uint64_t stride,
+                              int depth, int n_counters, int n_bits, float *d_P, uint64_t stride,
                               uint16_t *d_leaf_out, uint32_t leaf_first, uint32_t leaf_count,
                               hipStream_t stream);
 
