@@ -184,7 +184,7 @@ struct cgs_model_s {
   __bf16 *d_xt = nullptr, *d_h1t = nullptr, *d_h2t = nullptr, *d_dyt = nullptr,
          *d_dz2t = nullptr, *d_dz1t = nullptr;
   float *d_bp1 = nullptr, *d_bp2 = nullptr, *d_bp3 = nullptr, *d_lossp = nullptr,
-        *d_y = nullptr;
+        *d_y = nullptr, *d_g2t = nullptr;
   // gathered features [kGatherSteps][rows rounded up to 32][K1] and targets
   // [kGatherSteps][rows][C] of a run of steps
   __bf16 *d_xg = nullptr;
@@ -522,6 +522,7 @@ void free_mlp_scratch(cgs_model m) {
   dfree(m->d_bp3);
   dfree(m->d_lossp);
   dfree(m->d_y);
+  dfree(m->d_g2t);
   dfree(m->d_xg);
   dfree(m->d_tg);
   m->scratch_rows = 0;
@@ -1568,6 +1569,7 @@ hipError_t ensure_mlp_scratch(cgs_model m, uint32_t rows) {
   if (e == hipSuccess) e = dalloc(&m->d_bp3, nblk * Cp);
   if (e == hipSuccess) e = dalloc(&m->d_lossp, nblk);
   if (e == hipSuccess) e = dalloc(&m->d_y, n_pad * Cp);
+  if (e == hipSuccess && H == 512) e = dalloc(&m->d_g2t, H * n_pad); // split steps
   if (e == hipSuccess) e = dalloc(&m->d_xg, kGatherSteps * n_pad * m->sh.K1);
   if (e == hipSuccess) e = dalloc(&m->d_tg, kGatherSteps * (size_t)rows * m->sh.C);
   if (e != hipSuccess) {
@@ -1620,6 +1622,7 @@ TrainRowsArgs train_rows_args(cgs_model m, uint32_t k, uint32_t n, bool train) {
   a.bp2 = m->d_bp2;
   a.bp3 = m->d_bp3;
   a.lossp = m->d_lossp;
+  a.g2t = m->d_g2t;
   return a;
 }
 

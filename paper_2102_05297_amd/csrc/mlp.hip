@@ -20,8 +20,9 @@
 // training forward forms GELU'(z) from the same tail (within 4e-5 of it).
 //
 // Training runs a step in two launches (the training-step section below):
-// the forward and backward chain per 32 rows of the batch, then the weight
-// gradients by 32 x 32 tiles with Adam applied where they are formed.
+// the forward and backward chain per 16 rows of the batch (two launches at
+// 512 hidden units and small batches), then the weight gradients by 32 x 32
+// tiles with Adam applied where they are formed.
 #include <algorithm>
 
 #include "device_common.h"
@@ -692,6 +693,217 @@ __global__ __launch_bounds__(train_waves<H>() * 64) void mlp_train_rows(TrainRow
   }
 }
 
+// The training rows split over columns as well, for the wide layers: a
+// workgroup of mlp_train_rows reads every weight of the layers (1.1 MB at H =
+// 512, 64 bytes a cycle at best, and 16 workgroups are all a batch of 256
+// has), so here workgroup (b, s) takes 128 columns of 16 rows, in two
+// launches, as the output layer needs all of H2 and dZ1 all of dZ2:
+//   forward:  all of H1 (one MFMA per tile), its slice of Z2, H2 and GELU'(Z2)
+//   backward: Y, dY and all of dZ2 (K = H on two tiles, K = CP on the others),
+//             its slice of dZ1, with GELU'(Z1) of the slice formed again
+// Every wave has one tile of the H-deep product and requests its weights
+// first of all.  What every slice forms is stored by one of them.  The
+// products and sums are those of mlp_train_rows, in the same order.
+// Measured at 256 rows, 32 counters: 5.9 and 7.5 us; mlp_train_rows 22.1 us.
+constexpr int kSplitThreads = 512;
+constexpr int kSplitWaves = kSplitThreads / 64; // tiles of a slice
+
+template <int H, int NB3>
+__global__ __launch_bounds__(kSplitThreads) void mlp_split_forward(TrainRowsArgs a) {
+  using TS = TrainShape<H, NB3>;
+  constexpr int KS = TS::KS, LX = TS::LX, LH = TS::LH, Q = TS::NT / kSplitWaves;
+  __shared__ __align__(16) __bf16 xs[16 * LX];
+  __shared__ __align__(16) __bf16 h1s[16 * LH];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kg = lane >> 4, r16 = lane & 15;
+  const int slice = blockIdx.y;
+  const uint32_t m0 = 16u * blockIdx.x;
+  const int tile = kSplitWaves * slice + w, col2 = 16 * tile + r16;
+  bf16x8 x = bf16x8{};
+  if (tid < 64) {
+    const int row = tid >> 2, seg = tid & 3;
+    if (8 * seg < a.K1) x = frag_at(a.xin + (size_t)(m0 + row) * a.K1 + 8 * seg);
+  }
+  bf16x8 w1f[Q], w2f[KS];
+  float bv1[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    w1f[q] = frag_at(a.w1n + ((size_t)(w + kSplitWaves * q) * 64 + lane) * 8);
+    bv1[q] = a.b1[16 * (w + kSplitWaves * q) + r16];
+  }
+  const float bv2 = a.b2[col2];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) w2f[s] = frag_at(a.w2n + (((size_t)tile * KS + s) * 64 + lane) * 8);
+  if (tid < 64) *reinterpret_cast<bf16x8 *>(xs + (tid >> 2) * LX + 8 * (tid & 3)) = x;
+  lds_barrier();
+  if (slice == 0 && tid < 128) { // X^T for dW1: 32 feature rows, zeros past K1
+    const int k = tid >> 2, seg = tid & 3;
+    bf16x4 b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = xs[(4 * seg + e) * LX + k];
+    *reinterpret_cast<bf16x4 *>(a.xt + (size_t)k * a.n_pad + m0 + 4 * seg) = b;
+  }
+  float v[4], dg[4];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) { // tile w + 8 q is in slice q
+    const int col = 16 * (w + kSplitWaves * q) + r16;
+    f32x4 acc = {bv1[q], bv1[q], bv1[q], bv1[q]};
+    acc = mfma16(frag_at(xs + r16 * LX + 8 * kg), w1f[q], acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = gelu_with_grad(acc[r], dg[r]);
+    if (q == slice) {
+      store_act4(v, h1s, LH, col, a.h1t, a.n_pad, m0, kg);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h1s[(4 * kg + r) * LH + col] = (__bf16)v[r];
+    }
+  }
+  lds_barrier();
+  f32x4 acc = {bv2, bv2, bv2, bv2};
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+    acc = mfma16(frag_at(h1s + r16 * LH + 32 * s + 8 * kg), w2f[s], acc);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = gelu_with_grad(acc[r], dg[r]);
+  store_act4(v, nullptr, 0, col2, a.h2t, a.n_pad, m0, kg);
+  *reinterpret_cast<f32x4 *>(a.g2t + (size_t)col2 * a.n_pad + m0 + 4 * kg) =
+      f32x4{dg[0], dg[1], dg[2], dg[3]};
+}
+
+template <int H, int NB3>
+__global__ __launch_bounds__(kSplitThreads) void mlp_split_backward(TrainRowsArgs a) {
+  using TS = TrainShape<H, NB3>;
+  constexpr int KS = TS::KS, LH = TS::LH, LY = TS::LY, CP = TS::CP, NT3 = TS::NT3;
+  constexpr int Q = TS::NT / kSplitWaves;
+  static_assert(NT3 <= kSplitWaves, "one output tile per wave");
+  __shared__ __align__(16) __bf16 h2s[16 * LH];
+  __shared__ __align__(16) __bf16 dz2s[16 * LH];
+  __shared__ __align__(16) __bf16 dys[16 * LY];
+  __shared__ float lred[NT3];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kg = lane >> 4, r16 = lane & 15;
+  const int slice = blockIdx.y;
+  const uint32_t blk = blockIdx.x, m0 = 16u * blk;
+  const int tile = kSplitWaves * slice + w, col1 = 16 * tile + r16, col3 = 16 * w + r16;
+  // H2's rows, four of a column per load
+  constexpr int NL = 4 * H / kSplitThreads;
+  bf16x4 h2v[NL];
+#pragma unroll
+  for (int u = 0; u < NL; ++u) {
+    const int e = tid + u * kSplitThreads;
+    h2v[u] = *reinterpret_cast<const bf16x4 *>(a.h2t + (size_t)(e >> 2) * a.n_pad + m0 + 4 * (e & 3));
+  }
+  bf16x8 w3f[KS], w3t[Q][CP / 32], w2f[KS];
+  f32x4 g2[Q];
+  float tv[4], bv3 = 0.0f;
+  if (w < NT3) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) w3f[s] = frag_at(a.w3n + (((size_t)w * KS + s) * 64 + lane) * 8);
+    bv3 = col3 < a.C ? a.b3[col3] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t m = m0 + 4 * kg + r;
+      tv[r] = (m < a.n && col3 < a.C) ? a.tin[(size_t)m * a.C + col3] : 0.0f;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int t = w + kSplitWaves * q;
+#pragma unroll
+    for (int s = 0; s < CP / 32; ++s)
+      w3t[q][s] = frag_at(a.w3t + (((size_t)t * (CP / 32) + s) * 64 + lane) * 8);
+    g2[q] = *reinterpret_cast<const f32x4 *>(a.g2t + (size_t)(16 * t + r16) * a.n_pad + m0 + 4 * kg);
+  }
+  const bf16x8 xf = 8 * kg < a.K1 ? frag_at(a.xin + (size_t)(m0 + r16) * a.K1 + 8 * kg) : bf16x8{};
+  const bf16x8 w1f = frag_at(a.w1n + ((size_t)tile * 64 + lane) * 8);
+  const float bv1 = a.b1[col1];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) w2f[s] = frag_at(a.w2t + (((size_t)tile * KS + s) * 64 + lane) * 8);
+#pragma unroll
+  for (int u = 0; u < NL; ++u) {
+    const int e = tid + u * kSplitThreads;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h2s[(4 * (e & 3) + r) * LH + (e >> 2)] = h2v[u][r];
+  }
+  lds_barrier();
+  float v[4], g1[4];
+  // Y, dY and the squared errors on waves 0 .. NT3-1
+  if (w < NT3) {
+    f32x4 acc = {bv3, bv3, bv3, bv3};
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      acc = mfma16(frag_at(h2s + r16 * LH + 32 * s + 8 * kg), w3f[s], acc);
+    float sq = 0.0f, ds = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t m = m0 + 4 * kg + r;
+      const float d = (m < a.n && col3 < a.C) ? acc[r] - tv[r] : 0.0f;
+      sq += d * d;
+      v[r] = a.scale * d;
+      ds += v[r];
+    }
+    if (slice == 0) {
+      store_act4(v, dys, LY, col3, a.dyt, a.n_pad, m0, kg);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dys[(4 * kg + r) * LY + col3] = (__bf16)v[r];
+    }
+    ds = column_sum16(ds);
+    if (slice == 0 && kg == 0) a.bp3[(size_t)blk * CP + col3] = ds;
+    sq = wave_sum(sq);
+    if (lane == 0) lred[w] = sq;
+  }
+  { // GELU'(Z1) of the wave's tile
+    f32x4 acc = {bv1, bv1, bv1, bv1};
+    acc = mfma16(xf, w1f, acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) (void)gelu_with_grad(acc[r], g1[r]);
+  }
+  lds_barrier();
+  if (slice == 0 && tid == 0) {
+    float t = lred[0];
+#pragma unroll
+    for (int i = 1; i < NT3; ++i) t += lred[i];
+    a.lossp[blk] = t;
+  }
+  // dZ2 = (dY W3) * gelu'(Z2)
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int col = 16 * (w + kSplitWaves * q) + r16;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < CP / 32; ++s)
+      acc = mfma16(frag_at(dys + r16 * LY + 32 * s + 8 * kg), w3t[q][s], acc);
+    float bs = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      v[r] = acc[r] * g2[q][r];
+      bs += v[r];
+    }
+    if (q == slice) {
+      store_act4(v, dz2s, LH, col, a.dz2t, a.n_pad, m0, kg);
+      bs = column_sum16(bs);
+      if (kg == 0) a.bp2[(size_t)blk * H + col] = bs;
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dz2s[(4 * kg + r) * LH + col] = (__bf16)v[r];
+    }
+  }
+  lds_barrier();
+  // dZ1 = (dZ2 W2) * gelu'(Z1)
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+    acc = mfma16(frag_at(dz2s + r16 * LH + 32 * s + 8 * kg), w2f[s], acc);
+  float bs = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    v[r] = acc[r] * g1[r];
+    bs += v[r];
+  }
+  store_act4(v, nullptr, 0, col1, a.dz1t, a.n_pad, m0, kg);
+  bs = column_sum16(bs);
+  if (kg == 0) a.bp1[(size_t)blk * H + col1] = bs;
+}
+
 // Gradient g of master parameter p: stored (gradient mode), or one Adam step
 // (Kingma & Ba, Algorithm 1; c1 = 1/(1 - beta1^t), c2 = 1/(1 - beta2^t))
 // followed by the bf16 copies of the new value.
@@ -890,10 +1102,26 @@ hipError_t launch_mlp_forward(const MlpFwdArgs &a, bool train, hipStream_t strea
 
 namespace {
 
+// Steps of up to kSplitRows rows are split over columns at H = 512.  Measured
+// per step (with the gradient tiles), unsplit -> split, 32 counters: 30.5 ->
+// 19.0 us at 16 rows, 33.0 -> 22.4 at 256, 40.0 -> 33.0 at 1,024, 49.3 -> 48.5
+// at 2,048 (128 workgroups unsplit), 67.2 -> 90.9 at 4,096.  H = 256, whose
+// layers are a quarter: 16.3 -> 15.6 at 256 rows, 20.7 -> 21.8 at 1,024; not
+// split.
+constexpr uint32_t kSplitRows = 1024;
+
 template <int H, int NB3>
 hipError_t launch_train_rows_h(const TrainRowsArgs &a, hipStream_t stream) {
   using TS = TrainShape<H, NB3>;
   static_assert(TS::lds <= 64 * 1024, "static launch size");
+  if constexpr (H == 512) {
+    if (a.train && a.n_pad <= kSplitRows) {
+      const dim3 grid(a.n_pad / 16, H / (16 * kSplitWaves));
+      mlp_split_forward<H, NB3><<<grid, kSplitThreads, 0, stream>>>(a);
+      mlp_split_backward<H, NB3><<<grid, kSplitThreads, 0, stream>>>(a);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL((mlp_train_rows<H, NB3>), dim3(a.n_pad / 16), dim3(TS::NW * 64), TS::lds,
                      stream, a);
   return hipGetLastError();

@@ -53,6 +53,7 @@ struct TrainRowsArgs {
   float *yout;
   __bf16 *xt, *h1t, *h2t, *dyt, *dz2t, *dz1t;
   float *bp1, *bp2, *bp3, *lossp;
+  float *g2t;               // GELU'(Z2) [H][n_pad] between the launches of a split step
 };
 hipError_t launch_mlp_train_rows(const TrainRowsArgs &a, hipStream_t stream);
 // The features (and targets) of `steps` steps of n rows: step s, row r is
