@@ -3495,10 +3495,191 @@ cgs_status small_batch_step(cgs_batch b, Pick *picks) {
 
 } // namespace
 
+namespace {
+
+// Whether the runs of a batch on a small space are made on the device from
+// start to end: where that is expected to be faster than a launch and a host
+// turn per iteration.  On the device an iteration is one workgroup's, which
+// the number of runs does not slow, and the runtimes and counters are uploaded
+// first; with the host it grows with the runs.  The microseconds below fit,
+// host -> device, with 5 draws: 1,200 configurations, 150 tests, 64 runs 2,857
+// -> 590, 8 runs 944 -> 528; 6,750, 150 tests, 64 runs 2,950 -> 964, 4 runs 867
+// -> 892; 24,654, 150 tests, 64 runs 3,810 -> 2,214, 16 runs 1,657 -> 2,111;
+// 6,750, 20 tests, 64 runs 574 -> 362, 8 runs 207 -> 297.
+bool tune_pays_on_device(uint64_t nv, int n, const cgs_tuning_opts *o) {
+  const double iters =
+      1.0 + (double)std::min<uint64_t>((uint64_t)o->max_tests, nv) / (o->draws + 1.0);
+  const double host = 31.0 + 1.2 * n + 2e-5 * (double)nv * n;
+  const double device = 13.0 + 0.0022 * (double)nv;
+  return 110.0 + 0.0075 * (double)nv + iters * device < iters * host;
+}
+
+// The runs of cgs_tuning_run_batch on the device from start to end
+// (batch_tune): arguments as there, checked; every run has a first number.
+cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *counters,
+                          const cgs_expert_params &ep, const uint64_t *uniforms,
+                          uint64_t n_uniforms, const cgs_tuning_opts *opts, double thresh,
+                          uint64_t capacity, uint64_t *tested, uint8_t *profiled,
+                          uint64_t *n_tests, uint64_t *tests_to_well) {
+  const int n = b->n;
+  const uint64_t nv = b->sess[0]->space->n_valid;
+  hipStream_t st = b->stream;
+  for (int i = 0; i < n; ++i) {
+    if (!b->sess[i]->pending) continue; // recorded outside the batch
+    const cgs_status fs = flush_pending(b->sess[i]);
+    if (fs != CGS_OK) return fs;
+    HIP_TRY(hipStreamSynchronize(b->sess[i]->space->stream));
+  }
+  TuneArgs a{};
+  a.n_uniforms = n_uniforms;
+  // an iteration tests its configuration, of at most nv, and uses draws numbers
+  const uint64_t iters = std::min<uint64_t>((uint64_t)opts->max_tests, nv);
+  a.stride_u = std::min<uint64_t>(n_uniforms, 1 + (uint64_t)opts->draws * iters);
+  std::vector<uint64_t> packed; // (copies of single rows take 10 us each)
+  if (a.stride_u < n_uniforms) {
+    try {
+      packed.resize((size_t)n * a.stride_u);
+    } catch (...) {
+      return fail(CGS_ENOMEM, "host copy of the random numbers");
+    }
+    for (int i = 0; i < n; ++i)
+      std::copy_n(uniforms + (size_t)i * n_uniforms, a.stride_u,
+                  packed.begin() + (size_t)i * a.stride_u);
+  }
+  a.max_tests = (uint64_t)opts->max_tests;
+  a.cap = std::min<uint64_t>(a.max_tests, 2 * nv); // drawn once, profiled once
+  a.thresh = thresh;
+  a.ep = ep;
+  a.draws = (uint32_t)opts->draws;
+  a.max_iters = 1024; // per launch
+  a.stop_at_well = opts->stop_at_well;
+  std::vector<TuneRun> run(n);
+  for (int i = 0; i < n; ++i) {
+    run[i] = TuneRun{};
+    run[i].state = kTuneStart;
+    run[i].parity = b->sess[i]->parity;
+  }
+  float *d_rt = nullptr;
+  double *d_ct = nullptr;
+  uint64_t *d_u = nullptr;
+  hipError_t e = dalloc(&d_rt, nv);
+  if (e == hipSuccess) e = dalloc(&d_ct, nv * 24);
+  if (e == hipSuccess) e = dalloc(&d_u, (size_t)n * a.stride_u);
+  if (e == hipSuccess) e = dalloc(&a.tested, (size_t)n * a.cap);
+  if (e == hipSuccess) e = dalloc(&a.profiled, (size_t)n * a.cap);
+  if (e == hipSuccess) e = dalloc(&a.run, n);
+  if (e == hipSuccess) e = hipMemcpyAsync(d_rt, runtime, nv * 4, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipMemcpyAsync(d_ct, counters, nv * 24 * 8, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(d_u, packed.empty() ? uniforms : packed.data(), (size_t)n * a.stride_u * 8,
+                       hipMemcpyHostToDevice, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(a.run, run.data(), n * sizeof(TuneRun), hipMemcpyHostToDevice, st);
+  a.runtime = d_rt;
+  a.counters = d_ct;
+  a.uniforms = d_u;
+  if (e == hipSuccess) e = hipEventRecord(b->e0, st);
+  bool running = true;
+  while (e == hipSuccess && running) {
+    e = launch_batch_tune(b->d_sess, a, (uint32_t)n, b->max_per, st);
+    if (e == hipSuccess) e = hipEventRecord(b->e1, st);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(run.data(), a.run, n * sizeof(TuneRun), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    running = false;
+    for (const TuneRun &r : run) running = running || r.state <= kTuneRunning;
+  }
+  float ms = 0.0f;
+  if (e == hipSuccess) e = hipEventElapsedTime(&ms, b->e0, b->e1);
+  uint64_t longest = 0;
+  uint32_t steps = 1;
+  for (const TuneRun &r : run) {
+    longest = std::max(longest, r.nt);
+    steps = std::max(steps, r.steps);
+  }
+  // the lists whole where that is small, else each run's part
+  const bool whole = (uint64_t)n * a.cap <= (uint64_t)1 << 18;
+  const uint64_t ld = whole ? a.cap : longest;
+  std::vector<uint32_t> h_tested;
+  std::vector<uint8_t> h_prof;
+  try {
+    h_tested.resize((size_t)n * ld);
+    h_prof.resize((size_t)n * ld);
+  } catch (...) {
+    if (e == hipSuccess) e = hipErrorOutOfMemory;
+  }
+  for (int i = 0; i < (whole ? 1 : n) && e == hipSuccess; ++i) {
+    const size_t from = (size_t)i * a.cap, to = (size_t)i * ld, k = whole ? n * ld : run[i].nt;
+    if (k) e = hipMemcpyAsync(h_tested.data() + to, a.tested + from, k * 4, hipMemcpyDeviceToHost, st);
+    if (k && e == hipSuccess)
+      e = hipMemcpyAsync(h_prof.data() + to, a.profiled + from, k, hipMemcpyDeviceToHost, st);
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  settle(e, st);
+  dfree(d_rt);
+  dfree(d_ct);
+  dfree(d_u);
+  dfree(a.tested);
+  dfree(a.profiled);
+  dfree(a.run);
+  if (e != hipSuccess)
+    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "tuning runs: %s",
+                hipGetErrorString(e));
+  // the sessions look as after the steps and draws one by one
+  b->last_ms = ms / (float)steps; // of a step
+  b->seq += (uint64_t)kMaxDrawSeries * steps;
+  int bad = -1;
+  uint64_t bad_at = 0;
+  for (int i = 0; i < n; ++i) {
+    const TuneRun &r = run[i];
+    cgs_session s = b->sess[i];
+    if (r.steps > 0) {
+      s->cur_acc = r.cur_acc;
+      s->parity = r.parity;
+      s->stepped = true;
+      s->pending = false;
+      s->last_nb = false;
+      s->ran_in_batch = true;
+      s->batch_ms = b->last_ms;
+      s->n_active = (int)r.n_act;
+      s->last_total = r.last_total;
+      b->h_step[i].parity = r.cur_acc;
+      b->h_step[i].profile = r.profile;
+    }
+    if (r.state == kTuneEnded) continue;
+    // the first that would have failed, one iteration of every run at a time
+    const uint64_t at = r.late ? 2 * (uint64_t)r.iters - 1 : 2 * (uint64_t)r.iters;
+    if (bad < 0 || at < bad_at) {
+      bad = i;
+      bad_at = at;
+    }
+  }
+  if (bad >= 0) {
+    if (run[bad].state == kTuneBadCounters)
+      return fail(CGS_EINVAL, "run %d: expert system rejected the counters", bad);
+    if (run[bad].state == kTuneNoNumbers)
+      return fail(CGS_ERANGE, "run %d needs more than %llu random numbers", bad,
+                  (unsigned long long)n_uniforms);
+    return fail(CGS_EDEVICE, "session %d: no pick although Q > 0", bad);
+  }
+  for (int i = 0; i < n; ++i) {
+    const TuneRun &r = run[i];
+    for (uint64_t k = 0; k < r.nt; ++k) {
+      tested[(uint64_t)i * capacity + k] = h_tested[(size_t)i * ld + k];
+      if (profiled) profiled[(uint64_t)i * capacity + k] = h_prof[(size_t)i * ld + k];
+    }
+    n_tests[i] = r.nt;
+    tests_to_well[i] = r.found;
+  }
+  return CGS_OK;
+}
+
+} // namespace
+
 // Alg. 1 for every session of a batch at once.  Each run follows exactly the
 // steps of cgs_tuning_run with its own random numbers; the runs advance in
 // lockstep.  On small spaces an iteration is one launch and a run that has
-// ended rests; otherwise it is one batch step, then batched draws, and a run
+// ended rests (or all runs are one launch, tune_on_device); otherwise it is one batch step, then batched draws, and a run
 // that has ended keeps stepping with no profile while its results are
 // ignored.
 extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
@@ -3581,6 +3762,15 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
     if (st != CGS_OK) return st;
   }
   const bool series = b->small && opts->draws <= kMaxDrawSeries;
+  if (series && tune_pays_on_device(nv, n, opts)) {
+    cgs_expert_params ep;
+    cgs_default_expert_params(&ep);
+    if (expert) ep = *expert;
+    // settings that the expert system refuses fail where it is first asked, below
+    if (ep.inst_reaction >= 0.0 && ep.inst_reaction < 1.0 && ep.cores > 0.0)
+      return tune_on_device(b, runtime, counters, ep, uniforms, n_uniforms, opts, thresh, capacity,
+                            tested, profiled, n_tests, tests_to_well);
+  }
   std::vector<Pick> picks(series ? (size_t)n * kMaxDrawSeries : 0);
   cgs_status st = CGS_OK;
   if (series) {

@@ -302,6 +302,40 @@ struct SmallJob {
 hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, uint32_t n,
                               uint32_t max_tiles, uint32_t max_per, DrawResult *d_res,
                               hipStream_t stream);
+// Whole runs of Alg. 1 in a batch of small spaces, a workgroup per session:
+// every run goes on until it ends or has made max_iters iterations.
+enum TuneState : uint32_t {
+  kTuneStart,   // the uniform first draw is to be made
+  kTuneRunning, // configuration c is to be profiled
+  kTuneEnded,
+  kTuneBadCounters, // the expert system rejects c's counters
+  kTuneNoNumbers,   // the run needs more random numbers
+  kTuneNoPick       // a draw found no owner (a defect)
+};
+struct TuneRun {
+  uint64_t nt, found, u; // tests, tests to the first good one (0: none), numbers used
+  uint64_t last_total;   // Q of the last draw
+  uint32_t c, state;
+  uint32_t iters, late;  // iterations; error: 0 before the step, 1 in its draws
+  uint32_t steps, profile, n_act;
+  int32_t parity, cur_acc;
+  uint32_t pad;
+};
+struct TuneArgs {
+  const float *runtime;     // [n_valid]
+  const double *counters;   // [n_valid][24]
+  const uint64_t *uniforms; // [n][stride_u], n_uniforms of each run's exist
+  uint64_t n_uniforms, stride_u, max_tests, cap;
+  double thresh;
+  cgs_expert_params ep;
+  uint32_t draws, max_iters;
+  int32_t stop_at_well;
+  uint32_t *tested;  // [n][cap]
+  uint8_t *profiled; // [n][cap]
+  TuneRun *run;      // [n]
+};
+hipError_t launch_batch_tune(const BatchSess *d_sess, const TuneArgs &a, uint32_t n,
+                             uint32_t max_per, hipStream_t stream);
 hipError_t launch_draw_many(const float *d_s, uint32_t *d_explored, uint32_t n_valid,
                             const StepAcc *d_acc, float gamma, float w_min, int block_log2,
                             uint64_t *d_bsum, uint32_t n_blocks, const DrawSeries &series,

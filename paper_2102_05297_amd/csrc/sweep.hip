@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "expert.h"
 
 namespace cgs {
 
@@ -764,11 +765,15 @@ struct SmallView {
 // The last workgroup's part: weighs the n_valid scores, makes the draws and
 // leaves the block sums.  Thread t owns the run of a.per consecutive weights
 // from t * per (LDS words q[t * ld ..]).
-__device__ __forceinline__ void small_draws(const SmallView &a, uint32_t *q) {
+struct SmallPicks { // position (kNoIndex: none) and Q of every draw, in LDS
+  uint32_t pos[kMaxDrawSeries];
+  uint64_t total[kMaxDrawSeries];
+};
+__device__ __forceinline__ void small_draws(const SmallView &a, uint32_t *q, SmallPicks &picks) {
   __shared__ uint64_t scratch[kSmallThreads / kWave];
   __shared__ StepAccSums sums;
-  __shared__ uint32_t pick_pos[kMaxDrawSeries];
-  __shared__ uint64_t pick_total[kMaxDrawSeries];
+  uint32_t *pick_pos = picks.pos;
+  uint64_t *pick_total = picks.total;
   constexpr uint32_t kBlocks = (kSmallMaxValid + 4095) >> 12; // blocks hold 4096 or more
   __shared__ unsigned long long blk_sum[kBlocks];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, n_valid = a.n_valid, profile = a.profile;
@@ -852,7 +857,7 @@ __device__ __forceinline__ void small_draws(const SmallView &a, uint32_t *q) {
     }
   }
   lds_barrier();
-  if (tid < (uint32_t)a.n_draws) {
+  if (a.res && tid < (uint32_t)a.n_draws) {
     const uint32_t l = pick_pos[tid];
     const uint32_t raw = l != kNoIndex ? a.idx[l] : kNoIndex;
     if (a.prof_out && tid == 0) *a.prof_out = l; // kNoIndex == kNoProfile
@@ -883,7 +888,7 @@ __device__ __forceinline__ void small_draws(const SmallView &a, uint32_t *q) {
 // n_groups-th tile of 512 configurations (2,048 where groups take several),
 // and the rest of the step when it arrives last.  A single group needs no meeting.
 __device__ __forceinline__ void small_body(const SmallView &a, uint32_t group, uint32_t n_groups,
-                                           uint32_t *small_q) {
+                                           uint32_t *small_q, SmallPicks &picks) {
   __shared__ uint32_t red[3][kSmallThreads / kWave];
   __shared__ uint32_t arrived;
   const uint32_t tid = threadIdx.x, n_valid = a.n_valid, profile = a.profile;
@@ -944,7 +949,7 @@ __device__ __forceinline__ void small_body(const SmallView &a, uint32_t group, u
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (tid == 0) a.acc_next[0].pad = 0u;
   }
-  small_draws(a, small_q);
+  small_draws(a, small_q, picks);
   clear_acc(a.acc_next); // the next step's accumulators
   if (tid == 0 && profile < n_valid)
     atomicOr(&a.explored[profile >> 5], 1u << (profile & 31u));
@@ -952,12 +957,13 @@ __device__ __forceinline__ void small_body(const SmallView &a, uint32_t group, u
 
 __global__ __launch_bounds__(kSmallThreads) void small_step(SmallStep a) {
   extern __shared__ uint32_t small_q[];
+  __shared__ SmallPicks picks;
   const uint32_t profile = a.prof_dev ? *a.prof_dev : a.profile;
   const SmallView v{a.P,    a.stride, profile,      a.n_valid,  a.explored, a.s,
                     a.acc,  a.acc_next, a.gamma,    a.w_min,    a.block_log2, a.n_blocks,
                     a.bsum, a.idx,    a.res,        a.seq0,     a.prof_out, a.per,
                     a.per4, a.act.n,  a.series.n,   a.act.ctr,  a.act.delta, a.series.u64};
-  small_body(v, blockIdx.x, gridDim.x, small_q);
+  small_body(v, blockIdx.x, gridDim.x, small_q, picks);
 }
 
 // The same step in every session of a batch of small spaces, `groups`
@@ -966,6 +972,7 @@ __global__ __launch_bounds__(kSmallThreads) void batch_small(
     const BatchSess *__restrict__ sess, const SmallJob *__restrict__ jobs, uint32_t groups,
     DrawResult *__restrict__ res) {
   extern __shared__ uint32_t small_q[];
+  __shared__ SmallPicks picks;
   const uint32_t si = blockIdx.x / groups;
   const BatchSess &d = sess[si];
   const SmallJob &j = jobs[si];
@@ -975,7 +982,141 @@ __global__ __launch_bounds__(kSmallThreads) void batch_small(
                     d.gamma, d.w_min, d.block_log2, d.n_blocks, d.bsum, d.idx,
                     res + (size_t)si * kMaxDrawSeries, j.seq0, nullptr, d.per, d.per4,
                     j.n_act, j.n_draws, j.ctr, j.delta, j.u64};
-  small_body(v, blockIdx.x - si * groups, groups, small_q);
+  small_body(v, blockIdx.x - si * groups, groups, small_q, picks);
+}
+
+// Alg. 1 of one session per workgroup, iteration after iteration: the runs of
+// a batch share nothing, and a single workgroup needs no meeting, so a run
+// needs the host for nothing until it ends.  Per iteration: the current
+// configuration is tested and profiled (one thread: the expert system is 60
+// operations), the step and its draws are small_body's, the picks' runtimes
+// decide the next configuration.  The explored bits live in LDS meanwhile.
+// Every run ends: an iteration makes at least one test, of at most max_tests.
+// Bound: one CU per run; an iteration of 7,616 configurations takes 28 us, of
+// which the scores take half.  64 runs of 150 tests there: 2.92 ms with a
+// launch of batch_small, a copy and a wait per iteration (28.7 us of the 104 of
+// one are the kernel's) -> 1.04 ms, 0.72 of them this kernel's.
+__global__ __launch_bounds__(kSmallThreads) void batch_tune(const BatchSess *__restrict__ sess,
+                                                            TuneArgs t) {
+  extern __shared__ uint32_t small_q[];
+  __shared__ SmallPicks picks;
+  __shared__ uint32_t explored[kSmallMaxValid / 32];
+  __shared__ TuneRun r;
+  __shared__ double pc[24];
+  __shared__ uint64_t u64[kMaxDrawSeries];
+  __shared__ uint32_t ctr[24];
+  __shared__ float delta[24], runtime[kMaxDrawSeries];
+  __shared__ int32_t n_act, n_draws;
+  const uint32_t si = blockIdx.x, tid = threadIdx.x;
+  const BatchSess &d = sess[si];
+  const uint32_t n_words = (d.n_valid + 31) / 32;
+  const uint64_t *uni = t.uniforms + (size_t)si * t.stride_u;
+  uint32_t *tested = t.tested + (size_t)si * t.cap;
+  uint8_t *profiled = t.profiled + (size_t)si * t.cap;
+  for (uint32_t w = tid; w < n_words; w += kSmallThreads) explored[w] = d.explored[w];
+  if (tid == 0) r = t.run[si];
+  __syncthreads();
+  // thread 0: true ends the run
+  auto test = [&](uint32_t l, bool prof, float rt) {
+    tested[r.nt] = l; // below cap: a configuration is drawn once and profiled once
+    profiled[r.nt] = prof ? 1 : 0;
+    ++r.nt;
+    if (!r.found && (double)rt <= t.thresh) r.found = r.nt;
+    return (t.stop_at_well && r.found) || r.nt >= t.max_tests;
+  };
+  for (uint32_t it = 0; it < t.max_iters && r.state <= kTuneRunning; ++it) { // uniform
+    const bool start = r.state == kTuneStart;
+    if (!start && tid < 24) pc[tid] = t.counters[(size_t)r.c * 24 + tid];
+    if (!start && tid == 24) runtime[0] = t.runtime[r.c];
+    __syncthreads();
+    if (tid == 0) {
+      n_act = 0;
+      n_draws = 0; // no step
+      r.late = 0;
+      if (start) {
+        u64[0] = uni[r.u++];
+        n_draws = 1;
+      } else if (test(r.c, true, runtime[0])) {
+        r.state = kTuneEnded;
+      } else {
+        bool finite = true;
+        for (int i = 0; i < 24; ++i) finite = finite && isfinite(pc[i]);
+        if (!finite) {
+          r.state = kTuneBadCounters;
+        } else if (r.u >= t.n_uniforms) {
+          r.state = kTuneNoNumbers;
+        } else {
+          double b[18], dc[24];
+          expert::evaluate(pc, t.ep, b, dc);
+          int n = 0;
+#pragma unroll
+          for (int i = 0; i < 24; ++i) {
+            const float f = (float)dc[i];
+            if (f == 0.0f) continue;
+            ctr[n] = (uint32_t)i;
+            delta[n++] = f;
+          }
+          n_act = n;
+          int k = 0;
+          for (; k < (int)t.draws && r.u < t.n_uniforms; ++k) u64[k] = uni[r.u++];
+          n_draws = k;
+        }
+      }
+    }
+    __syncthreads();
+    if (n_draws == 0) break; // uniform
+    const uint32_t profile = start ? kNoProfile : r.c;
+    const int parity = r.parity;
+    const SmallView v{d.P, d.stride, profile, d.n_valid, explored, d.s,
+                      d.acc + parity * kAccSlots, d.acc + (parity ^ 1) * kAccSlots,
+                      d.gamma, d.w_min, d.block_log2, d.n_blocks, d.bsum, d.idx,
+                      nullptr, 0, nullptr, d.per, d.per4, n_act, n_draws, ctr, delta, u64};
+    small_body(v, 0, 1, small_q, picks);
+    if (tid < (uint32_t)n_draws)
+      runtime[tid] = picks.pos[tid] != kNoIndex ? t.runtime[picks.pos[tid]] : 0.0f;
+    __syncthreads(); // also orders this step's scores and accumulators with the next
+    if (tid == 0) {
+      r.cur_acc = parity;
+      r.parity = parity ^ 1;
+      r.profile = profile;
+      r.n_act = (uint32_t)n_act;
+      r.last_total = picks.total[n_draws - 1];
+      ++r.steps;
+      ++r.iters;
+      r.late = 1;
+      for (int k = 0; k < n_draws; ++k)
+        if (picks.total[k] != 0 && picks.pos[k] == kNoIndex) r.state = kTuneNoPick;
+      if (start && r.state == kTuneStart) {
+        r.state = picks.total[0] == 0 ? kTuneEnded : kTuneRunning;
+        r.c = picks.pos[0];
+      } else if (r.state == kTuneRunning) {
+        float best = INFINITY;
+        bool next = false, stop = false;
+        uint32_t next_c = 0;
+        for (int k = 0; k < n_draws && !stop; ++k) {
+          if (picks.total[k] == 0) break; // no configuration left
+          if (test(picks.pos[k], false, runtime[k])) {
+            stop = true;
+          } else {
+            if (runtime[k] <= best) {
+              best = runtime[k];
+              next_c = picks.pos[k];
+              next = true;
+            }
+            if (k + 1 == n_draws && n_draws < (int)t.draws) r.state = kTuneNoNumbers;
+          }
+        }
+        if (r.state == kTuneRunning) {
+          if (stop || !next) r.state = kTuneEnded;
+          else r.c = next_c;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+  for (uint32_t w = tid; w < n_words; w += kSmallThreads) d.explored[w] = explored[w];
+  if (tid == 0) t.run[si] = r;
 }
 
 // ------------------------------------------------------------ batched
@@ -1581,6 +1722,18 @@ hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, u
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_small, dim3(n * groups), dim3(kSmallThreads), lds, stream, d_sess,
                      d_jobs, groups, d_res);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_tune(const BatchSess *d_sess, const TuneArgs &a, uint32_t n,
+                             uint32_t max_per, hipStream_t stream) {
+  if (n == 0) return hipSuccess;
+  if (max_per > kSmallPer || a.draws < 1 || a.draws > kMaxDrawSeries) return hipErrorInvalidValue;
+  const size_t lds = small_ld(max_per) * kSmallThreads * sizeof(uint32_t);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(batch_tune),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  batch_tune<<<n, kSmallThreads, lds, stream>>>(d_sess, a);
   return hipGetLastError();
 }
 
