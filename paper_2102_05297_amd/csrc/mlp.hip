@@ -232,6 +232,18 @@ __device__ __forceinline__ void infer_block_out(const f32x16 (&acc)[T], int r, c
   }
 }
 
+// The two K steps of layer 3 that the activations f of layer-2 block r are.
+template <int H, int NB3>
+__device__ __forceinline__ void infer_layer3(const bf16x8 (&f)[2], int r, const bf16x8 *w3,
+                                             int lane, f32x16 (&accy)[NB3][1]) {
+  constexpr int S2 = H / 16;
+#pragma unroll
+  for (int r3 = 0; r3 < NB3; ++r3)
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+      accy[r3][0] = mfma(w3[(r3 * S2 + 2 * r + sp) * 64 + lane], f[sp], accy[r3][0]);
+}
+
 template <int H, int NB3, int S1, bool RESIDENT, bool W1LDS>
 constexpr size_t infer_lds() {
   return (size_t)((RESIDENT ? H * H : 2 * 32 * H) + NB3 * 32 * H + (W1LDS ? H * 16 * S1 : 0)) * 2 +
@@ -283,33 +295,94 @@ mlp_infer(
 #pragma unroll
       for (int t = 0; t < T; ++t) accy[r3][t] = bias_acc(bias + 2 * H + 32 * r3 + 4 * hh);
     if (!RESIDENT) __syncthreads(); // block 0 in the first buffer
-    // with two waves per SIMD the other wave's MFMAs cover this one's epilogue
+    if constexpr (NW == 4) {
+      // One wave per SIMD: block r's products with the GELU of block r - 1
+      // between them, as an MFMA waits 32 cycles for the one before it (the
+      // same accumulator) and nothing else would issue.  On 4.0M configurations
+      // 12-512-512-40 5.88 -> 5.11 ms, 12-256-256-40 2.40 -> 2.35; with two
+      // waves per SIMD, which fill each other's waits, it is slower
+      // (12-512-512-32 3.33 -> 3.50, 12-256-256-24 1.32 -> 1.40).
+      f32x16 prev = {};
 #pragma unroll 1
-    for (int r = 0; r < NB; ++r) {
-      const bf16x8 *wr = RESIDENT ? w2 + r * NBLK : w2 + (r & 1) * NBLK;
-      const bool more = !RESIDENT && r + 1 < NB;
-      bf16x8 st[RESIDENT ? 1 : PER];
-      if (more) {
+      for (int r = 0; r < NB; ++r) {
+        const bf16x8 *wr = (RESIDENT ? w2 + r * NBLK : w2 + (r & 1) * NBLK) + lane;
+        if (!RESIDENT && r + 1 < NB) {
+          // the next block straight into the other buffer, which every wave has left
 #pragma unroll
-        for (int u = 0; u < PER; ++u) st[u] = a.w2p[(size_t)(r + 1) * NBLK + u * NT + tid];
+          for (int u = 0; u < PER; ++u)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(a.w2p + (size_t)(r + 1) * NBLK +
+                                                                 u * NT + tid),
+                (__attribute__((address_space(3))) void *)(w2 + ((r + 1) & 1) * NBLK + u * NT +
+                                                           (tid & ~63)),
+                16, 0, 0);
+        }
+        f32x16 acc = bias_acc(bias + H + 32 * r + 4 * hh);
+        bf16x8 f[2];
+        float p = 0.0f; // a value's exponent between its two halves
+        bf16x8 wq[2] = {wr[0], wr[64]};
+#pragma unroll
+        for (int ks = 0; ks < S2; ++ks) {
+          const bf16x8 wf = wq[ks & 1];
+          if (ks + 2 < S2) wq[ks & 1] = wr[(ks + 2) * 64];
+          acc = mfma(wf, h1[ks][0], acc);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (S2 == 32) { // half a value per product
+            const int v = ks / 2;
+            const float z = prev[v];
+            if (ks % 2 == 0) p = gelu_tail_log2(tail_arg(fabsf(z)));
+            else f[v / 8][v % 8] = (__bf16)fmaf(-fabsf(z), __builtin_amdgcn_exp2f(p), relu(z));
+          } else {
+            constexpr int E = 16 / S2;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const int v = ks * E + e;
+              f[v / 8][v % 8] = (__bf16)gelu(prev[v]);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (r > 0) infer_layer3<H, NB3>(f, r - 1, w3, lane, accy);
+        prev = acc;
+        if (!RESIDENT) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          lds_barrier();
+        }
       }
-      f32x16 acc[T];
-#pragma unroll
-      for (int t = 0; t < T; ++t) acc[t] = bias_acc(bias + H + 32 * r + 4 * hh);
-#pragma unroll
-      for (int ks = 0; ks < S2; ++ks) {
-        const bf16x8 wf = wr[ks * 64 + lane];
-#pragma unroll
-        for (int t = 0; t < T; ++t) acc[t] = mfma(wf, h1[ks][t], acc[t]);
-        // at most four fragments in flight ahead of their MFMAs
-        if (ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      {
+        bf16x8 f[2];
+        gelu_frags<true>(prev, f[0], f[1]);
+        infer_layer3<H, NB3>(f, NB - 1, w3, lane, accy);
       }
-      infer_block_out<H, T, NB3, true>(acc, r, w3, lane, accy);
-      if (more) {
+    } else {
+      // with two waves per SIMD the other wave's MFMAs cover this one's epilogue
+#pragma unroll 1
+      for (int r = 0; r < NB; ++r) {
+        const bf16x8 *wr = RESIDENT ? w2 + r * NBLK : w2 + (r & 1) * NBLK;
+        const bool more = !RESIDENT && r + 1 < NB;
+        bf16x8 st[RESIDENT ? 1 : PER];
+        if (more) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u) w2[((r + 1) & 1) * NBLK + u * NT + tid] = st[u];
+          for (int u = 0; u < PER; ++u) st[u] = a.w2p[(size_t)(r + 1) * NBLK + u * NT + tid];
+        }
+        f32x16 acc[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = bias_acc(bias + H + 32 * r + 4 * hh);
+#pragma unroll
+        for (int ks = 0; ks < S2; ++ks) {
+          const bf16x8 wf = wr[ks * 64 + lane];
+#pragma unroll
+          for (int t = 0; t < T; ++t) acc[t] = mfma(wf, h1[ks][t], acc[t]);
+          // at most four fragments in flight ahead of their MFMAs
+          if (ks % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+        infer_block_out<H, T, NB3, true>(acc, r, w3, lane, accy);
+        if (more) {
+#pragma unroll
+          for (int u = 0; u < PER; ++u) w2[((r + 1) & 1) * NBLK + u * NT + tid] = st[u];
+        }
+        if (!RESIDENT) __syncthreads();
       }
-      if (!RESIDENT) __syncthreads();
     }
     infer_store<T, NB3>(a, accy, first, hh, col, ok);
   }
