@@ -2957,7 +2957,7 @@ struct cgs_batch_s {
   uint16_t *d_tile_sess = nullptr, *d_blk_sess = nullptr;
   uint32_t total_tiles = 0, total_blocks = 0;
   uint64_t total_valid = 0;
-  uint64_t row_bytes = 0; // predictions of every session
+  uint64_t row_bytes = 0; // predictions of the sessions' models
   int total_counters = 0;
   cgs_batch_schedule sched{};
   hipGraph_t graph = nullptr;
@@ -3055,6 +3055,7 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   *out = nullptr;
   if (n < 1 || n > 65535 || !sessions || !models) return fail(CGS_EINVAL, "need 1..65535 sessions");
   std::vector<BatchSess> desc(n);
+  std::vector<std::pair<const float *, uint64_t>> rows(n); // predictions and their bytes
   uint64_t tiles = 0, blocks = 0, valid = 0, row_bytes = 0;
   uint32_t max_tiles = 0, max_per = 0;
   bool small = true;
@@ -3090,9 +3091,13 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     tiles += (d.n_valid + kBatchTile - 1) / kBatchTile;
     blocks += d.n_blocks;
     valid += d.n_valid;
-    row_bytes += 4ull * d.n_valid * (uint64_t)m->n_counters;
+    rows[i] = {m->d_P, 4ull * d.n_valid * (uint64_t)m->n_counters};
     counters += m->n_counters;
   }
+  // sessions of one model read the same rows
+  std::sort(rows.begin(), rows.end());
+  for (int i = 0; i < n; ++i)
+    if (i == 0 || rows[i].first != rows[i - 1].first) row_bytes += rows[i].second;
   if (tiles > 0xffffffffull || blocks > 0xffffffffull)
     return fail(CGS_ERANGE, "batch too large");
   cgs_batch b = new (std::nothrow) cgs_batch_s();
