@@ -477,7 +477,6 @@ def tree_fit_path(cgs, sp, spec, repeats=5):
 
 
 POLY_ORDER, POLY_COUNTERS = 3, 24
-VALU_FP32_PEAK_T = 78.6   # fp32 FMA on the vector units, packed FP32 not used
 
 
 def poly_path(cgs, sp, spec, repeats=3, n_heldout=100000, n_steps=20):
@@ -509,8 +508,10 @@ def poly_path(cgs, sp, spec, repeats=3, n_heldout=100000, n_steps=20):
     truth = Y[len(design):]
     rel_mae = float(np.mean(np.abs(pred - truth) / (np.abs(truth).mean(axis=0) + 1e-30)))
     eval_ms = float(np.median(evals))
-    flop = len(valid) * 2.0 * T * POLY_COUNTERS
-    achieved = flop / (eval_ms / 1e3) / 1e12
+    # the predictions written and the index list read: the terms are summed
+    # once per combination of outer digits, not per configuration
+    eval_bytes = 4 * POLY_COUNTERS + 4
+    achieved = len(valid) * eval_bytes / (eval_ms / 1e3) / 1e9
     # the model drives the search like any other
     U, pcs, thr = workload_inputs(n_steps)
     t0 = time.perf_counter()
@@ -526,10 +527,9 @@ def poly_path(cgs, sp, spec, repeats=3, n_heldout=100000, n_steps=20):
         "eval_configs_per_s": len(valid) / (eval_ms / 1e3),
         "heldout_configs": int(len(held)), "heldout_rel_mae": rel_mae,
         "search_step_ms": step_ms,
-        "eval_roofline": {"kernel": "poly_eval", "bound": "valu", "achieved": achieved,
-                          "peak": VALU_FP32_PEAK_T, "unit": "TFLOP/s",
-                          "frac": achieved / VALU_FP32_PEAK_T,
-                          "flop_per_config": 2 * T * POLY_COUNTERS},
+        "eval_roofline": {"kernel": "poly_eval_nested", "bound": "hbm", "achieved": achieved,
+                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+                          "bytes_per_config": eval_bytes},
     }
 
 

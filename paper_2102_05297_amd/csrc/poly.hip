@@ -9,8 +9,10 @@
 // point's counters appended as columns T..T+C-1; per subspace the Gram matrix
 // of those columns gives F^T F and F^T Y; a ridge 1e-9 trace / T is added and
 // one workgroup per subspace factors it (Cholesky, packed lower triangle in
-// LDS) and solves for every counter.  Evaluation: one thread per valid
-// configuration, float32, coefficients of a group of subspaces in LDS.
+// LDS, panels of 16 columns) and solves for every counter.  Evaluation,
+// float32: the terms summed once per combination of all but the last
+// parameters' digits, then one thread per valid configuration (nested); or
+// every term per configuration, coefficients of a group of subspaces in LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

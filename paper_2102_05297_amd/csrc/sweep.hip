@@ -12,7 +12,9 @@
 //   acc[2][64]     per-step min / max / count accumulators, two sets used by
 //                  alternate steps (the step using one set clears the other)
 //
-// Kernels per step (three launches up to the first draw):
+// Kernels per step (three launches up to the first draw; spaces of up to
+// 32,768 configurations and restricted steps of up to 8,192 neighbours have
+// all of it in one, small_step and nb_step below):
 //   score_pass    4 configurations per thread, float4 loads of up to 8
 //                 counter rows issued before any arithmetic; float32 with
 //                 every operation rounded (this file is built without
