@@ -231,6 +231,16 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Waits until the L2 has this wave's stores of global memory.  Neither a
+// barrier nor a release of one wave does that for the others (__syncthreads
+// compiles to a wait for LDS, as the waves of a workgroup share a cache), and
+// the write-back of an agent-scope release covers what has reached the L2.  So
+// every wave waits before the barrier after which one thread releases the
+// whole workgroup's stores to other workgroups.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Exclusive scan over the whole block (NT threads, NT % 64 == 0); `total`
 // receives the block sum.  `scratch` holds NT / 64 entries.  Contains
 // barriers (kLdsOnly: of LDS only): every thread must call it.

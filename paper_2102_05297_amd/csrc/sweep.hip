@@ -654,8 +654,9 @@ __global__ __launch_bounds__(kDrawThreads) void draw_many(
 // round trips, and every draw weighs a block again; here the draws after the
 // weighing cost two LDS barriers and one LDS read each.
 // The workgroups meet on one counter: each adds 1 with release once its
-// scores and its min / max slot are written, the one that brings it to the
-// number of workgroups goes on after an acquire (no workgroup waits).
+// scores and its min / max slot are written (every wave waits for its own
+// stores first, stores_done), the one that brings it to the number of
+// workgroups goes on after an acquire (no workgroup waits).
 // 512 threads: with 256 the last workgroup's single wave per SIMD leaves its
 // weighing waiting on its own latencies (2.6 against 1.5 us on 7,616
 // configurations), with 1,024 every barrier of a draw costs more (0.62 to
@@ -928,6 +929,7 @@ __device__ __forceinline__ void small_body(const SmallView &a, uint32_t group, u
     red[1][tid >> 6] = kmax;
     red[2][tid >> 6] = cnt;
   }
+  if (n_groups > 1) stores_done(); // the scores, for the group that arrives last
   __syncthreads();
   if (tid == 0) {
     StepAcc slot{red[0][0], red[1][0], red[2][0], 0u};
@@ -1436,6 +1438,7 @@ __global__ __launch_bounds__(kNbThreads) void nb_step(NbFused a) {
     red[1][tid >> 6] = kmax;
     red[2][tid >> 6] = cnt;
   }
+  stores_done(); // the candidates, for the workgroup that arrives last
   __syncthreads();
   if (tid == 0) {
     StepAcc slot{red[0][0], red[1][0], red[2][0], 0u};
