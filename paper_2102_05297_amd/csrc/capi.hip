@@ -239,6 +239,9 @@ struct cgs_session_s {
   cgs_model pending_model = nullptr;
   uint32_t pending_profile = kNoProfile;
   ActiveCounters pending_act{};
+  // something was launched on the space's stream since a batch last waited for
+  // it (join_sessions)
+  bool own_work = false;
   int parity = 0;     // accumulator set of the next launched step
   int cur_acc = 0;    // accumulator set of the last launched step
   bool stepped = false;
@@ -1259,6 +1262,7 @@ cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq, Pick *p
 cgs_status draw_series(cgs_session s, int n, const uint64_t *u64, uint64_t *valid, int *made) {
   cgs_space sp = s->space;
   *made = 0;
+  s->own_work = true;
   const uint64_t seq_first = s->seq + 1;
   if (s->pending && small_steps(s)) {
     HIP_TRY(launch_pending(s, n, u64, s->d_ring));
@@ -2036,6 +2040,7 @@ hipError_t launch_pending_nb(cgs_session s, bool do_draw, uint64_t u64) {
   const uint32_t nv = (uint32_t)sp->n_valid;
   const bool timed = s->params.timing > 0 && s->n_launched % (uint64_t)s->params.timing == 0;
   hipError_t e = hipSuccess;
+  s->own_work = true;
   // one launch for the neighbourhoods it takes, without timing (whose markers
   // stand between the kernels)
   if (s->params.timing == 0 && st.total <= kNbFusedMax) {
@@ -2131,6 +2136,7 @@ hipError_t launch_full_step(cgs_session s, cgs_model m, const ActiveCounters &ac
   StepAcc *acc_next = s->d_acc + (s->parity ^ 1) * kAccSlots;
   const bool timed = s->params.timing > 0 && s->n_launched % (uint64_t)s->params.timing == 0;
   hipError_t e = hipSuccess;
+  s->own_work = true;
   if (small_steps(s)) {
     SmallStep a{};
     a.P = m->d_P;
@@ -2793,6 +2799,7 @@ extern "C" cgs_status cgs_sample_next(cgs_session s, uint64_t u64, uint64_t *raw
   if (s->pending) {
     HIP_TRY(launch_pending(s, 1, &u64, s->d_res));
   } else {
+    s->own_work = true;
     TimedSpan *span = nullptr;
     if (s->step_timed) {
       const int kinds[1] = {2};
@@ -3001,6 +3008,26 @@ void destroy_batch(cgs_batch b) {
   delete b;
 }
 
+// Before the batch's stream touches the sessions' arrays: launches the steps
+// recorded outside the batch and waits for what the sessions enqueued on
+// their spaces' streams.  A draw there returns once its result is published,
+// when its kernel still has block sums, accumulators and explored bits to
+// write.
+cgs_status join_sessions(cgs_batch b) {
+  for (cgs_session s : b->sess) {
+    const cgs_status st = flush_pending(s);
+    if (st != CGS_OK) return st;
+  }
+  hipStream_t waited = nullptr;
+  for (cgs_session s : b->sess) {
+    if (!s->own_work) continue;
+    if (s->space->stream != waited) HIP_TRY(hipStreamSynchronize(s->space->stream));
+    waited = s->space->stream;
+    s->own_work = false;
+  }
+  return CGS_OK;
+}
+
 // Enqueues one batched step (copy of the step records, score, weight, draw).
 hipError_t enqueue_batch(cgs_batch b, bool draw) {
   hipError_t e = hipMemcpyAsync(b->d_step, b->h_step, (size_t)b->n * sizeof(BatchStep),
@@ -3068,6 +3095,7 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     const cgs_status st = flush_pending(s);
     if (st != CGS_OK) return st;
     HIP_TRY(hipStreamSynchronize(s->space->stream));
+    s->own_work = false;
     BatchSess &d = desc[i];
     d.P = m->d_P;
     d.stride = m->stride;
@@ -3174,15 +3202,12 @@ extern "C" cgs_status cgs_batch_step(cgs_batch b, const uint64_t *profile_raw, c
                                      const uint64_t *u64, uint64_t *raw_out, uint64_t *valid_out,
                                      int32_t *status_out) {
   if (!b || !profile_raw || !u64) return fail(CGS_EINVAL, "NULL argument");
+  const cgs_status joined = join_sessions(b);
+  if (joined != CGS_OK) return joined;
   size_t doff = 0;
   for (int i = 0; i < b->n; ++i) {
     cgs_session s = b->sess[i];
     cgs_model m = b->models[i];
-    if (s->pending) {
-      const cgs_status st = flush_pending(s);
-      if (st != CGS_OK) return st;
-      HIP_TRY(hipStreamSynchronize(s->space->stream));
-    }
     BatchStep &st = b->h_step[i];
     const int C = m->n_counters;
     st.n_act = 0;
@@ -3275,6 +3300,8 @@ extern "C" cgs_status cgs_batch_autotune(cgs_batch b, const char *cache_path,
       fclose(f);
     }
   }
+  const cgs_status joined = join_sessions(b);
+  if (joined != CGS_OK) return joined;
   // timing records: profile 0, every counter active, no draw; accumulator
   // set = the one the sessions' next step will not use
   for (int i = 0; i < b->n; ++i) {
@@ -3410,6 +3437,8 @@ extern "C" cgs_status cgs_batch_draw(cgs_batch b, const uint64_t *u64, uint64_t 
     st.u64 = u64[i];
     st.seq = b->seq + 1;
   }
+  const cgs_status joined = join_sessions(b);
+  if (joined != CGS_OK) return joined;
   HIP_TRY(hipMemcpyAsync(b->d_step, b->h_step, (size_t)b->n * sizeof(BatchStep),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(launch_batch_draw(b->d_sess, b->d_step, (uint32_t)b->n, b->stream));
@@ -3453,12 +3482,9 @@ cgs_status ensure_small_jobs(cgs_batch b) {
 // picks[i * kMaxDrawSeries + k]; the sessions then look as after a step and
 // draws of their own in the batch.
 cgs_status small_batch_step(cgs_batch b, Pick *picks) {
+  const cgs_status joined = join_sessions(b);
+  if (joined != CGS_OK) return joined;
   for (int i = 0; i < b->n; ++i) {
-    if (b->sess[i]->pending) { // recorded outside the batch
-      const cgs_status st = flush_pending(b->sess[i]);
-      if (st != CGS_OK) return st;
-      HIP_TRY(hipStreamSynchronize(b->sess[i]->space->stream));
-    }
     b->h_jobs[i].parity = b->sess[i]->parity;
     b->h_jobs[i].seq0 = b->seq + 1;
   }
@@ -3529,12 +3555,8 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
   const int n = b->n;
   const uint64_t nv = b->sess[0]->space->n_valid;
   hipStream_t st = b->stream;
-  for (int i = 0; i < n; ++i) {
-    if (!b->sess[i]->pending) continue; // recorded outside the batch
-    const cgs_status fs = flush_pending(b->sess[i]);
-    if (fs != CGS_OK) return fs;
-    HIP_TRY(hipStreamSynchronize(b->sess[i]->space->stream));
-  }
+  const cgs_status joined = join_sessions(b);
+  if (joined != CGS_OK) return joined;
   TuneArgs a{};
   a.n_uniforms = n_uniforms;
   // an iteration tests its configuration, of at most nv, and uses draws numbers
