@@ -3028,6 +3028,20 @@ cgs_status join_sessions(cgs_batch b) {
   return CGS_OK;
 }
 
+// A session after a step in its batch, which used accumulator set `acc`: as
+// after a full step of its own (in whatever way its last one was restricted).
+void stepped_in_batch(cgs_session s, int acc, float ms, int n_active) {
+  s->cur_acc = acc;
+  s->parity = acc ^ 1;
+  s->stepped = true;
+  s->pending = false;
+  s->pending_nb = false;
+  s->last_nb = false;
+  s->ran_in_batch = true;
+  s->batch_ms = ms;
+  s->n_active = n_active;
+}
+
 // Enqueues one batched step (copy of the step records, score, weight, draw).
 hipError_t enqueue_batch(cgs_batch b, bool draw) {
   hipError_t e = hipMemcpyAsync(b->d_step, b->h_step, (size_t)b->n * sizeof(BatchStep),
@@ -3248,14 +3262,7 @@ extern "C" cgs_status cgs_batch_step(cgs_batch b, const uint64_t *profile_raw, c
   HIP_TRY(hipEventElapsedTime(&b->last_ms, b->e0, b->e1));
   for (int i = 0; i < b->n; ++i) {
     cgs_session s = b->sess[i];
-    // the session now looks as if it had run this step itself
-    s->cur_acc = s->parity;
-    s->parity ^= 1;
-    s->stepped = true;
-    s->pending = false;
-    s->ran_in_batch = true;
-    s->batch_ms = b->last_ms;
-    s->n_active = b->h_step[i].n_act;
+    stepped_in_batch(s, s->parity, b->last_ms, b->h_step[i].n_act);
     Pick r;
     if (!read_pick(b->h_res + i, b->seq, &r))
       return fail(CGS_EDEVICE, "session %d: draw %llu did not publish its result", i,
@@ -3502,14 +3509,7 @@ cgs_status small_batch_step(cgs_batch b, Pick *picks) {
     const SmallJob &j = b->h_jobs[i];
     if (j.n_draws == 0) continue;
     cgs_session s = b->sess[i];
-    s->cur_acc = s->parity;
-    s->parity ^= 1;
-    s->stepped = true;
-    s->pending = false;
-    s->last_nb = false;
-    s->ran_in_batch = true;
-    s->batch_ms = b->last_ms;
-    s->n_active = j.n_act;
+    stepped_in_batch(s, s->parity, b->last_ms, j.n_act);
     b->h_step[i].parity = s->cur_acc; // cgs_batch_draw may go on from this step
     b->h_step[i].profile = j.profile;
     for (int k = 0; k < j.n_draws; ++k) {
@@ -3661,14 +3661,7 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
     const TuneRun &r = run[i];
     cgs_session s = b->sess[i];
     if (r.steps > 0) {
-      s->cur_acc = r.cur_acc;
-      s->parity = r.parity;
-      s->stepped = true;
-      s->pending = false;
-      s->last_nb = false;
-      s->ran_in_batch = true;
-      s->batch_ms = b->last_ms;
-      s->n_active = (int)r.n_act;
+      stepped_in_batch(s, r.cur_acc, b->last_ms, (int)r.n_act);
       s->last_total = r.last_total;
       b->h_step[i].parity = r.cur_acc;
       b->h_step[i].profile = r.profile;

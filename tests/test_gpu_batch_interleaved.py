@@ -52,3 +52,27 @@ def test_draws_between_batch_steps(radix, n, graph):
     for a, b in zip(sessions, alone):
         assert (a.copy_explored() == b.copy_explored()).all()
         assert (a.copy_scores() == b.copy_scores()).all() and (a.copy_weights() == b.copy_weights()).all()
+
+
+@pytest.mark.parametrize("radix", [(15, 13, 7, 3), (16, 16, 16, 16)])
+def test_a_batch_step_after_a_restricted_step(radix):
+    m = cgs()
+    sp, model, sessions, alone = _spaces(m, radix, 2)
+    batch = m.Batch(sessions, [model] * 2)
+    g = synth.rng(122, *radix)
+    U, D = synth.uniforms_u64(g, 12), synth.deltas(g, 4, C)
+    raw, _, _ = batch.step([m.NO_PROFILE] * 2, None, U[:2])
+    for i in range(2):
+        alone[i].search_step(model, m.NO_PROFILE)
+        assert alone[i].sample_next(int(U[i]))[0] == raw[i]
+        for s in (sessions[i], alone[i]):
+            s.search_step_neighbourhood(model, int(raw[i]), 1, delta=D[i])
+        assert sessions[i].sample_next(int(U[2 + i])) == alone[i].sample_next(int(U[2 + i]))
+    nxt, _, _ = batch.step([int(r) for r in raw], D[2:], U[4:6])
+    for i in range(2):
+        alone[i].search_step(model, int(raw[i]), delta=D[2 + i])
+        assert alone[i].sample_next(int(U[4 + i]))[0] == nxt[i]
+        assert (sessions[i].copy_scores() == alone[i].copy_scores()).all()
+        assert (sessions[i].copy_weights() == alone[i].copy_weights()).all()
+        assert sessions[i].sample_next(int(U[6 + i])) == alone[i].sample_next(int(U[6 + i]))
+        assert (sessions[i].copy_explored() == alone[i].copy_explored()).all()
