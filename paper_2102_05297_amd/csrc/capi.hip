@@ -147,9 +147,10 @@ struct cgs_space_s {
     for (; left > 0; --left) bits &= bits - 1u;
     return 32 * w + (uint64_t)__builtin_ctz(bits);
   }
-  // scratch for the standalone sampler
+  // the standalone sampler's result and the number of its last draw
   DrawResult *d_res = nullptr;
   DrawResult *h_res = nullptr;
+  uint64_t seq = 0;
 };
 
 struct cgs_model_s {
@@ -406,6 +407,7 @@ extern "C" cgs_status cgs_space_create(int n_params, const int32_t *radix, const
   SP_TRY(dalloc(&sp->d_mask, desc.n_words));
   SP_TRY(dalloc(&sp->d_rank, desc.n_words));
   SP_TRY(palloc(&sp->h_res, &sp->d_res, 1));
+  std::memset(sp->h_res, 0, sizeof(DrawResult)); // a pooled block's words carry numbers
   const uint32_t n_tiles = enumeration_tiles((uint32_t)n_raw);
   uint32_t *d_tile_count = nullptr, *d_tile_off = nullptr;
   uint64_t *d_total = nullptr;
@@ -3168,6 +3170,7 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   if (e == hipSuccess) e = dalloc(&b->d_blk_sess, blk_sess.size());
   if (e == hipSuccess) e = palloc<BatchStep>(&b->h_step, nullptr, (size_t)n);
   if (e == hipSuccess) e = palloc(&b->h_res, &b->d_res, (size_t)n);
+  if (e == hipSuccess) std::memset(b->h_res, 0, (size_t)n * sizeof(DrawResult));
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->e0, hipEventDisableSystemFence);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&b->e1, hipEventDisableSystemFence);
   if (e == hipSuccess) {
@@ -3981,11 +3984,12 @@ cgs_status sample_resident(cgs_space sp, uint32_t *d_q, uint64_t n, int lg, uint
                            uint32_t n_blocks, const uint64_t *u64, int n_draws, int64_t *picks) {
   hipError_t e = launch_array_block_sums(d_q, (uint32_t)n, lg, d_bsum, sp->stream);
   for (int i = 0; i < n_draws && e == hipSuccess; ++i) {
-    e = launch_array_draw(d_q, (uint32_t)n, lg, d_bsum, n_blocks, u64[i], sp->d_res, sp->stream);
+    e = launch_array_draw(d_q, (uint32_t)n, lg, d_bsum, n_blocks, u64[i], sp->d_res, ++sp->seq,
+                          sp->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
     if (e == hipSuccess) {
       Pick p;
-      if (!read_pick(sp->h_res, 1, &p)) return fail(CGS_EDEVICE, "draw did not publish its result");
+      if (!read_pick(sp->h_res, sp->seq, &p)) return fail(CGS_EDEVICE, "draw did not publish its result");
       if (p.total == 0) break;
       if (p.valid == kNoPick) return fail(CGS_EDEVICE, "draw found no index although Q > 0");
       picks[i] = (int64_t)p.valid;

@@ -373,7 +373,7 @@ hipError_t launch_copy_weights(const float *d_s, uint32_t *d_explored, uint32_t 
 hipError_t launch_array_block_sums(const uint32_t *d_q, uint32_t n, int block_log2,
                                    uint64_t *d_bsum, hipStream_t stream);
 hipError_t launch_array_draw(uint32_t *d_q, uint32_t n, int block_log2, uint64_t *d_bsum,
-                             uint32_t n_blocks, uint64_t u64, DrawResult *d_res,
+                             uint32_t n_blocks, uint64_t u64, DrawResult *d_res, uint64_t seq,
                              hipStream_t stream);
 
 } // namespace cgs

@@ -1566,9 +1566,10 @@ __global__ __launch_bounds__(kDrawThreads) void draw_array(uint32_t *__restrict_
                                                            int block_log2,
                                                            uint64_t *__restrict__ bsum,
                                                            uint32_t n_blocks, uint64_t u64,
-                                                           DrawResult *__restrict__ res) {
+                                                           DrawResult *__restrict__ res,
+                                                           uint64_t seq) {
   ArrayWeights w{q, n};
-  draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, 1, &u64, nullptr, res, 1);
+  draw_series<kDrawThreads>(w, block_log2, bsum, n_blocks, 1, &u64, nullptr, res, seq);
 }
 
 __global__ __launch_bounds__(kWeightThreads) void array_block_sums(const uint32_t *__restrict__ q,
@@ -1863,10 +1864,10 @@ hipError_t launch_array_block_sums(const uint32_t *d_q, uint32_t n, int block_lo
 }
 
 hipError_t launch_array_draw(uint32_t *d_q, uint32_t n, int block_log2, uint64_t *d_bsum,
-                             uint32_t n_blocks, uint64_t u64, DrawResult *d_res,
+                             uint32_t n_blocks, uint64_t u64, DrawResult *d_res, uint64_t seq,
                              hipStream_t stream) {
   hipLaunchKernelGGL(draw_array, dim3(1), dim3(kDrawThreads), 0, stream, d_q, n, block_log2,
-                     d_bsum, n_blocks, u64, d_res);
+                     d_bsum, n_blocks, u64, d_res, seq);
   return hipGetLastError();
 }
 

@@ -93,7 +93,7 @@ void run(const std::string &k, void **args) {
   } else if (is("11draw_scores")) {
     publish(arg<cgs::DrawResult *>(args, 14), arg<uint64_t>(args, 15));
   } else if (is("10draw_array")) {
-    publish(arg<cgs::DrawResult *>(args, 6), args[7] ? arg<uint64_t>(args, 7) : 1);
+    publish(arg<cgs::DrawResult *>(args, 6), arg<uint64_t>(args, 7));
   } else if (is("10small_step")) {
     const auto &a = *static_cast<const cgs::SmallStep *>(args[0]);
     for (int i = 0; i < a.series.n; ++i) publish(a.res + i, a.seq0 + i);
