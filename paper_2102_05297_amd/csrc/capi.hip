@@ -260,6 +260,7 @@ struct cgs_session_s {
   StepAcc *d_nb_acc = nullptr;
   bool ran_in_batch = false; // the last step ran inside a batch step
   float batch_ms = 0.0f;     // device time of that batch step
+  uint64_t batch_steps = 0;  // steps made in batches so far
   uint64_t seq = 0;          // sequence number of the last launched draw
   int n_active = 0;
   uint64_t last_total = 0;
@@ -2974,6 +2975,7 @@ struct cgs_batch_s {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   float last_ms = 0.0f;
   uint64_t seq = 0; // sequence number of the last batch step's draws
+  std::vector<uint64_t> step_no; // each session's batch_steps after this batch's last step (0: none)
   // whole steps of small spaces in one launch (cgs_tuning_run_batch), where
   // every session's space is small
   bool small = false;
@@ -3042,6 +3044,7 @@ void stepped_in_batch(cgs_session s, int acc, float ms, int n_active) {
   s->ran_in_batch = true;
   s->batch_ms = ms;
   s->n_active = n_active;
+  ++s->batch_steps;
 }
 
 // Enqueues one batched step (copy of the step records, score, weight, draw).
@@ -3149,6 +3152,7 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   b->n = n;
   b->sess.assign(sessions, sessions + n);
   b->models.assign(models, models + n);
+  b->step_no.assign(n, 0);
   b->total_tiles = (uint32_t)tiles;
   b->total_blocks = (uint32_t)blocks;
   b->total_valid = valid;
@@ -3266,6 +3270,7 @@ extern "C" cgs_status cgs_batch_step(cgs_batch b, const uint64_t *profile_raw, c
   for (int i = 0; i < b->n; ++i) {
     cgs_session s = b->sess[i];
     stepped_in_batch(s, s->parity, b->last_ms, b->h_step[i].n_act);
+    b->step_no[i] = s->batch_steps;
     Pick r;
     if (!read_pick(b->h_res + i, b->seq, &r))
       return fail(CGS_EDEVICE, "session %d: draw %llu did not publish its result", i,
@@ -3439,8 +3444,9 @@ extern "C" cgs_status cgs_batch_draw(cgs_batch b, const uint64_t *u64, uint64_t 
   if (!b || !u64) return fail(CGS_EINVAL, "NULL argument");
   for (int i = 0; i < b->n; ++i) {
     cgs_session s = b->sess[i];
-    // the session must still hold the weights of the batch's last step
-    if (!s->stepped || !s->ran_in_batch || s->pending || s->cur_acc != b->h_step[i].parity)
+    // the session must still hold the weights of this batch's last step
+    if (!s->stepped || !s->ran_in_batch || s->pending || s->batch_steps != b->step_no[i] ||
+        s->cur_acc != b->h_step[i].parity)
       return fail(CGS_ESTATE, "session %d: no batch step to draw from", i);
     BatchStep &st = b->h_step[i];
     st.draw = 1;
@@ -3513,6 +3519,7 @@ cgs_status small_batch_step(cgs_batch b, Pick *picks) {
     if (j.n_draws == 0) continue;
     cgs_session s = b->sess[i];
     stepped_in_batch(s, s->parity, b->last_ms, j.n_act);
+    b->step_no[i] = s->batch_steps;
     b->h_step[i].parity = s->cur_acc; // cgs_batch_draw may go on from this step
     b->h_step[i].profile = j.profile;
     for (int k = 0; k < j.n_draws; ++k) {
@@ -3665,6 +3672,7 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
     cgs_session s = b->sess[i];
     if (r.steps > 0) {
       stepped_in_batch(s, r.cur_acc, b->last_ms, (int)r.n_act);
+      b->step_no[i] = s->batch_steps;
       s->last_total = r.last_total;
       b->h_step[i].parity = r.cur_acc;
       b->h_step[i].profile = r.profile;

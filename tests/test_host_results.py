@@ -37,3 +37,21 @@ b = one()                                      # the same pinned block
 fake.fake_publish(0)
 assert status(lambda: b.step([m.NO_PROFILE], None, U[:1])) == m.EDEVICE
 """)
+
+
+def test_a_batch_draws_only_from_a_step_of_its_own():
+    fake.run("""
+sp = space(16, 16, 3)
+f = forest(sp, 24)
+s = m.Session(sp)
+one = lambda: m.Batch([s], [f], m.cgs_batch_schedule(4, 4, 0, 0))
+b = one()
+assert status(lambda: b.draw(U[:1])) == m.ESTATE
+for steps in (1, 2):                           # either accumulator set
+    for _ in range(steps):
+        b.step([m.NO_PROFILE], None, U[:1])
+    b.draw(U[:1])
+    b.close()
+    b = one()                                  # the step was another batch's
+    assert status(lambda: b.draw(U[:1])) == m.ESTATE
+""")
