@@ -3086,10 +3086,12 @@ cgs_batch_schedule default_schedule(cgs_batch b) {
   return s;
 }
 
+// What the autotuner's choice depends on: the work, and which score kernels it
+// timed.
 std::string batch_key(cgs_batch b) {
   char buf[160];
-  snprintf(buf, sizeof buf, "gfx950 n=%d tiles=%u blocks=%u counters=%d", b->n, b->total_tiles,
-           b->total_blocks, b->total_counters);
+  snprintf(buf, sizeof buf, "gfx950 n=%d tiles=%u blocks=%u counters=%d%s", b->n, b->total_tiles,
+           b->total_blocks, b->total_counters, batch_streams(b->row_bytes) ? " streamed" : "");
   return buf;
 }
 
