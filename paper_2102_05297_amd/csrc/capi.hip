@@ -594,23 +594,31 @@ MlpFwdArgs mlp_args(cgs_model m) {
   return a;
 }
 
-// Where launch_check_floats leaves the first bad value of a model's inputs,
-// and its copy for the host.
-struct FloatCheck {
-  uint64_t *d_first = nullptr;
-  uint64_t first = kNoPick;
-  ~FloatCheck() { dfree(d_first); }
-};
-
-// Enqueues the check of x[0..n) on the stream; `c.first` is the first bad
-// position (kNoPick: none) once the stream has been synchronised.
-hipError_t check_floats(FloatCheck &c, const float *d_x, uint64_t n, bool nonneg,
-                        hipStream_t stream) {
-  hipError_t e = dalloc(&c.d_first, 1);
-  if (e == hipSuccess) e = launch_check_floats(d_x, n, nonneg, c.d_first, stream);
+// Uploads a model's values x[0..n) to a new block *d and checks them there
+// (finite; with nonneg, not negative).  It comes first of what a model needs
+// and is waited for, so that a bad value, `what` with its position, is
+// refused before the predictions are allocated or anything is evaluated; where
+// even the values do not fit on the device, the host looks through them.
+cgs_status upload_checked(float **d, const float *x, uint64_t n, bool nonneg, const char *what,
+                          hipStream_t stream) {
+  uint64_t *d_first = nullptr, first = kNoPick;
+  hipError_t e = dalloc(d, n);
+  if (e == hipSuccess) e = dalloc(&d_first, 1);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(&c.first, c.d_first, sizeof(uint64_t), hipMemcpyDeviceToHost, stream);
-  return e;
+    e = hipMemcpyAsync(*d, x, n * sizeof(float), hipMemcpyHostToDevice, stream);
+  if (e == hipSuccess) e = launch_check_floats(*d, n, nonneg, d_first, stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(&first, d_first, sizeof(uint64_t), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  settle(e, stream);
+  dfree(d_first);
+  for (uint64_t i = 0; e == hipErrorOutOfMemory && first == kNoPick && i < n; ++i)
+    if (!std::isfinite(x[i]) || (nonneg && x[i] < 0.0f)) first = i;
+  if (first != kNoPick) return fail(CGS_EINVAL, what, (unsigned long long)first);
+  if (e != hipSuccess)
+    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
+                hipGetErrorString(e));
+  return CGS_OK;
 }
 
 cgs_status evaluate_model(cgs_model m) {
@@ -678,27 +686,24 @@ extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth
   m->n_trees = n_trees;
   m->depth = depth;
   m->stride = (sp->n_valid + 63) & ~(uint64_t)63;
+  cgs_status st = upload_checked(&m->d_leaves, leaves, n_leaf_vals, true,
+                                 "leaf value %llu is negative or not finite", sp->stream);
+  if (st != CGS_OK) {
+    destroy_model(m);
+    return st;
+  }
   hipError_t e = dalloc(&m->d_nodes, nodes.size());
-  if (e == hipSuccess) e = dalloc(&m->d_leaves, n_leaf_vals);
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
   if (e == hipSuccess && !nodes.empty())
     e = hipMemcpyAsync(m->d_nodes, nodes.data(), nodes.size() * sizeof(uint16_t),
                        hipMemcpyHostToDevice, sp->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(m->d_leaves, leaves, n_leaf_vals * sizeof(float), hipMemcpyHostToDevice,
-                       sp->stream);
-  FloatCheck bad;
-  if (e == hipSuccess) e = check_floats(bad, m->d_leaves, n_leaf_vals, true, sp->stream);
   if (e == hipSuccess) e = clear_padding(m);
   if (e != hipSuccess) {
     destroy_model(m);
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
                 hipGetErrorString(e));
   }
-  cgs_status st = evaluate_model(m); // synchronises
-  if (bad.first != kNoPick)
-    st = fail(CGS_EINVAL, "leaf value %llu is negative or not finite",
-              (unsigned long long)bad.first);
+  st = evaluate_model(m);
   if (st != CGS_OK) {
     destroy_model(m);
     return st;
@@ -1212,15 +1217,15 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
   m->n_counters = n_counters;
   m->stride = (nv + 63) & ~(uint64_t)63;
   float *d_src = nullptr;
+  const cgs_status st = upload_checked(&d_src, pred_host, nv * (uint64_t)n_counters, true,
+                                       "prediction %llu is negative or not finite", sp->stream);
+  if (st != CGS_OK) {
+    dfree(d_src);
+    destroy_model(m);
+    return st;
+  }
   hipError_t e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
-  if (e == hipSuccess) e = dalloc(&d_src, nv * (size_t)n_counters);
   if (e == hipSuccess) e = clear_padding(m);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_src, pred_host, nv * (size_t)n_counters * sizeof(float),
-                       hipMemcpyHostToDevice, sp->stream);
-  FloatCheck bad;
-  if (e == hipSuccess)
-    e = check_floats(bad, d_src, nv * (uint64_t)n_counters, true, sp->stream);
   if (e == hipSuccess)
     e = launch_rows_to_columns(d_src, (uint32_t)nv, n_counters, m->d_P, m->stride, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
@@ -1230,11 +1235,6 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
     destroy_model(m);
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "prediction table: %s",
                 hipGetErrorString(e));
-  }
-  if (bad.first != kNoPick) {
-    destroy_model(m);
-    return fail(CGS_EINVAL, "prediction %llu is negative or not finite",
-                (unsigned long long)bad.first);
   }
   *out = m;
   return CGS_OK;
@@ -1751,8 +1751,12 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
     m->n_cu = prop.multiProcessorCount;
   hipStream_t st = sp->stream;
-  hipError_t e = dalloc(&m->d_theta, n);
-  if (e == hipSuccess) e = dalloc(&m->d_m, n);
+  cgs_status stt = upload_checked(&m->d_theta, params, n, false, "parameter %llu not finite", st);
+  if (stt != CGS_OK) {
+    destroy_model(m);
+    return stt;
+  }
+  hipError_t e = dalloc(&m->d_m, n);
   if (e == hipSuccess) e = dalloc(&m->d_v, n);
   if (e == hipSuccess) e = dalloc(&m->d_grad, n);
   if (e == hipSuccess) e = dalloc(&m->d_w1p, m->n_w1p);
@@ -1764,8 +1768,6 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (e == hipSuccess) e = dalloc(&m->d_w2n, m->n_w2p);
   if (e == hipSuccess) e = dalloc(&m->d_w3n, m->n_w3p);
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)C * m->stride);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(m->d_theta, params, n * sizeof(float), hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_m, 0, n * sizeof(float), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_v, 0, n * sizeof(float), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w1p, 0, m->n_w1p * sizeof(__bf16), st);
@@ -1775,8 +1777,6 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3t, 0, m->n_w3p * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w1n, 0, H * 32 * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3n, 0, m->n_w3p * sizeof(__bf16), st);
-  FloatCheck bad;
-  if (e == hipSuccess) e = check_floats(bad, m->d_theta, n, false, st);
   if (e == hipSuccess) e = clear_padding(m);
   if (e == hipSuccess)
     e = launch_pack_weights(m->sh, m->d_theta, n, mlp_copies(m), st);
@@ -1785,9 +1785,7 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "perceptron buffers: %s",
                 hipGetErrorString(e));
   }
-  cgs_status stt = evaluate_model(m); // synchronises
-  if (bad.first != kNoPick)
-    stt = fail(CGS_EINVAL, "parameter %llu not finite", (unsigned long long)bad.first);
+  stt = evaluate_model(m);
   if (stt != CGS_OK) {
     destroy_model(m);
     return stt;
