@@ -133,6 +133,13 @@ void cgs_default_params(cgs_params *out);
 void cgs_default_expert_params(cgs_expert_params *out);
 /* Wait for all work enqueued on the space's stream. */
 cgs_status cgs_synchronize(cgs_space space);
+/* Memory that destroyed handles leave is kept for the next ones while some
+ * space exists: up to 1 GiB of device memory per GPU, 16 MiB of pinned host
+ * memory and 8 streams.  It goes back to the driver with the last space, when
+ * an allocation of this library would fail otherwise, and on this call, which
+ * a program makes before another allocator in the process needs the memory.
+ * Handles that exist keep theirs.  Any thread may call it at any time. */
+void cgs_release_memory(void);
 
 /* ------------------------------------------------------------- space */
 /* Enumerate the tuning space (Sect. 1; TS of Alg. 1): decode every raw index

@@ -45,6 +45,7 @@ EXPORTS = (
     "cgs_poly_copy_coefficients", "cgs_model_load_predictions", "cgs_default_tuning_opts",
     "cgs_tuning_run", "cgs_batch_draw", "cgs_tuning_run_batch", "cgs_search_run",
     "cgs_default_online_opts", "cgs_online_run", "cgs_sample_weights_noalloc",
+    "cgs_release_memory",
 )
 
 
@@ -135,6 +136,7 @@ _sig("cgs_version", [])
 _sig("cgs_default_params", [_ptr(cgs_params)], None)
 _sig("cgs_default_expert_params", [_ptr(cgs_expert_params)], None)
 _sig("cgs_synchronize", [_p])
+_sig("cgs_release_memory", [], None)
 _sig("cgs_space_create", [C.c_int, _p, _p, C.c_int, _p, _p, _ptr(_p)])
 _sig("cgs_space_info", [_p, _ptr(_u64), _ptr(_u64)])
 _sig("cgs_space_decode", [_p, _u64, _p])
@@ -218,6 +220,11 @@ def library_path() -> str:
 
 def cgs_version() -> int:
     return int(_lib.cgs_version())
+
+
+def cgs_release_memory() -> None:
+    """Returns the memory kept for the next handles to the driver."""
+    _lib.cgs_release_memory()
 
 
 def cgs_default_params() -> cgs_params:

@@ -276,6 +276,8 @@ struct cgs_session_s {
 extern "C" const char *cgs_last_error(void) { return g_error.c_str(); }
 extern "C" int cgs_version(void) { return kVersion; }
 
+extern "C" void cgs_release_memory(void) { pool::release(); }
+
 extern "C" void cgs_default_params(cgs_params *out) {
   if (!out) return;
   out->gamma = -0.25f;

@@ -83,6 +83,12 @@ void detach() {
   if (--s.spaces == 0) trim(s);
 }
 
+void release() {
+  State &s = state();
+  std::lock_guard<std::mutex> lock(s.mu);
+  trim(s);
+}
+
 hipError_t device_get(void **p, size_t bytes) {
   *p = nullptr;
   int dev = 0;

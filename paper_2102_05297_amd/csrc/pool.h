@@ -11,7 +11,8 @@
 //     exceeds that goes back to the driver at once, and so does everything
 //     kept when an allocation fails (which is then tried again).
 //   - Given back: the pool lives as long as some space does.  When the last
-//     space is destroyed, everything kept is returned to the driver.
+//     space is destroyed, everything kept is returned to the driver, and on
+//     request (cgs_release_memory) at any time.
 //   - Threads: every call locks the pool.
 //   - Streams: a block or stream is put back only once the work that used it
 //     has finished (the caller has synchronised its stream), so the next
@@ -37,6 +38,9 @@ constexpr size_t kStreamCap = 8;
 // One more / one less live space; the last one empties the pool.
 void attach();
 void detach();
+
+// Returns everything kept to the driver.
+void release();
 
 // A block of at least `bytes` on the current device.
 hipError_t device_get(void **p, size_t bytes);
