@@ -7,6 +7,7 @@ def test_what_is_kept_is_given_back():
     fake.run("""
 sp = space(16, 16, 16, 16, 16)
 f = forest(sp, 8)
+m.cgs_release_memory()
 live = fake.fake_used()
 forest(sp, 64).close()
 m.Session(sp).close()
