@@ -23,15 +23,22 @@ size_t size_class(size_t bytes) {
   return (bytes + step - 1) / step * step;
 }
 
-using Key = std::pair<int, size_t>; // device (-1: host), class
+using Key = std::pair<int, size_t>; // device, class
+// A kept block, and when it was put back (the pool's count of put-backs).
+struct Block {
+  void *p;
+  uint64_t since;
+};
 struct Pinned {
   void *host, *dev;
+  uint64_t since;
 };
 
 struct State {
   std::mutex mu;
   long spaces = 0;
-  std::map<Key, std::vector<void *>> free_dev;
+  uint64_t count = 0; // blocks put back so far
+  std::map<Key, std::vector<Block>> free_dev; // of a class, the longest kept first
   std::map<int, size_t> kept_dev; // bytes in free_dev by device
   std::unordered_map<void *, Key> live_dev;
   std::map<size_t, std::vector<Pinned>> free_pin;
@@ -49,7 +56,7 @@ State &state() {
 // Returns everything kept to the driver (the lock is held).
 void trim(State &s) {
   for (auto &b : s.free_dev)
-    for (void *p : b.second) (void)hipFree(p);
+    for (Block &k : b.second) (void)hipFree(k.p);
   s.free_dev.clear();
   s.kept_dev.clear();
   for (auto &b : s.free_pin)
@@ -58,6 +65,40 @@ void trim(State &s) {
   s.kept_pin = 0;
   for (auto &b : s.free_str) (void)hipStreamDestroy(b.second);
   s.free_str.clear();
+}
+
+// Gives kept device blocks of one GPU back, those kept longest first, until
+// `size` more bytes stay within the cap: sizes that no handle asks for any
+// more make room for those in use (the lock is held; size <= kDeviceCap).
+void make_room(State &s, int dev, size_t size) {
+  size_t &kept = s.kept_dev[dev];
+  while (kept + size > kDeviceCap) {
+    auto oldest = s.free_dev.end();
+    for (auto it = s.free_dev.begin(); it != s.free_dev.end(); ++it)
+      if (it->first.first == dev && !it->second.empty() &&
+          (oldest == s.free_dev.end() || it->second.front().since < oldest->second.front().since))
+        oldest = it;
+    if (oldest == s.free_dev.end()) return;
+    (void)hipFree(oldest->second.front().p);
+    oldest->second.erase(oldest->second.begin());
+    kept -= oldest->first.second;
+    if (oldest->second.empty()) s.free_dev.erase(oldest);
+  }
+}
+// The same for pinned blocks.
+void make_room_pinned(State &s, size_t size) {
+  while (s.kept_pin + size > kPinnedCap) {
+    auto oldest = s.free_pin.end();
+    for (auto it = s.free_pin.begin(); it != s.free_pin.end(); ++it)
+      if (!it->second.empty() &&
+          (oldest == s.free_pin.end() || it->second.front().since < oldest->second.front().since))
+        oldest = it;
+    if (oldest == s.free_pin.end()) return;
+    (void)hipHostFree(oldest->second.front().host);
+    oldest->second.erase(oldest->second.begin());
+    s.kept_pin -= oldest->first;
+    if (oldest->second.empty()) s.free_pin.erase(oldest);
+  }
 }
 
 // Runs `body`, reporting a failed host allocation as hipErrorOutOfMemory.
@@ -101,7 +142,7 @@ hipError_t device_get(void **p, size_t bytes) {
     auto it = s.free_dev.find(key);
     void *q = nullptr;
     if (it != s.free_dev.end() && !it->second.empty()) {
-      q = it->second.back();
+      q = it->second.back().p;
       s.live_dev.emplace(q, key);
       it->second.pop_back();
       s.kept_dev[dev] -= key.second;
@@ -134,10 +175,10 @@ void device_put(void *p) {
   const Key key = it->second;
   s.live_dev.erase(it);
   try {
-    size_t &kept = s.kept_dev[key.first];
-    if (s.spaces > 0 && kept + key.second <= kDeviceCap) {
-      s.free_dev[key].push_back(p);
-      kept += key.second;
+    if (s.spaces > 0 && key.second <= kDeviceCap) {
+      make_room(s, key.first, key.second);
+      s.free_dev[key].push_back(Block{p, s.count++});
+      s.kept_dev[key.first] += key.second;
       return;
     }
   } catch (const std::bad_alloc &) {
@@ -191,10 +232,12 @@ void pinned_put(void *host) {
   auto it = s.live_pin.find(host);
   if (it == s.live_pin.end()) return;
   const size_t size = it->second.first;
-  const Pinned b{host, it->second.second};
+  Pinned b{host, it->second.second, 0};
   s.live_pin.erase(it);
   try {
-    if (s.spaces > 0 && s.kept_pin + size <= kPinnedCap) {
+    if (s.spaces > 0 && size <= kPinnedCap) {
+      make_room_pinned(s, size);
+      b.since = s.count++;
       s.free_pin[size].push_back(b);
       s.kept_pin += size;
       return;

@@ -7,9 +7,10 @@
 // streams are therefore kept for the next handle.
 //
 //   - Bounded: at most kDeviceCap bytes of device memory per GPU, kPinnedCap
-//     bytes of pinned host memory and kStreamCap streams are kept; what
-//     exceeds that goes back to the driver at once, and so does everything
-//     kept when an allocation fails (which is then tried again).
+//     bytes of pinned host memory and kStreamCap streams are kept.  A block that
+//     would exceed its bound makes the ones kept longest go back to the driver
+//     first; everything kept goes back when an allocation fails (which is then
+//     tried again).
 //   - Given back: the pool lives as long as some space does.  When the last
 //     space is destroyed, everything kept is returned to the driver, and on
 //     request (cgs_release_memory) at any time.

@@ -167,7 +167,10 @@ hipError_t hipFree(void *p) {
   note("free", nullptr);
   return give(p);
 }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return take(p, n); }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+  note("pin", nullptr, std::to_string(n));
+  return take(p, n);
+}
 hipError_t hipHostFree(void *p) { return give(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) {
   *d = h;
