@@ -3902,7 +3902,10 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
         const int made = cur->h_jobs[j].n_draws;
         for (int k = 0; k < made && !r.stop; ++k) {
           const Pick &p = picks[(size_t)j * kMaxDrawSeries + k];
-          if (p.total == 0) break; // no configuration left
+          if (p.total == 0) { // no configuration left: the draws after it were not needed
+            r.u -= (uint64_t)(made - 1 - k);
+            break;
+          }
           if (test(map[j], p.valid, false)) {
             r.stop = true;
           } else {

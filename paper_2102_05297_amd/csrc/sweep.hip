@@ -1098,7 +1098,10 @@ __global__ __launch_bounds__(kSmallThreads) void batch_tune(const BatchSess *__r
         bool next = false, stop = false;
         uint32_t next_c = 0;
         for (int k = 0; k < n_draws && !stop; ++k) {
-          if (picks.total[k] == 0) break; // no configuration left
+          if (picks.total[k] == 0) { // no configuration left: the draws after it were not needed
+            r.u -= (uint64_t)(n_draws - 1 - k);
+            break;
+          }
           if (test(picks.pos[k], false, runtime[k])) {
             stop = true;
           } else {
