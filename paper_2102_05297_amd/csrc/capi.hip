@@ -3559,14 +3559,17 @@ bool tune_pays_on_device(uint64_t nv, int n, const cgs_tuning_opts *o) {
 
 // The runs of cgs_tuning_run_batch on the device from start to end
 // (batch_tune): arguments as there, checked; every run has a first number.
+// *room = false, with nothing done, where its buffers do not fit: the runs
+// need none with a launch per iteration.
 cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *counters,
                           const cgs_expert_params &ep, const uint64_t *uniforms,
                           uint64_t n_uniforms, const cgs_tuning_opts *opts, double thresh,
                           uint64_t capacity, uint64_t *tested, uint8_t *profiled,
-                          uint64_t *n_tests, uint64_t *tests_to_well) {
+                          uint64_t *n_tests, uint64_t *tests_to_well, bool *room) {
   const int n = b->n;
   const uint64_t nv = b->sess[0]->space->n_valid;
   hipStream_t st = b->stream;
+  *room = true;
   const cgs_status joined = join_sessions(b);
   if (joined != CGS_OK) return joined;
   TuneArgs a{};
@@ -3574,17 +3577,6 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
   // an iteration tests its configuration, of at most nv, and uses draws numbers
   const uint64_t iters = std::min<uint64_t>((uint64_t)opts->max_tests, nv);
   a.stride_u = std::min<uint64_t>(n_uniforms, 1 + (uint64_t)opts->draws * iters);
-  std::vector<uint64_t> packed; // (copies of single rows take 10 us each)
-  if (a.stride_u < n_uniforms) {
-    try {
-      packed.resize((size_t)n * a.stride_u);
-    } catch (...) {
-      return fail(CGS_ENOMEM, "host copy of the random numbers");
-    }
-    for (int i = 0; i < n; ++i)
-      std::copy_n(uniforms + (size_t)i * n_uniforms, a.stride_u,
-                  packed.begin() + (size_t)i * a.stride_u);
-  }
   a.max_tests = (uint64_t)opts->max_tests;
   a.cap = std::min<uint64_t>(a.max_tests, 2 * nv); // drawn once, profiled once
   a.thresh = thresh;
@@ -3592,8 +3584,26 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
   a.draws = (uint32_t)opts->draws;
   a.max_iters = 1024; // per launch
   a.stop_at_well = opts->stop_at_well;
-  std::vector<TuneRun> run(n);
+  // the lists come back whole where that is small, else run by run
+  const bool whole = (uint64_t)n * a.cap <= (uint64_t)1 << 18;
+  const size_t n_list = whole ? (size_t)n * a.cap : (size_t)a.cap;
+  std::vector<uint64_t> packed; // (copies of single rows take 10 us each)
+  std::vector<TuneRun> run;
+  std::vector<uint32_t> h_tested;
+  std::vector<uint8_t> h_prof;
+  try {
+    if (a.stride_u < n_uniforms) packed.resize((size_t)n * a.stride_u);
+    run.resize(n);
+    h_tested.resize(n_list);
+    h_prof.resize(n_list);
+  } catch (...) {
+    *room = false;
+    return CGS_OK;
+  }
   for (int i = 0; i < n; ++i) {
+    if (!packed.empty())
+      std::copy_n(uniforms + (size_t)i * n_uniforms, a.stride_u,
+                  packed.begin() + (size_t)i * a.stride_u);
     run[i] = TuneRun{};
     run[i].state = kTuneStart;
     run[i].parity = b->sess[i]->parity;
@@ -3607,6 +3617,20 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
   if (e == hipSuccess) e = dalloc(&a.tested, (size_t)n * a.cap);
   if (e == hipSuccess) e = dalloc(&a.profiled, (size_t)n * a.cap);
   if (e == hipSuccess) e = dalloc(&a.run, n);
+  auto release = [&]() {
+    settle(e, st);
+    dfree(d_rt);
+    dfree(d_ct);
+    dfree(d_u);
+    dfree(a.tested);
+    dfree(a.profiled);
+    dfree(a.run);
+  };
+  if (e == hipErrorOutOfMemory) {
+    release();
+    *room = false;
+    return CGS_OK;
+  }
   if (e == hipSuccess) e = hipMemcpyAsync(d_rt, runtime, nv * 4, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(d_ct, counters, nv * 24 * 8, hipMemcpyHostToDevice, st);
   if (e == hipSuccess)
@@ -3630,40 +3654,12 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
   }
   float ms = 0.0f;
   if (e == hipSuccess) e = hipEventElapsedTime(&ms, b->e0, b->e1);
-  uint64_t longest = 0;
+  if (e != hipSuccess) {
+    release();
+    return fail(CGS_EDEVICE, "tuning runs: %s", hipGetErrorString(e));
+  }
   uint32_t steps = 1;
-  for (const TuneRun &r : run) {
-    longest = std::max(longest, r.nt);
-    steps = std::max(steps, r.steps);
-  }
-  // the lists whole where that is small, else each run's part
-  const bool whole = (uint64_t)n * a.cap <= (uint64_t)1 << 18;
-  const uint64_t ld = whole ? a.cap : longest;
-  std::vector<uint32_t> h_tested;
-  std::vector<uint8_t> h_prof;
-  try {
-    h_tested.resize((size_t)n * ld);
-    h_prof.resize((size_t)n * ld);
-  } catch (...) {
-    if (e == hipSuccess) e = hipErrorOutOfMemory;
-  }
-  for (int i = 0; i < (whole ? 1 : n) && e == hipSuccess; ++i) {
-    const size_t from = (size_t)i * a.cap, to = (size_t)i * ld, k = whole ? n * ld : run[i].nt;
-    if (k) e = hipMemcpyAsync(h_tested.data() + to, a.tested + from, k * 4, hipMemcpyDeviceToHost, st);
-    if (k && e == hipSuccess)
-      e = hipMemcpyAsync(h_prof.data() + to, a.profiled + from, k, hipMemcpyDeviceToHost, st);
-  }
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  settle(e, st);
-  dfree(d_rt);
-  dfree(d_ct);
-  dfree(d_u);
-  dfree(a.tested);
-  dfree(a.profiled);
-  dfree(a.run);
-  if (e != hipSuccess)
-    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "tuning runs: %s",
-                hipGetErrorString(e));
+  for (const TuneRun &r : run) steps = std::max(steps, r.steps);
   // the sessions look as after the steps and draws one by one
   b->last_ms = ms / (float)steps; // of a step
   b->seq += (uint64_t)kMaxDrawSeries * steps;
@@ -3688,6 +3684,7 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
     }
   }
   if (bad >= 0) {
+    release();
     if (run[bad].state == kTuneBadCounters)
       return fail(CGS_EINVAL, "run %d: expert system rejected the counters", bad);
     if (run[bad].state == kTuneNoNumbers)
@@ -3695,14 +3692,27 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
                   (unsigned long long)n_uniforms);
     return fail(CGS_EDEVICE, "session %d: no pick although Q > 0", bad);
   }
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < n && e == hipSuccess; ++i) {
     const TuneRun &r = run[i];
-    for (uint64_t k = 0; k < r.nt; ++k) {
-      tested[(uint64_t)i * capacity + k] = h_tested[(size_t)i * ld + k];
-      if (profiled) profiled[(uint64_t)i * capacity + k] = h_prof[(size_t)i * ld + k];
+    const size_t from = (size_t)i * a.cap, at = whole ? from : 0;
+    if (!whole || i == 0) {
+      const size_t k = whole ? n_list : (size_t)r.nt;
+      if (k) e = hipMemcpyAsync(h_tested.data(), a.tested + from, k * 4, hipMemcpyDeviceToHost, st);
+      if (k && e == hipSuccess)
+        e = hipMemcpyAsync(h_prof.data(), a.profiled + from, k, hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);
+      if (e != hipSuccess) break;
     }
-    n_tests[i] = r.nt;
-    tests_to_well[i] = r.found;
+    for (uint64_t k = 0; k < r.nt; ++k) {
+      tested[(uint64_t)i * capacity + k] = h_tested[at + k];
+      if (profiled) profiled[(uint64_t)i * capacity + k] = h_prof[at + k];
+    }
+  }
+  release();
+  if (e != hipSuccess) return fail(CGS_EDEVICE, "tuning runs: %s", hipGetErrorString(e));
+  for (int i = 0; i < n; ++i) {
+    n_tests[i] = run[i].nt;
+    tests_to_well[i] = run[i].found;
   }
   return CGS_OK;
 }
@@ -3800,9 +3810,13 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
     cgs_default_expert_params(&ep);
     if (expert) ep = *expert;
     // settings that the expert system refuses fail where it is first asked, below
-    if (ep.inst_reaction >= 0.0 && ep.inst_reaction < 1.0 && ep.cores > 0.0)
-      return tune_on_device(b, runtime, counters, ep, uniforms, n_uniforms, opts, thresh, capacity,
-                            tested, profiled, n_tests, tests_to_well);
+    if (ep.inst_reaction >= 0.0 && ep.inst_reaction < 1.0 && ep.cores > 0.0) {
+      bool room = true;
+      const cgs_status ts =
+          tune_on_device(b, runtime, counters, ep, uniforms, n_uniforms, opts, thresh, capacity,
+                         tested, profiled, n_tests, tests_to_well, &room);
+      if (room) return ts;
+    }
   }
   std::vector<Pick> picks(series ? (size_t)n * kMaxDrawSeries : 0);
   cgs_status st = CGS_OK;

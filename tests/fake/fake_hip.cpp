@@ -40,8 +40,8 @@ void note(const char *what, hipStream_t s, const std::string &more = "") {
   g_log += std::string(what) + " " + std::to_string(n) + (more.empty() ? "" : " " + more) + "\n";
 }
 
-hipError_t take(void **p, size_t n) {
-  if (g_used + n > g_limit) return hipErrorOutOfMemory;
+hipError_t take(void **p, size_t n, size_t limit) {
+  if (g_used + n > limit) return hipErrorOutOfMemory;
   *p = std::calloc(1, n ? n : 1); // pages come with their first use
   g_used += n;
   g_live[*p] = n;
@@ -159,7 +159,7 @@ hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int v) {
 }
 
 hipError_t hipMalloc(void **p, size_t n) {
-  const hipError_t e = take(p, n);
+  const hipError_t e = take(p, n, g_limit);
   note("malloc", nullptr, std::to_string(n) + (e == hipSuccess ? "" : " refused"));
   return e;
 }
@@ -169,7 +169,7 @@ hipError_t hipFree(void *p) {
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
   note("pin", nullptr, std::to_string(n));
-  return take(p, n);
+  return take(p, n, SIZE_MAX); // the limit is the device's
 }
 hipError_t hipHostFree(void *p) { return give(p); }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) {
