@@ -380,12 +380,8 @@ hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, ui
     const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(tiles, (uint32_t)n_cu * per_cu));
 #define CGS_FOREST_RES(TMV, BV)                                                                 \
   do {                                                                                          \
-    if (res_lds > 65536) {                                                                      \
-      const hipError_t e = hipFuncSetAttribute(                                                 \
-          reinterpret_cast<const void *>(forest_eval_resident<TMV, BV>),                        \
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)res_lds);                            \
-      if (e != hipSuccess) return e;                                                            \
-    }                                                                                           \
+    const hipError_t e = allow_lds(forest_eval_resident<TMV, BV>, res_lds, kResidentLds);       \
+    if (e != hipSuccess) return e;                                                              \
     hipLaunchKernelGGL((forest_eval_resident<TMV, BV>), dim3(grid), dim3(kResidentThreads),     \
                        res_lds, stream, d_space, d_idx, first, count, d_nodes, d_leaves,        \
                        n_trees, depth, n_counters, d_P, stride, d_leaf_out);                    \

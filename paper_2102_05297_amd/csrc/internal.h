@@ -205,6 +205,17 @@ struct MlpFwdArgs {
 
 hipError_t launch_mlp_forward(const MlpFwdArgs &a, bool train, hipStream_t stream);
 
+// Lets `kernel` use up to `most` bytes of dynamic LDS, for launches that need more
+// than 62 KB of it (below that, with a kernel's static part, it needs no leave).
+// `most` is the same for every launch of a kernel: the limit is the process's,
+// and one set for a smaller launch could stand in the way of a larger one on
+// another thread.
+template <typename K> hipError_t allow_lds(K kernel, size_t bytes, size_t most) {
+  if (bytes <= 62 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+}
+
 // ---- launchers (each enqueues on `stream`; return hipSuccess or an error)
 constexpr uint32_t kEnumTile = 2048; // raw indices per tile of the enumeration
 // d_tables: enumeration_table_bytes(), read until phase 0 is done; d_tile_off

@@ -800,12 +800,6 @@ __global__ __launch_bounds__(kNestThreads, CB <= 32 ? 4 : 2) void poly_eval_nest
   }
 }
 
-template <typename K> hipError_t allow_lds(K kernel, size_t bytes) {
-  if (bytes <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 constexpr size_t kEvalLds = 144 * 1024;
 constexpr size_t kSolveLds = 156 * 1024;
 
@@ -859,7 +853,7 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
   poly_features<<<gf, kPolyThreads, 0, stream>>>(d_pd, d_space, d_idx, nv, d_pts, d_Y, n, d_F,
                                                  d_err);
   const size_t gram_lds = (size_t)2 * kGramChunk * (kGB + 1) * sizeof(double);
-  hipError_t e = allow_lds(poly_gram, gram_lds);
+  hipError_t e = allow_lds(poly_gram, gram_lds, gram_lds);
   if (e != hipSuccess) return e;
   // few (subspace, block pair) workgroups: each subspace's points in parts
   const uint32_t parts = d_Gp ? poly_gram_parts(S, n_pairs) : 1u;
@@ -871,7 +865,7 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
     poly_gram_sum<<<g, 256, 0, stream>>>(d_Gp, total, parts, d_G);
   }
   const size_t lds = poly_solve_lds(T, C);
-  e = allow_lds(poly_solve, lds);
+  e = allow_lds(poly_solve, lds, kSolveLds);
   if (e != hipSuccess) return e;
   poly_solve<<<S, kSolveThreads, lds, stream>>>(d_pd, d_G, poly_solve_cc(T, C), d_beta64,
                                                d_beta32, d_err);
@@ -880,14 +874,15 @@ hipError_t launch_poly_fit(const PolyDev *d_pd, int T, int C, int S, const Space
 
 namespace {
 
+constexpr size_t kNestLds = (160 - 10) * 1024; // 10 KB: the kernel's own arrays
+
 // Outer combinations per tile of the nested evaluation: the most that leave
 // room for two workgroups in a CU's LDS, or for one (0: not even eight).
 uint32_t nest_tile(int CB, const PolyNest &n, size_t *lds) {
   if (n.M == 0) return 0;
   const size_t fixed = ((size_t)n.r_in * (n.M | 1) + kNestSlack + (size_t)n.M * CB) * 4;
   const size_t per = ((size_t)n.M * CB + (n.K | 1)) * 4;
-  constexpr size_t kStatic = 10 * 1024; // the kernel's own arrays
-  for (size_t room : {80 * 1024 - kStatic, 160 * 1024 - kStatic})
+  for (size_t room : {kNestLds - 80 * 1024, kNestLds})
     for (uint32_t tile = kNestTile; tile >= 8; tile /= 2)
       if (fixed + tile * per <= room) {
         *lds = fixed + tile * per;
@@ -915,7 +910,7 @@ hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const Poly
     const uint32_t grid = std::min<uint32_t>((n_outer + span - 1) / span, 1u << 20);
 #define CGS_POLY_NEST(CBV)                                                                      \
   do {                                                                                          \
-    e = allow_lds(poly_eval_nested<CBV>, nest_lds);                                             \
+    e = allow_lds(poly_eval_nested<CBV>, nest_lds, kNestLds);                                   \
     if (e == hipSuccess)                                                                        \
       poly_eval_nested<CBV><<<grid, kNestThreads, nest_lds, stream>>>(                          \
           d_pd, d_nest, d_space, d_idx, d_mask, d_rank, nv, d_beta32, tile, d_P, stride);       \
@@ -939,7 +934,7 @@ hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const Poly
       1, std::min<uint32_t>(1024, (nv + kEvalThreads - 1) / kEvalThreads));
 #define CGS_POLY_EVAL(CBV)                                                                      \
   do {                                                                                          \
-    e = allow_lds(poly_eval<CBV>, lds);                                                         \
+    e = allow_lds(poly_eval<CBV>, lds, kEvalLds);                                               \
     if (e == hipSuccess)                                                                        \
       poly_eval<CBV><<<grid * groups, kEvalThreads, lds, stream>>>(                             \
           d_pd, d_space, d_idx, nv, d_beta32, SG, grid, d_P, stride);                           \

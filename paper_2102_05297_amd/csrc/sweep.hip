@@ -1699,11 +1699,7 @@ void small_shape(uint32_t n_valid, uint32_t *tiles, uint32_t *per, FastDiv *per4
 }
 
 namespace {
-template <typename K> hipError_t allow_small_lds(K kernel, size_t lds) {
-  if (lds <= 62 * 1024) return hipSuccess; // with the static part, no opt-in needed
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
+constexpr size_t kSmallLds = small_ld(kSmallPer) * kSmallThreads * sizeof(uint32_t);
 } // namespace
 
 hipError_t launch_small_step(SmallStep &a, hipStream_t stream) {
@@ -1713,7 +1709,7 @@ hipError_t launch_small_step(SmallStep &a, hipStream_t stream) {
   uint32_t grid;
   small_shape(a.n_valid, &grid, &a.per, &a.per4);
   const size_t lds = small_ld(a.per) * kSmallThreads * sizeof(uint32_t);
-  const hipError_t e = allow_small_lds(small_step, lds);
+  const hipError_t e = allow_lds(small_step, lds, kSmallLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(small_step, dim3(grid), dim3(kSmallThreads), lds, stream, a);
   return hipGetLastError();
@@ -1727,7 +1723,7 @@ hipError_t launch_batch_small(const BatchSess *d_sess, const SmallJob *d_jobs, u
   const uint32_t groups =
       std::max<uint32_t>(1, std::min<uint32_t>(std::min<uint32_t>(max_tiles, kAccSlots), kBatchSmallGroups / n));
   const size_t lds = small_ld(max_per) * kSmallThreads * sizeof(uint32_t);
-  const hipError_t e = allow_small_lds(batch_small, lds);
+  const hipError_t e = allow_lds(batch_small, lds, kSmallLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(batch_small, dim3(n * groups), dim3(kSmallThreads), lds, stream, d_sess,
                      d_jobs, groups, d_res);
@@ -1739,8 +1735,7 @@ hipError_t launch_batch_tune(const BatchSess *d_sess, const TuneArgs &a, uint32_
   if (n == 0) return hipSuccess;
   if (max_per > kSmallPer || a.draws < 1 || a.draws > kMaxDrawSeries) return hipErrorInvalidValue;
   const size_t lds = small_ld(max_per) * kSmallThreads * sizeof(uint32_t);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(batch_tune),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = allow_lds(batch_tune, kSmallLds, kSmallLds); // its static part is 6 KB
   if (e != hipSuccess) return e;
   batch_tune<<<n, kSmallThreads, lds, stream>>>(d_sess, a);
   return hipGetLastError();
@@ -1806,11 +1801,11 @@ hipError_t launch_nb_step(const NbFused &a, hipStream_t stream) {
   const size_t score = (2 * st.n_subsets + 1 + (size_t)cands * (st.act.n | 1)) * 4;
   const size_t lds = std::max(score, (size_t)2 * kNbThreads * (per | 1) * 4);
   auto kernel = lp == 16 ? nb_step<16> : lp == 8 ? nb_step<8> : nb_step<2>;
-  if (lds > 62 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
+  // most: every subset of 32 parameters, and 128 candidates' terms of every counter
+  constexpr size_t kNbLds = (2 * (size_t)kNbMaxSubsets + 1 + kNbThreads / 2 * (CGS_MAX_COUNTERS | 1)) * 4;
+  static_assert(kNbLds >= (size_t)2 * kNbThreads * (kNbFusedMax / kNbThreads | 1) * 4, "the compaction's");
+  const hipError_t e = allow_lds(kernel, lds, kNbLds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNbThreads), lds, stream, a);
   return hipGetLastError();
 }

@@ -1362,7 +1362,7 @@ hipError_t tree_fit_run(const TreeFitIn &in, TreeFitOut &out, TreeFitWork **work
 
   auto kh = P <= 8 ? fit_hist<8> : P <= 16 ? fit_hist<16> : fit_hist<32>;
   if (e == hipSuccess) e = allow_lds(kh, hist_lds);
-  if (e == hipSuccess) e = allow_lds(fit_split, split_lds);
+  if (e == hipSuccess) e = allow_lds(fit_split, split_lds, (size_t)2 * 8192 * 8);
   if (e == hipSuccess) e = allow_lds(fit_pcount, starts_lds);
   if (e == hipSuccess) e = allow_lds(fit_partition, tile_lds);
   static_assert(CGS_MAX_DEPTH + 1 <= 15, "fit_test instantiations");
