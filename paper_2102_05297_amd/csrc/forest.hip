@@ -133,7 +133,8 @@ __global__ __launch_bounds__(kForestThreads) void forest_eval(
 // node is one byte, the place of its bit (63, never set, for a threshold that
 // no digit exceeds).  A level is an LDS read and three instructions instead
 // of ten, and twice the nodes fit.  The walk bounds deep forests with few
-// counters, the leaf gathers the others (16 trees x 64 counters).
+// counters, the leaf gathers the others (16 trees x 64 counters).  Which forests
+// take it: byte_nodes_pay.
 // Measured on 4.0M configurations of 12 parameters (42 tests), nodes as
 // (feature, threshold) -> as bits: 16 trees of depth 12, 24 counters 674 -> 411
 // us, 8 counters 559 -> 256; 4 trees of depth 8 188 -> 142; one tree of depth
@@ -141,12 +142,18 @@ __global__ __launch_bounds__(kForestThreads) void forest_eval(
 // leaf ids and the results staged in LDS, took 594 us for the first and 270
 // for the second: the six loads of a lane from one leaf vector meet in the
 // vector cache anyway.
+//
+// A thread walks TM trees, whatever the number that exist, and holds their leaf
+// ids: up to 32 trees in multiples of eight at 1,024 threads, 128 registers
+// each; beyond, 512 threads (at 1,024 the leaf ids of 64 trees spill: 33 trees of
+// depth 6 and 8 counters 495 us on 1M configurations, 220 with 40 walked by 512
+// threads; 17 trees of depth 2 and 64 counters 436 us with 32 walked, 376 with 24).
 constexpr int kResidentThreads = 1024;
 constexpr int kResidentTrees = 16; // without kBits
 constexpr size_t kResidentLds = 160 * 1024 - 1024;
 
-template <int TM, bool kBits>
-__global__ __launch_bounds__(kResidentThreads) void forest_eval_resident(
+template <int TM, bool kBits, int NT>
+__global__ __launch_bounds__(NT) void forest_eval_resident(
     const SpaceDev *__restrict__ sp, const uint32_t *__restrict__ idx, uint32_t first,
     uint32_t count, const uint16_t *__restrict__ nodes, const float *__restrict__ leaves,
     int n_trees, int depth, int n_counters, float *__restrict__ P, uint64_t stride,
@@ -167,17 +174,17 @@ __global__ __launch_bounds__(kResidentThreads) void forest_eval_resident(
   const uint32_t n_int = (1u << depth) - 1u;
   // kBits: over [T][2^D], whose entry 0 is not a node
   const uint32_t total = kBits ? (uint32_t)n_trees << depth : (uint32_t)n_trees * n_int;
-  for (uint32_t j0 = threadIdx.x; j0 < total; j0 += kForestBatch * kResidentThreads) {
+  for (uint32_t j0 = threadIdx.x; j0 < total; j0 += kForestBatch * NT) {
     uint16_t v[kForestBatch];
 #pragma unroll
     for (int b = 0; b < kForestBatch; ++b) {
-      const uint32_t j = j0 + b * kResidentThreads, n = j & n_int;
+      const uint32_t j = j0 + b * NT, n = j & n_int;
       const bool have = j < total && (!kBits || n > 0);
       v[b] = have ? nodes[kBits ? (j >> depth) * n_int + n - 1u : j] : (uint16_t)0;
     }
 #pragma unroll
     for (int b = 0; b < kForestBatch; ++b) {
-      const uint32_t j = j0 + b * kResidentThreads;
+      const uint32_t j = j0 + b * NT;
       if (j >= total) continue;
       if (kBits) {
         const uint32_t base = bit_base[v[b] & 0xffu], thr = v[b] >> 8;
@@ -193,9 +200,9 @@ __global__ __launch_bounds__(kResidentThreads) void forest_eval_resident(
   const float t_div = (float)n_trees;
   const bool pow2 = (n_trees & (n_trees - 1)) == 0;
   const float t_inv = 1.0f / t_div;
-  const uint32_t n_tiles = (count + kResidentThreads - 1) / kResidentThreads;
+  const uint32_t n_tiles = (count + NT - 1) / NT;
   for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const uint32_t i = tile * kResidentThreads + threadIdx.x;
+    const uint32_t i = tile * NT + threadIdx.x;
     if (i >= count) break; // the last tile; no barrier follows
     const uint32_t l = first + i;
     uint64_t lo, hi = 0; // kBits: lo holds the tests' bits
@@ -353,6 +360,24 @@ hipError_t launch_sq_diff_dense(const float *Pa, const float *Pb, uint64_t strid
   return hipGetLastError();
 }
 
+// Whether a forest of T trees of depth D with C counters takes byte nodes where
+// the space allows them.  Microseconds on 1M configurations, (feature,
+// threshold) nodes -> bytes: the walks of one or two shallow trees are too short
+// to pay for the configuration's bits (1 x depth 1 x 5 20.6 -> 21.5, x depth 8 24.9
+// -> 22.5; 2 x 4 x 8 25.6 -> 27.4, 2 x 8 x 8 31.8 -> 28.8, 2 x 8 x 24 44.2 -> 46.1).
+// From three trees on every depth gains (3 x 1 x 24 52.4 -> 51.3, 16 x 11 x 8 220 ->
+// 104), up to 32 trees.  Beyond, few waves are in flight for the leaf gathers, so
+// their loads per tree decide: two always pay (33 x 2 x 8 193 -> 179, 40 x 11 x 8
+// 508 -> 344), six only where nearly all of the 64 trees walked exist (48 x 6 x 24
+// 639 -> 696, 57 x 6 x 24 862 -> 828), sixteen hardly (57 x 6 x 64 1,979 -> 2,118).
+bool byte_nodes_pay(int T, int D, int C) {
+  if (T == 1) return D >= 4;
+  if (T == 2) return D >= 8 && C <= 8;
+  if (T <= 32) return true;
+  const int loads = C % 4 ? C : C / 4; // of a leaf vector, 16 bytes each where they can be
+  return loads <= 2 || (T > 56 && loads <= 6);
+}
+
 // Evaluates valid configurations [first, first + count).  With d_leaf_out
 // set, also writes leaf ids [T][count] and skips nothing else.
 hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, uint32_t n_valid,
@@ -364,7 +389,7 @@ hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, ui
   const uint32_t count = d_leaf_out ? leaf_count : n_valid;
   if (count == 0) return hipSuccess;
   const uint32_t n_int = (1u << depth) - 1u;
-  const bool bits = n_bits <= 63;
+  const bool bits = n_bits <= 63 && byte_nodes_pay(n_trees, depth, n_counters);
   const size_t res_lds =
       bits ? (size_t)n_trees << depth : (size_t)n_trees * n_int * sizeof(uint16_t);
   const bool resident =
@@ -376,30 +401,36 @@ hipError_t launch_forest_eval(const SpaceDev *d_space, const uint32_t *d_idx, ui
     if (hipGetDevice(&dev) == hipSuccess)
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     const uint32_t per_cu = (uint32_t)std::max<size_t>(1, std::min<size_t>(2, kResidentLds / std::max<size_t>(res_lds, 1)));
-    const uint32_t tiles = (count + kResidentThreads - 1) / kResidentThreads;
-    const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(tiles, (uint32_t)n_cu * per_cu));
-#define CGS_FOREST_RES(TMV, BV)                                                                 \
+    auto grid_of = [&](uint32_t threads) {
+      const uint32_t tiles = (count + threads - 1) / threads;
+      return std::max<uint32_t>(1, std::min<uint32_t>(tiles, (uint32_t)n_cu * per_cu));
+    };
+#define CGS_FOREST_RES(TMV, BV, NT)                                                             \
   do {                                                                                          \
-    const hipError_t e = allow_lds(forest_eval_resident<TMV, BV>, res_lds, kResidentLds);       \
+    const hipError_t e = allow_lds(forest_eval_resident<TMV, BV, NT>, res_lds, kResidentLds);       \
     if (e != hipSuccess) return e;                                                              \
-    hipLaunchKernelGGL((forest_eval_resident<TMV, BV>), dim3(grid), dim3(kResidentThreads),     \
+    hipLaunchKernelGGL((forest_eval_resident<TMV, BV, NT>), dim3(grid_of(NT)), dim3(NT),         \
                        res_lds, stream, d_space, d_idx, first, count, d_nodes, d_leaves,        \
                        n_trees, depth, n_counters, d_P, stride, d_leaf_out);                    \
   } while (0)
+    constexpr int kN = kResidentThreads;
     if (bits) {
-      if (n_trees <= 1) CGS_FOREST_RES(1, true);
-      else if (n_trees <= 2) CGS_FOREST_RES(2, true);
-      else if (n_trees <= 4) CGS_FOREST_RES(4, true);
-      else if (n_trees <= 8) CGS_FOREST_RES(8, true);
-      else if (n_trees <= 16) CGS_FOREST_RES(16, true);
-      else if (n_trees <= 32) CGS_FOREST_RES(32, true);
-      else CGS_FOREST_RES(64, true);
+      if (n_trees <= 1) CGS_FOREST_RES(1, true, kN);
+      else if (n_trees <= 2) CGS_FOREST_RES(2, true, kN);
+      else if (n_trees <= 4) CGS_FOREST_RES(4, true, kN);
+      else if (n_trees <= 8) CGS_FOREST_RES(8, true, kN);
+      else if (n_trees <= 16) CGS_FOREST_RES(16, true, kN);
+      else if (n_trees <= 24) CGS_FOREST_RES(24, true, kN);
+      else if (n_trees <= 32) CGS_FOREST_RES(32, true, kN);
+      else if (n_trees <= 40) CGS_FOREST_RES(40, true, kN / 2);
+      else if (n_trees <= 48) CGS_FOREST_RES(48, true, kN / 2);
+      else CGS_FOREST_RES(64, true, kN / 2);
     } else {
-      if (n_trees <= 1) CGS_FOREST_RES(1, false);
-      else if (n_trees <= 2) CGS_FOREST_RES(2, false);
-      else if (n_trees <= 4) CGS_FOREST_RES(4, false);
-      else if (n_trees <= 8) CGS_FOREST_RES(8, false);
-      else CGS_FOREST_RES(16, false);
+      if (n_trees <= 1) CGS_FOREST_RES(1, false, kN);
+      else if (n_trees <= 2) CGS_FOREST_RES(2, false, kN);
+      else if (n_trees <= 4) CGS_FOREST_RES(4, false, kN);
+      else if (n_trees <= 8) CGS_FOREST_RES(8, false, kN);
+      else CGS_FOREST_RES(16, false, kN);
     }
 #undef CGS_FOREST_RES
     return hipGetLastError();
