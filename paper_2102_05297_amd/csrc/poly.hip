@@ -891,11 +891,39 @@ uint32_t nest_tile(int CB, const PolyNest &n, size_t *lds) {
   return 0;
 }
 
+// Whether the nested evaluation is expected to be clearly faster.  Its tiles are
+// a chain of short phases whose cost hardly depends on how many of a tile's
+// configurations are valid, while a configuration by itself costs T terms: few
+// terms, few valid configurations or a short tile leave nothing to gain.  The
+// microseconds below were fitted to 567 spaces (3 to 16 values, 64 to 16.8M
+// valid configurations of 0.01 % to all raw ones, 5 to 101 terms, 1 to 64
+// counters), where each form was timed: by itself, terms and counters per valid
+// configuration; nested, a workgroup's run of tiles times the launch's waves of
+// workgroups, for the tiles that hold anything.  They are within a third, and
+// 1.4 keeps what is not clear by itself.  Taken wherever a tile fits, the nested
+// form was slower on 334 of them, down to a quarter of the speed (5 x 16 values,
+// 17 % valid, 21 terms, 64 counters 30 -> 130 us); with this rule on one by more
+// than 5 % (70 against 56 us).  For the space above it says 759 and 163 us.
+bool nested_pays(int T, int CB, const PolyNest &n, uint32_t tile, size_t lds, uint32_t n_raw,
+                 uint32_t nv) {
+  const double m = 1e-6 * nv, MC = (double)n.M * CB;
+  const double single = 5.0 + 0.6 * T + m * (0.03 * T * CB + (CB > 32 ? 0.2 : 0.4) * T + 0.5 * CB);
+  const uint32_t n_outer = n_raw / n.r_in, tiles = (n_outer + tile - 1) / tile;
+  const double groups = (tiles + kNestRun - 1) / kNestRun, at_once = lds <= kNestLds - 80 * 1024 ? 512 : 256;
+  const double serial = std::min(tiles, kNestRun) * std::max(1.0, groups / at_once);
+  const double per_tile = (double)nv / tiles, held = std::min(1.0, per_tile);
+  const double eval = std::max(1.0, per_tile / kNestThreads) * (0.0024 * MC + 0.07 * CB);
+  const double form = tile / 32.0 * n.K * (0.0016 + 0.0007 * ((CB + 15) / 16));
+  const double nested = 13.0 + 0.006 * n.M * n.r_in + serial * (1.7 + held * (0.7 + eval + form)) +
+                        m * 0.64 * CB;
+  return nested * 1.4 < single;
+}
+
 } // namespace
 
-// Nested wherever the space has inner parameters (poly_nest: eight or more
-// combinations, so that forming g pays: 276 against 982 us above) and a tile
-// of combinations fits in LDS; otherwise every configuration by itself.
+// Nested where the space has inner parameters (poly_nest: eight or more
+// combinations), a tile of combinations fits in LDS and it pays; otherwise every
+// configuration by itself.
 hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const PolyNest &nest,
                             const PolyNest *d_nest, const SpaceDev *d_space, uint32_t n_raw,
                             const uint32_t *d_idx, const uint32_t *d_mask,
@@ -904,7 +932,8 @@ hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const Poly
   const int CB = C <= 8 ? 8 : C <= 16 ? 16 : C <= 24 ? 24 : C <= 32 ? 32 : C <= 48 ? 48 : 64;
   hipError_t e = hipSuccess;
   size_t nest_lds = 0;
-  if (const uint32_t tile = nest_tile(CB, nest, &nest_lds)) {
+  const uint32_t tile = nest_tile(CB, nest, &nest_lds);
+  if (tile && nested_pays(T, CB, nest, tile, nest_lds, n_raw, nv)) {
     const uint32_t n_outer = n_raw / nest.r_in;
     const uint32_t span = kNestRun * tile;
     const uint32_t grid = std::min<uint32_t>((n_outer + span - 1) / span, 1u << 20);
