@@ -1058,9 +1058,11 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
   m->n_counters = C;
   m->poly = pd;
   poly_nest(sp, pd, m->nest);
+  if (!poly_is_nested(T, C, m->nest, (uint32_t)sp->n_raw, (uint32_t)sp->n_valid)) m->nest.M = 0;
   m->stride = (sp->n_valid + 63) & ~(uint64_t)63;
-  std::vector<uint32_t> h_off, h_list, h_sub;
+  std::vector<uint32_t> h_off, h_list, h_copy;
   uint32_t *d_pts = nullptr, *d_sub = nullptr, *d_pairs = nullptr, *d_err = nullptr;
+  uint32_t *h_pin = nullptr;
   uint32_t *d_list = nullptr, *d_off = nullptr;
   float *d_y = nullptr;
   double *d_F = nullptr, *d_G = nullptr, *d_Gp = nullptr;
@@ -1073,7 +1075,8 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
     dfree(d_pts);
     dfree(d_list);
     dfree(d_off);
-    dfree(d_sub);
+    if (h_pin) pfree(h_pin); // d_sub is its device address
+    else dfree(d_sub);
     dfree(d_pairs);
     dfree(d_err);
     dfree(d_y);
@@ -1082,37 +1085,48 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
     dfree(d_Gp);
   };
   hipError_t e = dalloc(&m->d_poly, 1);
-  if (e == hipSuccess) e = dalloc(&m->d_nest, 1);
-  if (e == hipSuccess)
+  if (e == hipSuccess && m->nest.M) e = dalloc(&m->d_nest, 1);
+  if (e == hipSuccess && m->nest.M)
     e = hipMemcpyAsync(m->d_nest, &m->nest, sizeof(PolyNest), hipMemcpyHostToDevice, sp->stream);
   if (e == hipSuccess) e = dalloc(&m->d_beta64, (size_t)S * T * C);
   if (e == hipSuccess) e = dalloc(&m->d_beta32, (size_t)S * T * C);
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)C * m->stride);
   if (e == hipSuccess) e = dalloc(&d_pts, n);
   if (e == hipSuccess) e = dalloc(&d_y, n * (size_t)C);
-  if (e == hipSuccess) e = dalloc(&d_sub, n);
+  // the points' subspaces come straight to the host where they are few: a copy
+  // through device memory took 10 us more (a space without binary parameters has
+  // one subspace and needs neither)
+  constexpr uint64_t kPinnedPoints = 1u << 20;
+  if (e == hipSuccess && S > 1)
+    e = n <= kPinnedPoints ? palloc(&h_pin, &d_sub, n) : dalloc(&d_sub, n);
   if (e == hipSuccess)
     e = hipMemcpyAsync(m->d_poly, &pd, sizeof(pd), hipMemcpyHostToDevice, sp->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(d_pts, points, n * 4, hipMemcpyHostToDevice, sp->stream);
-  if (e == hipSuccess)
+  if (e == hipSuccess && S > 1)
     e = launch_poly_subspaces(m->d_poly, sp->d_desc, sp->d_idx, (uint32_t)sp->n_valid, d_pts,
                               (uint32_t)n, d_sub, sp->stream);
   // each subspace's points in input order: a stable counting sort on the host
   // (points outside the valid list are in no list: the fit flags them)
   try {
-    h_sub.resize(n);
     h_off.assign((size_t)S + 1, 0);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h_sub.data(), d_sub, n * 4, hipMemcpyDeviceToHost, sp->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
+    if (S > 1 && !h_pin) {
+      h_copy.resize(n);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(h_copy.data(), d_sub, n * 4, hipMemcpyDeviceToHost, sp->stream);
+    }
+    if (e == hipSuccess && S > 1) e = hipStreamSynchronize(sp->stream);
+    const uint32_t *h_sub = h_pin ? h_pin : h_copy.data();
+    auto sub_of = [&](uint64_t i) {
+      return S > 1 ? h_sub[i] : points[i] < sp->n_valid ? 0u : 1u; // S: none
+    };
     if (e == hipSuccess) {
-      for (uint32_t s : h_sub)
-        if (s < (uint32_t)S) ++h_off[(size_t)s + 1];
+      for (uint64_t i = 0; i < n; ++i)
+        if (sub_of(i) < (uint32_t)S) ++h_off[(size_t)sub_of(i) + 1];
       for (int s = 0; s < S; ++s) h_off[(size_t)s + 1] += h_off[s];
       h_list.resize(h_off[S]);
       std::vector<uint32_t> pos(h_off.begin(), h_off.end() - 1);
       for (uint64_t i = 0; i < n; ++i)
-        if (h_sub[i] < (uint32_t)S) h_list[pos[h_sub[i]]++] = (uint32_t)i;
+        if (sub_of(i) < (uint32_t)S) h_list[pos[sub_of(i)]++] = (uint32_t)i;
     }
   } catch (...) {
     if (e == hipSuccess) e = hipErrorOutOfMemory;

@@ -180,6 +180,10 @@ struct PolyNest {
   int32_t order[kNestMaxPadded];
   uint32_t slots[kNestMaxPadded];
 };
+// Whether a model is evaluated nested: the space has inner parameters (nest.M), a
+// tile of combinations fits in LDS and it pays.  Where not, the caller sets
+// nest.M = 0.
+bool poly_is_nested(int T, int C, const PolyNest &nest, uint32_t n_raw, uint32_t nv);
 hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const PolyNest &nest,
                             const PolyNest *d_nest, const SpaceDev *d_space, uint32_t n_raw,
                             const uint32_t *d_idx, const uint32_t *d_mask,

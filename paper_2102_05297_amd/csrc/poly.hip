@@ -919,21 +919,30 @@ bool nested_pays(int T, int CB, const PolyNest &n, uint32_t tile, size_t lds, ui
   return nested * 1.4 < single;
 }
 
+int counters_padded(int C) {
+  return C <= 8 ? 8 : C <= 16 ? 16 : C <= 24 ? 24 : C <= 32 ? 32 : C <= 48 ? 48 : 64;
+}
+
 } // namespace
 
-// Nested where the space has inner parameters (poly_nest: eight or more
-// combinations), a tile of combinations fits in LDS and it pays; otherwise every
+bool poly_is_nested(int T, int C, const PolyNest &nest, uint32_t n_raw, uint32_t nv) {
+  size_t lds = 0;
+  const int CB = counters_padded(C);
+  const uint32_t tile = nest_tile(CB, nest, &lds);
+  return tile && nested_pays(T, CB, nest, tile, lds, n_raw, nv);
+}
+
+// Nested where the model was found to be (poly_is_nested); otherwise every
 // configuration by itself.
 hipError_t launch_poly_eval(const PolyDev *d_pd, int T, int C, int S, const PolyNest &nest,
                             const PolyNest *d_nest, const SpaceDev *d_space, uint32_t n_raw,
                             const uint32_t *d_idx, const uint32_t *d_mask,
                             const uint32_t *d_rank, uint32_t nv, const float *d_beta32,
                             float *d_P, uint64_t stride, hipStream_t stream) {
-  const int CB = C <= 8 ? 8 : C <= 16 ? 16 : C <= 24 ? 24 : C <= 32 ? 32 : C <= 48 ? 48 : 64;
+  const int CB = counters_padded(C);
   hipError_t e = hipSuccess;
   size_t nest_lds = 0;
-  const uint32_t tile = nest_tile(CB, nest, &nest_lds);
-  if (tile && nested_pays(T, CB, nest, tile, nest_lds, n_raw, nv)) {
+  if (const uint32_t tile = nest_tile(CB, nest, &nest_lds)) { // nest.M == 0: none
     const uint32_t n_outer = n_raw / nest.r_in;
     const uint32_t span = kNestRun * tile;
     const uint32_t grid = std::min<uint32_t>((n_outer + span - 1) / span, 1u << 20);
