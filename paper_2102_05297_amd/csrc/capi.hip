@@ -2275,7 +2275,7 @@ extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params,
   const uint64_t n_words = (sp->n_valid + 31) / 32;
   hipError_t e = dalloc(&s->d_explored, n_words);
   if (e == hipSuccess) e = dalloc(&s->d_s, stride);
-  if (e == hipSuccess) e = dalloc(&s->d_bsum, s->n_blocks);
+  if (e == hipSuccess) e = dalloc(&s->d_bsum, (s->n_blocks + 1) & ~(uint64_t)1); // draws load pairs
   if (e == hipSuccess) e = dalloc(&s->d_acc, 2 * kAccSlots);
   if (e == hipSuccess) e = dalloc(&s->d_prof, 2);
   // one pinned block: the ring, the single result, the accumulators' copy
@@ -4061,7 +4061,7 @@ extern "C" cgs_status cgs_sample_weights(cgs_space sp, const uint32_t *q, uint64
   uint32_t *d_q = nullptr;
   uint64_t *d_bsum = nullptr;
   hipError_t e = dalloc(&d_q, (n + 63) & ~(uint64_t)63); // whole runs of draw weights
-  if (e == hipSuccess) e = dalloc(&d_bsum, n_blocks);
+  if (e == hipSuccess) e = dalloc(&d_bsum, (n_blocks + 1) & ~(uint64_t)1); // draws load pairs
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_q, q, n * sizeof(uint32_t), hipMemcpyHostToDevice, sp->stream);
   cgs_status r = e == hipSuccess ? sample_resident(sp, d_q, n, lg, d_bsum, n_blocks, u64, n_draws, picks)

@@ -373,8 +373,14 @@ static_assert(kNoIndex == kNoProfile, "a draw without a pick leaves no profile")
 // 7,616, four further draws of one series 14.5 us; 7.9, 7.7 and 28 us with
 // 1,024 threads, scans through the LDS crossbar, __syncthreads, the raw
 // index fetched after the pick and a releasing store per result.  16 block
-// sums a round trip: 6.0, 5.7 and 15.9 us (more instructions for the few
-// sums there are), 8.2 instead of 8.5 us on 27.7M configurations.
+// sums in the first round trip: 6.0, 5.7 and 15.9 us (more instructions for
+// the few sums there are).  Of spaces with more than 2,048 blocks the further
+// sums are loaded 16 bytes at a time: the 64 lanes of a load lie in 64 cache
+// lines, so the loads themselves bound it (a draw and its host turn, 8 bytes a
+// load -> 16: 16,384 blocks 20.1 -> 17.3 us, 65,536 45.4 -> 30.9; 21.3 and 43.1
+// with 1,024 threads; 32 sums a round trip 20.5 and 45.3).  Larger blocks: 2^13
+// configurations 13.5 us (16.1 with 1,024 threads), 2^16 42 (56), 2^20 513
+// (1,055) on 16.8M configurations.
 template <int NT, typename W>
 __device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum,
                             uint32_t n_blocks, int n, const uint64_t *u64,
@@ -391,10 +397,11 @@ __device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum
   const uint32_t tid = threadIdx.x;
 
   wsrc.stage_load();
-  const uint32_t per = (n_blocks + NT - 1) / NT;
+  constexpr uint32_t kChunk = 8; // block sums loaded per round trip
+  uint32_t per = (n_blocks + NT - 1) / NT;
+  if (per > kChunk) per = (per + 1u) & ~1u; // runs start at even blocks
   const uint32_t b0 = min(n_blocks, tid * per);
   const uint32_t b1 = min(n_blocks, b0 + per);
-  constexpr uint32_t kChunk = 8; // block sums loaded per round trip
   uint64_t mine, run0[kChunk];   // the run's total and its first block sums
   auto load_sums = [&](uint32_t c, uint64_t (&v)[kChunk]) {
 #pragma unroll
@@ -407,11 +414,27 @@ __device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum
     }
     return sum;
   };
+  // further sums two a load, as the lanes' loads of one instruction lie in as many
+  // cache lines: the array is padded to an even number
+  constexpr uint32_t kMore = 16;
+  auto load_pairs = [&](uint32_t c, uint64_t (&v)[kMore]) {
+    ulonglong2 w[kMore / 2];
+#pragma unroll
+    for (uint32_t k = 0; k < kMore / 2; ++k)
+      w[k] = *reinterpret_cast<const ulonglong2 *>(bsum + min(c + 2 * k, (n_blocks - 1) & ~1u));
+    uint64_t sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kMore; ++k) {
+      v[k] = c + k < b1 ? (k & 1u ? w[k / 2].y : w[k / 2].x) : 0ull;
+      sum += v[k];
+    }
+    return sum;
+  };
   if (n_blocks != 0) {
     mine = load_sums(b0, run0);
-    for (uint32_t c = b0 + kChunk; c < b1; c += kChunk) {
-      uint64_t v[kChunk];
-      mine += load_sums(c, v);
+    for (uint32_t c = b0 + kChunk; c < b1; c += kMore) {
+      uint64_t v[kMore];
+      mine += load_pairs(c, v);
     }
   } else {
     mine = 0;
@@ -435,9 +458,9 @@ __device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum
       uint64_t run = pre;
       uint32_t at = kNoIndex;
       uint64_t rem = 0;
-      auto find = [&](uint32_t c, const uint64_t (&v)[kChunk]) {
+      auto find = [&](uint32_t c, const auto &v) {
 #pragma unroll
-        for (uint32_t k = 0; k < kChunk; ++k) {
+        for (uint32_t k = 0; k < sizeof(v) / sizeof(v[0]); ++k) {
           const bool hit = at == kNoIndex && r < run + v[k];
           rem = hit ? r - run : rem;
           at = hit ? c + k : at;
@@ -445,9 +468,9 @@ __device__ void draw_series(W &wsrc, int block_log2, uint64_t *__restrict__ bsum
         }
       };
       find(b0, run0);
-      for (uint32_t c = b0 + kChunk; c < b1 && at == kNoIndex; c += kChunk) {
-        uint64_t v[kChunk];
-        load_sums(c, v);
+      for (uint32_t c = b0 + kChunk; c < b1 && at == kNoIndex; c += kMore) {
+        uint64_t v[kMore];
+        load_pairs(c, v);
         find(c, v);
       }
       found_block = at;
