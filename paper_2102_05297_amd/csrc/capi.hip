@@ -3558,17 +3558,20 @@ namespace {
 // start to end: where that is expected to be faster than a launch and a host
 // turn per iteration.  On the device an iteration is one workgroup's, which
 // the number of runs does not slow, and the runtimes and counters are uploaded
-// first; with the host it grows with the runs.  The microseconds below fit,
-// host -> device, with 5 draws: 1,200 configurations, 150 tests, 64 runs 2,857
-// -> 590, 8 runs 944 -> 528; 6,750, 150 tests, 64 runs 2,950 -> 964, 4 runs 867
-// -> 892; 24,654, 150 tests, 64 runs 3,810 -> 2,214, 16 runs 1,657 -> 2,111;
-// 6,750, 20 tests, 64 runs 574 -> 362, 8 runs 207 -> 297.
+// first; with the host it grows with the runs and their draws.  The
+// microseconds are a fit to 360 batches of 1,200 to 32,768 configurations, 1 to
+// 200 runs, 1 to 33 draws and 8 to 400 tests, each made both ways (the host's
+// share is that machine's): the rule's way was the slower one by more than a
+// tenth on two of them, by 12 %.  Host -> device, 64 runs: 6,750 configurations,
+// 5 draws, 150 tests 2,950 -> 964; 32,768, 33 draws, 150 tests 2,690 -> 974;
+// 24,696, 1 draw, 8 tests 545 -> 639; 16 runs: 6,750, 33 draws, 150 tests 825 ->
+// 506; one run: 1,200, 5 draws, 40 tests 249 -> 312.
 bool tune_pays_on_device(uint64_t nv, int n, const cgs_tuning_opts *o) {
-  const double iters =
-      1.0 + (double)std::min<uint64_t>((uint64_t)o->max_tests, nv) / (o->draws + 1.0);
-  const double host = 31.0 + 1.2 * n + 2e-5 * (double)nv * n;
-  const double device = 13.0 + 0.0022 * (double)nv;
-  return 110.0 + 0.0075 * (double)nv + iters * device < iters * host;
+  const double d = o->draws, v = (double)nv;
+  const double iters = 1.0 + (double)std::min<uint64_t>((uint64_t)o->max_tests, nv) / (d + 1.0);
+  const double host = 26.0 + 0.5 * d + 3.4e-4 * v + n * (0.1 + 0.19 * d + 1.4e-5 * v);
+  const double device = 7.8 + 1.05 * d + 0.0022 * v;
+  return 108.0 + 0.0049 * v + 0.3 * n + iters * device < iters * host;
 }
 
 // The runs of cgs_tuning_run_batch on the device from start to end
