@@ -58,3 +58,17 @@ for bad in values:
         fake.fake_limit(1 << 40)
 load(None)
 """)
+
+
+@pytest.mark.parametrize("depth,C,device", [(0, 24, False), (10, 16, False), (10, 17, True)])   # up to 16,384 values
+def test_few_values_are_looked_through_on_the_host(depth, C, device):
+    fake.run(f"""
+sp = space(4, 4, 4)
+z = np.zeros((1, (1 << {depth}) - 1), np.uint8)
+leaves = np.ones((1, 1 << {depth}, {C}), np.float32)
+fake.fake_clear()
+m.ForestModel(sp, z, z, leaves)
+assert any("check_" in e[2] for e in log() if e[0] == "launch") == {device}
+leaves[0, -1, -1] = np.nan
+assert status(lambda: m.ForestModel(sp, z, z, leaves)) == m.EINVAL
+""")
