@@ -3,7 +3,7 @@
 // that they can fail), copies are made at once, and every launch, wait and
 // allocation is logged by stream.  Kernels do not run; the few whose results
 // the host needs to go on are stood in for: an enumeration finds every
-// configuration valid, the check of a model's inputs is made, and a draw
+// configuration valid (every n-th with fake_every(n)), the check of a model's inputs is made, and a draw
 // publishes configuration 0 (unless fake_publish(0)).
 //
 // The entry points stand in front of the real runtime's when this library is
@@ -29,6 +29,7 @@ std::unordered_map<const void *, int> g_lds;            // attribute of a kernel
 std::map<std::string, int> g_stream;                    // address -> number
 size_t g_used = 0, g_limit = (size_t)1 << 46;
 bool g_publish = true;
+uint32_t g_every = 1;
 dim3 g_grid, g_block;
 size_t g_shared;
 hipStream_t g_on;
@@ -69,11 +70,14 @@ void run(const std::string &k, void **args) {
   if (is("9enum_mark")) {
     const auto *sp = arg<const cgs::SpaceDev *>(args, 0);
     auto *mask = arg<uint32_t *>(args, 6);
-    for (uint32_t i = 0; i < sp->n_raw; i += 32)
-      mask[i / 32] = sp->n_raw - i >= 32 ? ~0u : (1u << (sp->n_raw - i)) - 1u;
     auto *count = arg<uint32_t *>(args, 7);
-    for (uint32_t t = 0; t < arg<uint32_t>(args, 5); ++t)
-      count[t] = sp->n_raw - t * cgs::kEnumTile < cgs::kEnumTile ? sp->n_raw - t * cgs::kEnumTile : cgs::kEnumTile;
+    for (uint32_t t = 0; t < arg<uint32_t>(args, 5); ++t) count[t] = 0;
+    if (g_every > 1) std::memset(mask, 0, sp->n_words * 4);
+    for (uint64_t i = 0; i < sp->n_raw; i += g_every == 1 ? 32 : g_every) {
+      const uint64_t n = g_every > 1 ? 1 : sp->n_raw - i >= 32 ? 32 : sp->n_raw - i;
+      mask[i / 32] |= (n == 32 ? ~0u : (1u << n) - 1u) << (g_every > 1 ? i % 32 : 0);
+      count[i / cgs::kEnumTile] += (uint32_t)n;
+    }
   } else if (is("9enum_scan")) {
     const auto *count = arg<const uint32_t *>(args, 0);
     auto *off = arg<uint32_t *>(args, 2);
@@ -83,6 +87,10 @@ void run(const std::string &k, void **args) {
       sum += count[t];
     }
     *arg<uint64_t *>(args, 3) = sum;
+  } else if (is("12enum_compact") && g_every > 1) {
+    const auto *sp = arg<const cgs::SpaceDev *>(args, 0);
+    auto *idx = arg<uint32_t *>(args, 3);
+    for (uint64_t i = 0; i < sp->n_raw; i += g_every) *idx++ = (uint32_t)i;
   } else if (is("11check_begin")) {
     *arg<uint64_t *>(args, 0) = ~0ull;
   } else if (is("12check_floats")) {
@@ -124,6 +132,7 @@ void fake_clear() { g_log.clear(); }
 void fake_limit(size_t bytes_left) { g_limit = g_used + bytes_left; }
 size_t fake_used() { return g_used; }
 void fake_publish(int on) { g_publish = on != 0; }
+void fake_every(unsigned n) { g_every = n; }
 
 void **__hipRegisterFatBinary(const void *) {
   static void *h;
