@@ -28,21 +28,23 @@ constexpr uint32_t kTile = kEnumTile;
 static_assert(kTile == kEnumThreads * kRowsPerWave, "a row of 64 per wave and step");
 constexpr uint32_t kTruth = CGS_MAX_RADIX * CGS_MAX_RADIX;
 constexpr uint32_t kMaxLow = 1024; // 16 KB of LDS
+constexpr uint32_t kMaxMid = 256;  // 4 KB
 
 // The tables of one space: truth[c * 256 + 16 da + db], bit dc: constraint c
 // holds for digits da, db, dc of its parameters; low[r]: the packed digits of
-// raw index r < n_low, the product of the last parameters' radices.
-// Workgroups 0 .. n_cons - 1 write one constraint each, the others `low`.
+// raw index r < n_low, the product of the last parameters' radices; low[n_low +
+// m]: those of raw index m n_low, m < n_mid, the product of the radices before
+// them.  Workgroups 0 .. n_cons - 1 write one constraint each, the others `low`.
 __global__ __launch_bounds__(kEnumThreads) void enum_tables(const SpaceDev *__restrict__ sp,
-                                                            uint32_t n_low,
+                                                            uint32_t n_low, uint32_t n_mid,
                                                             uint32_t *__restrict__ truth,
                                                             ulonglong2 *__restrict__ low) {
   const uint32_t n_cons = (uint32_t)sp->n_cons, tid = threadIdx.x;
   if (blockIdx.x >= n_cons) {
     const uint32_t r = (blockIdx.x - n_cons) * kEnumThreads + tid;
-    if (r >= n_low) return;
+    if (r >= n_low + n_mid) return;
     uint64_t lo, hi;
-    decode_packed(r, sp, lo, hi);
+    decode_packed(r < n_low ? r : (r - n_low) * n_low, sp, lo, hi);
     low[r] = make_ulonglong2(lo, hi);
     return;
   }
@@ -64,25 +66,34 @@ __global__ __launch_bounds__(kEnumThreads) void enum_tables(const SpaceDev *__re
 // every parameter and evaluating every constraint takes (a division for each
 // parameter and for each divisibility constraint): the 64 configurations of a
 // row share their high digits (at most two values, as n_low >= 64 unless it
-// is the whole space), decoded with scalar instructions; the low digits are
-// one LDS read, and a constraint is one LDS read of its truth table.
+// is the whole space); the low digits are one LDS read per configuration, those
+// above them are decoded with scalar instructions, about once per tile; a
+// constraint is one LDS read of its truth table.  kMid: the high digits would
+// change too often (n_low < 512), so the middle ones have a table too.
 // Measured on 2^24 configurations of 12 parameters, 6 constraints: 87 us (3 us
 // for the tables); a decode and the constraints themselves per configuration
-// 205 us; decoding the high digits for every row 387 us.
+// 205 us; decoding the high digits for every row 387 us.  Without the middle
+// table, n_low = 128 (the last radices 16, 16 and 8) came near that: 2^31 raw
+// indices, 2 constraints 13.5 ms, 6.9 with it; on n_low = 1,024 (2^30) it would
+// take 3.1 -> 3.4.
+template <bool kMid>
 __global__ __launch_bounds__(kEnumThreads) void enum_mark(
     const SpaceDev *__restrict__ sp, const uint32_t *__restrict__ truth_in,
     const ulonglong2 *__restrict__ low_in, uint32_t n_low, FastDiv div_low, uint32_t n_tiles,
-    uint32_t *__restrict__ mask, uint32_t *__restrict__ tile_count) {
-  extern __shared__ ulonglong2 low[]; // [n_low], then the truth tables
+    uint32_t *__restrict__ mask, uint32_t *__restrict__ tile_count, uint32_t n_mid,
+    FastDiv div_mid) {
+  extern __shared__ ulonglong2 low[]; // [n_low], [n_mid], then the truth tables
   __shared__ uint32_t wave_cnt[kEnumThreads / kWave];
   const uint32_t n_raw = sp->n_raw, n_words = sp->n_words, n_cons = (uint32_t)sp->n_cons;
-  uint32_t *truth = reinterpret_cast<uint32_t *>(low + n_low);
-  for (uint32_t e = threadIdx.x; e < n_low; e += kEnumThreads) low[e] = low_in[e];
+  const ulonglong2 *mid = low + n_low;
+  uint32_t *truth = reinterpret_cast<uint32_t *>(low + n_low + n_mid);
+  for (uint32_t e = threadIdx.x; e < n_low + n_mid; e += kEnumThreads) low[e] = low_in[e];
   for (uint32_t e = threadIdx.x; e < n_cons * kTruth; e += kEnumThreads) truth[e] = truth_in[e];
   __syncthreads();
 
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t n_both = n_low * (kMid ? n_mid : 1u);
   uint32_t have = ~0u; // the value whose digits are lo0, hi0 (the next one's: lo1, hi1)
   uint64_t lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
   for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -92,20 +103,28 @@ __global__ __launch_bounds__(kEnumThreads) void enum_mark(
 #pragma unroll
     for (int row = 0; row < kRowsPerWave; ++row) {
       const uint64_t row_base = min(wave_base + (uint64_t)row * kWave, (uint64_t)(n_raw - 1));
-      const uint32_t q = fastdiv((uint32_t)row_base, div_low);
-      if (q != have) {
-        have = q;
-        decode_packed(q * n_low, sp, lo0, hi0);
-        const uint64_t next = (uint64_t)(q + 1) * n_low;
+      const uint32_t q = fastdiv((uint32_t)row_base, div_low), h = kMid ? fastdiv(q, div_mid) : q;
+      if (h != have) {
+        have = h;
+        decode_packed(h * n_both, sp, lo0, hi0);
+        const uint64_t next = (uint64_t)(h + 1) * n_both;
         if (next < n_raw) decode_packed((uint32_t)next, sp, lo1, hi1);
       }
       uint32_t r = (uint32_t)row_base - q * n_low + lane;
       const bool wrap = r >= n_low;
       if (wrap) r -= n_low;
       const bool in = wave_base + (uint64_t)row * kWave + lane < n_raw;
-      const ulonglong2 d = low[in ? r : 0u];
-      lo[row] = d.x | (wrap ? lo1 : lo0);
-      hi[row] = d.y | (wrap ? hi1 : hi0);
+      ulonglong2 d = low[in ? r : 0u];
+      bool over = wrap; // past the value of lo0, hi0
+      if (kMid) {
+        const uint32_t m = q - h * n_mid + (wrap ? 1u : 0u);
+        over = m >= n_mid;
+        const ulonglong2 e = mid[over ? 0u : m];
+        d.x |= e.x;
+        d.y |= e.y;
+      }
+      lo[row] = d.x | (over ? lo1 : lo0);
+      hi[row] = d.y | (over ? hi1 : hi0);
       ok[row] = in ? 1u : 0u;
     }
     for (uint32_t c = 0; c < n_cons; ++c) {
@@ -208,7 +227,7 @@ hipError_t launch_gather_idx(const uint32_t *d_idx, const uint32_t *d_pos, uint3
 }
 
 size_t enumeration_table_bytes() {
-  return kMaxLow * sizeof(ulonglong2) + CGS_MAX_CONSTRAINTS * kTruth * sizeof(uint32_t);
+  return (kMaxLow + kMaxMid) * sizeof(ulonglong2) + CGS_MAX_CONSTRAINTS * kTruth * sizeof(uint32_t);
 }
 
 uint32_t enumeration_tiles(uint32_t n_raw) {
@@ -226,17 +245,22 @@ hipError_t launch_enumeration(const SpaceDev &space, const SpaceDev *d_space, vo
   if (n_tiles == 0) return hipSuccess;
   if (phase == 0) {
     uint32_t n_low = 1; // 64 or more, or the whole space: no radix is above 16
-    for (int j = space.n_params - 1; j >= 0 && n_low * space.radix[j] <= kMaxLow; --j)
-      n_low *= space.radix[j];
+    int j = space.n_params - 1;
+    for (; j >= 0 && n_low * space.radix[j] <= kMaxLow; --j) n_low *= space.radix[j];
+    uint32_t n_mid = 1; // 17 or more, or what is left
+    for (; n_low < 512 && j >= 0 && n_mid * space.radix[j] <= kMaxMid; --j)
+      n_mid *= space.radix[j];
     const uint32_t n_cons = (uint32_t)space.n_cons;
     ulonglong2 *low = static_cast<ulonglong2 *>(d_tables);
-    uint32_t *truth = reinterpret_cast<uint32_t *>(low + kMaxLow);
-    enum_tables<<<n_cons + (n_low + kEnumThreads - 1) / kEnumThreads, kEnumThreads, 0, stream>>>(
-        d_space, n_low, truth, low);
-    const size_t lds = n_low * sizeof(ulonglong2) + n_cons * kTruth * sizeof(uint32_t);
+    uint32_t *truth = reinterpret_cast<uint32_t *>(low + kMaxLow + kMaxMid);
+    enum_tables<<<n_cons + (n_low + n_mid + kEnumThreads - 1) / kEnumThreads, kEnumThreads, 0,
+                  stream>>>(d_space, n_low, n_mid, truth, low);
+    const size_t lds = (n_low + n_mid) * sizeof(ulonglong2) + n_cons * kTruth * sizeof(uint32_t);
     // up to eight workgroups per CU; more tiles than that share the tables
-    enum_mark<<<std::min<uint32_t>(n_tiles, 2048), kEnumThreads, lds, stream>>>(
-        d_space, truth, low, n_low, make_fastdiv(n_low), n_tiles, d_mask, d_tile_count);
+    (n_mid > 1 ? enum_mark<true> : enum_mark<false>)<<<std::min<uint32_t>(n_tiles, 2048),
+                                                       kEnumThreads, lds, stream>>>(
+        d_space, truth, low, n_low, make_fastdiv(n_low), n_tiles, d_mask, d_tile_count, n_mid,
+        make_fastdiv(n_mid));
     hipLaunchKernelGGL(enum_scan, dim3(1), dim3(kScanThreads), 0, stream, d_tile_count, n_tiles,
                        d_tile_off, d_total);
   } else {

@@ -67,7 +67,7 @@ void publish(cgs::DrawResult *r, uint64_t seq) {
 
 void run(const std::string &k, void **args) {
   auto is = [&](const char *name) { return k.find(name) != std::string::npos; };
-  if (is("9enum_mark")) {
+  if (is("enum_mark")) {
     const auto *sp = arg<const cgs::SpaceDev *>(args, 0);
     auto *mask = arg<uint32_t *>(args, 6);
     auto *count = arg<uint32_t *>(args, 7);
