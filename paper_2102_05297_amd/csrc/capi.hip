@@ -1694,7 +1694,8 @@ struct AdamStep {
 hipError_t mlp_step_rows(cgs_model m, uint32_t k, uint32_t n, float *d_loss,
                          const AdamStep *adam) {
   hipStream_t st = m->space->stream;
-  const TrainRowsArgs a = train_rows_args(m, k, n, true);
+  TrainRowsArgs a = train_rows_args(m, k, n, true);
+  a.alone = adam == nullptr;
   hipError_t e = launch_mlp_train_rows(a, st);
   if (e != hipSuccess) return e;
   GradTilesArgs g{};

@@ -1180,7 +1180,9 @@ namespace {
 // 19.0 us at 16 rows, 33.0 -> 22.4 at 256, 40.0 -> 33.0 at 1,024, 49.3 -> 48.5
 // at 2,048 (128 workgroups unsplit), 67.2 -> 90.9 at 4,096.  H = 256, whose
 // layers are a quarter: 16.3 -> 15.6 at 256 rows, 20.7 -> 21.8 at 1,024; not
-// split.
+// split.  A step by itself (gradients alone) is not split either: with the
+// weights and the code out of the caches it gains nothing, and the second launch
+// costs 5 to 8 us (256 rows, 1 counter 160 -> 165 us a call).
 constexpr uint32_t kSplitRows = 1024;
 
 template <int H, int NB3>
@@ -1188,7 +1190,7 @@ hipError_t launch_train_rows_h(const TrainRowsArgs &a, hipStream_t stream) {
   using TS = TrainShape<H, NB3>;
   static_assert(TS::lds <= 64 * 1024, "static launch size");
   if constexpr (H == 512) {
-    if (a.train && a.n_pad <= kSplitRows) {
+    if (a.train && !a.alone && a.n_pad <= kSplitRows) {
       const dim3 grid(a.n_pad / 16, H / (16 * kSplitWaves));
       mlp_split_forward<H, NB3><<<grid, kSplitThreads, 0, stream>>>(a);
       mlp_split_backward<H, NB3><<<grid, kSplitThreads, 0, stream>>>(a);

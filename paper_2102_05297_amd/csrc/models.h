@@ -45,6 +45,7 @@ struct TrainRowsArgs {
   const __bf16 *xin;        // the step's features [n_pad][K1] (launch_mlp_gather_rows)
   const float *tin;         // the step's targets [n][C], or null (forward only)
   bool train;               // tin set
+  bool alone;               // a step by itself, not one of a run
   uint32_t n, n_pad;        // rows; a multiple of 32 >= n
   int H, C, K1;
   float scale;              // 2 / (n C)
