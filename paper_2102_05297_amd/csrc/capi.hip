@@ -613,42 +613,67 @@ MlpFwdArgs mlp_args(cgs_model m) {
   return a;
 }
 
-// Uploads a model's values x[0..n) to a new block *d and checks them there
-// (finite; with nonneg, not negative).  It comes first of what a model needs
-// and is waited for, so that a bad value, `what` with its position, is
-// refused before the predictions are allocated or anything is evaluated.  The
-// host looks through the values where they are few (16,384 take it 12 us, the
-// device's check and its wait 25 to 30: a table of 24 x 64 values loads in 44 ->
-// 23 us) and where they do not fit on the device.
-cgs_status upload_checked(float **d, const float *x, uint64_t n, bool nonneg, const char *what,
-                          hipStream_t stream) {
-  constexpr uint64_t kHostValues = 1u << 14;
-  uint64_t *d_first = nullptr, first = kNoPick;
-  auto look = [&]() {
+// A model's values on their way to the device, checked (finite; with nonneg,
+// not negative): begin() uploads them to a new block and enqueues the check,
+// finish() waits for it.  Between the two the model's other buffers are made, so
+// that a bad value, `what` with its position, is refused before anything is
+// evaluated, also where those buffers do not fit.  The host looks through the
+// values where they are few (16,384 take it 12 us, the device's check and its
+// wait 25 to 30: a table of 24 x 64 values loads in 44 -> 23 us) and where they do
+// not fit on the device.
+struct ValueCheck {
+  static constexpr uint64_t kHostValues = 1u << 14;
+  const float *x;
+  uint64_t n;
+  bool nonneg;
+  const char *what;
+  hipStream_t stream;
+  uint64_t *d_first = nullptr, *h_first = nullptr;
+  uint64_t first = kNoPick;
+  ~ValueCheck() {
+    if (d_first || h_first) (void)hipStreamSynchronize(stream);
+    dfree(d_first);
+    pfree(h_first);
+  }
+  void look() {
     for (uint64_t i = 0; first == kNoPick && i < n; ++i)
       if (!std::isfinite(x[i]) || (nonneg && x[i] < 0.0f)) first = i;
-  };
-  const bool few = n <= kHostValues;
-  if (few) look();
-  hipError_t e = first == kNoPick ? dalloc(d, n) : hipSuccess;
-  if (e == hipSuccess && first == kNoPick && !few) e = dalloc(&d_first, 1);
-  if (e == hipSuccess && first == kNoPick)
-    e = hipMemcpyAsync(*d, x, n * sizeof(float), hipMemcpyHostToDevice, stream);
-  if (e == hipSuccess && !few) {
-    e = launch_check_floats(*d, n, nonneg, d_first, stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(&first, d_first, sizeof(uint64_t), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
   }
-  settle(e, stream);
-  dfree(d_first);
-  if (e == hipErrorOutOfMemory) look();
-  if (first != kNoPick) return fail(CGS_EINVAL, what, (unsigned long long)first);
-  if (e != hipSuccess)
-    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
-                hipGetErrorString(e));
-  return CGS_OK;
-}
+  hipError_t begin(float **d) {
+    const bool few = n <= kHostValues;
+    if (few) look();
+    if (first != kNoPick) return hipErrorInvalidValue;
+    hipError_t e = dalloc(d, n);
+    if (e == hipSuccess && !few) e = dalloc(&d_first, 1);
+    if (e == hipSuccess && !few) e = palloc(&h_first, (uint64_t **)nullptr, 1);
+    if (e == hipSuccess) e = hipMemcpyAsync(*d, x, n * sizeof(float), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess && !few) {
+      *h_first = kNoPick;
+      e = launch_check_floats(*d, n, nonneg, d_first, stream);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(h_first, d_first, sizeof(uint64_t), hipMemcpyDeviceToHost, stream);
+    }
+    return e;
+  }
+  // e: the first error since begin()
+  cgs_status finish(hipError_t e) {
+    if (h_first) {
+      const hipError_t w = hipStreamSynchronize(stream);
+      if (w == hipSuccess) {
+        first = *h_first;
+        dfree(d_first);
+        pfree(h_first);
+      }
+      if (e == hipSuccess) e = w;
+    }
+    if (e == hipErrorOutOfMemory) look();
+    if (first != kNoPick) return fail(CGS_EINVAL, what, (unsigned long long)first);
+    if (e != hipSuccess)
+      return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
+                  hipGetErrorString(e));
+    return CGS_OK;
+  }
+};
 
 cgs_status evaluate_model(cgs_model m) {
   cgs_space sp = m->space;
@@ -715,22 +740,20 @@ extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth
   m->n_trees = n_trees;
   m->depth = depth;
   m->stride = (sp->n_valid + 63) & ~(uint64_t)63;
-  cgs_status st = upload_checked(&m->d_leaves, leaves, n_leaf_vals, true,
-                                 "leaf value %llu is negative or not finite", sp->stream);
-  if (st != CGS_OK) {
-    destroy_model(m);
-    return st;
-  }
-  hipError_t e = dalloc(&m->d_nodes, nodes.size());
+  ValueCheck check{leaves, n_leaf_vals, true, "leaf value %llu is negative or not finite",
+                   sp->stream};
+  hipError_t e = check.begin(&m->d_leaves);
+  if (e == hipSuccess) e = dalloc(&m->d_nodes, nodes.size());
   if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
   if (e == hipSuccess && !nodes.empty())
     e = hipMemcpyAsync(m->d_nodes, nodes.data(), nodes.size() * sizeof(uint16_t),
                        hipMemcpyHostToDevice, sp->stream);
-  if (e == hipSuccess) e = clear_padding(m);
-  if (e != hipSuccess) {
+  cgs_status st = check.finish(e);
+  if (st == CGS_OK && (e = clear_padding(m)) != hipSuccess)
+    st = fail(CGS_EDEVICE, "model buffers: %s", hipGetErrorString(e));
+  if (st != CGS_OK) {
     destroy_model(m);
-    return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "model buffers: %s",
-                hipGetErrorString(e));
+    return st;
   }
   st = evaluate_model(m);
   if (st != CGS_OK) {
@@ -1260,15 +1283,18 @@ extern "C" cgs_status cgs_model_load_predictions(cgs_space sp, int n_counters,
   m->n_counters = n_counters;
   m->stride = (nv + 63) & ~(uint64_t)63;
   float *d_src = nullptr;
-  const cgs_status st = upload_checked(&d_src, pred_host, nv * (uint64_t)n_counters, true,
-                                       "prediction %llu is negative or not finite", sp->stream);
+  ValueCheck check{pred_host, nv * (uint64_t)n_counters, true,
+                   "prediction %llu is negative or not finite", sp->stream};
+  hipError_t e = check.begin(&d_src);
+  if (e == hipSuccess) e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
+  const cgs_status st = check.finish(e);
   if (st != CGS_OK) {
+    settle(hipErrorUnknown, sp->stream);
     dfree(d_src);
     destroy_model(m);
     return st;
   }
-  hipError_t e = dalloc(&m->d_P, (size_t)n_counters * m->stride);
-  if (e == hipSuccess) e = clear_padding(m);
+  e = clear_padding(m);
   if (e == hipSuccess)
     e = launch_rows_to_columns(d_src, (uint32_t)nv, n_counters, m->d_P, m->stride, sp->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sp->stream);
@@ -1795,12 +1821,9 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
     m->n_cu = prop.multiProcessorCount;
   hipStream_t st = sp->stream;
-  cgs_status stt = upload_checked(&m->d_theta, params, n, false, "parameter %llu not finite", st);
-  if (stt != CGS_OK) {
-    destroy_model(m);
-    return stt;
-  }
-  hipError_t e = dalloc(&m->d_m, n);
+  ValueCheck check{params, n, false, "parameter %llu not finite", st};
+  hipError_t e = check.begin(&m->d_theta);
+  if (e == hipSuccess) e = dalloc(&m->d_m, n);
   if (e == hipSuccess) e = dalloc(&m->d_v, n);
   if (e == hipSuccess) e = dalloc(&m->d_grad, n);
   if (e == hipSuccess) e = dalloc(&m->d_w1p, m->n_w1p);
@@ -1821,6 +1844,11 @@ extern "C" cgs_status cgs_model_load_mlp(cgs_space sp, const cgs_mlp_desc *desc,
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3t, 0, m->n_w3p * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w1n, 0, H * 32 * sizeof(__bf16), st);
   if (e == hipSuccess) e = hipMemsetAsync(m->d_w3n, 0, m->n_w3p * sizeof(__bf16), st);
+  cgs_status stt = check.finish(e);
+  if (stt != CGS_OK) {
+    destroy_model(m);
+    return stt;
+  }
   if (e == hipSuccess) e = clear_padding(m);
   if (e == hipSuccess)
     e = launch_pack_weights(m->sh, m->d_theta, n, mlp_copies(m), st);
