@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -24,17 +25,19 @@ using namespace cgs;
 // ------------------------------------------------------------------ errors
 namespace {
 
-thread_local std::string g_error;
+thread_local char g_error[512];
 
 cgs_status fail(cgs_status st, const char *fmt, ...) {
-  char buf[512];
   va_list ap;
   va_start(ap, fmt);
-  vsnprintf(buf, sizeof(buf), fmt, ap);
+  vsnprintf(g_error, sizeof(g_error), fmt, ap);
   va_end(ap);
-  g_error = buf;
   return st;
 }
+
+// What an entry point returns where the host's own vectors do not fit: no
+// exception leaves the library.
+cgs_status no_host_memory() { return fail(CGS_ENOMEM, "host allocation"); }
 
 #define HIP_TRY(expr)                                                                         \
   do {                                                                                        \
@@ -281,7 +284,7 @@ struct cgs_session_s {
 };
 
 // ------------------------------------------------------------------ misc
-extern "C" const char *cgs_last_error(void) { return g_error.c_str(); }
+extern "C" const char *cgs_last_error(void) { return g_error; }
 extern "C" int cgs_version(void) { return kVersion; }
 
 extern "C" void cgs_release_memory(void) { pool::release(); }
@@ -712,7 +715,7 @@ cgs_status evaluate_model(cgs_model m) {
 
 extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth, int n_counters,
                                             const uint8_t *feat, const uint8_t *thr,
-                                            const float *leaves, cgs_model *out) {
+                                            const float *leaves, cgs_model *out) try {
   if (!out) return fail(CGS_EINVAL, "NULL out");
   *out = nullptr;
   if (!sp || !leaves || (depth > 0 && (!feat || !thr))) return fail(CGS_EINVAL, "NULL argument");
@@ -762,6 +765,8 @@ extern "C" cgs_status cgs_model_load_forest(cgs_space sp, int n_trees, int depth
   }
   *out = m;
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_model_fit_tree(cgs_space sp, uint64_t n, int n_counters,
@@ -1027,7 +1032,7 @@ void poly_nest(const cgs_space_s *sp, const PolyDev &pd, PolyNest &n) {
 } // namespace
 
 extern "C" cgs_status cgs_poly_design(cgs_space sp, uint64_t capacity, uint32_t *valid_idx,
-                                      uint64_t *count) {
+                                      uint64_t *count) try {
   if (!sp || !count || (capacity && !valid_idx)) return fail(CGS_EINVAL, "NULL argument");
   *count = 0;
   const uint32_t nv = (uint32_t)sp->n_valid;
@@ -1073,11 +1078,13 @@ extern "C" cgs_status cgs_poly_design(cgs_space sp, uint64_t capacity, uint32_t 
     return fail(CGS_ERANGE, "the design has %llu configurations, capacity %llu",
                 (unsigned long long)n, (unsigned long long)capacity);
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counters,
                                          const uint32_t *points, const float *targets, int order,
-                                         cgs_model *out, cgs_poly_fit_report *report) {
+                                         cgs_model *out, cgs_poly_fit_report *report) try {
   if (!out) return fail(CGS_EINVAL, "NULL out");
   *out = nullptr;
   if (!sp || !points || !targets) return fail(CGS_EINVAL, "NULL argument");
@@ -1246,6 +1253,8 @@ extern "C" cgs_status cgs_model_fit_poly(cgs_space sp, uint64_t n, int n_counter
   }
   *out = m;
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_poly_shape(cgs_model m, int *n_subspaces, int *n_terms) {
@@ -1473,7 +1482,7 @@ extern "C" cgs_status cgs_model_forest_shape(cgs_model m, int *n_trees, int *dep
 }
 
 extern "C" cgs_status cgs_model_copy_forest(cgs_model m, uint8_t *feat, uint8_t *thr,
-                                            float *leaves) {
+                                            float *leaves) try {
   if (!m) return fail(CGS_EINVAL, "NULL model");
   if (m->kind != 0) return fail(CGS_EINVAL, "not a forest model");
   const size_t n_int = (size_t)m->n_trees * (((size_t)1 << m->depth) - 1);
@@ -1492,6 +1501,8 @@ extern "C" cgs_status cgs_model_copy_forest(cgs_model m, uint8_t *feat, uint8_t 
     thr[i] = (uint8_t)(nodes[i] >> 8);
   }
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_model_info(cgs_model m, int *n_counters, float *eval_ms) {
@@ -1507,7 +1518,7 @@ extern "C" cgs_status cgs_model_refresh(cgs_model m) {
 }
 
 extern "C" cgs_status cgs_model_copy_predictions(cgs_model m, uint64_t first, uint64_t count,
-                                                 float *dst) {
+                                                 float *dst) try {
   if (!m || (!dst && count)) return fail(CGS_EINVAL, "NULL argument");
   cgs_space sp = m->space;
   if (first > sp->n_valid || count > sp->n_valid - first)
@@ -1522,6 +1533,8 @@ extern "C" cgs_status cgs_model_copy_predictions(cgs_model m, uint64_t first, ui
     for (int c = 0; c < m->n_counters; ++c)
       dst[i * m->n_counters + c] = rows[(size_t)c * count + i];
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_model_gather_predictions(cgs_model m, const uint32_t *idx, uint64_t n,
@@ -1558,7 +1571,7 @@ extern "C" cgs_status cgs_model_gather_predictions(cgs_model m, const uint32_t *
 }
 
 extern "C" cgs_status cgs_model_rmse(cgs_model a, cgs_model b, const uint32_t *sample,
-                                     uint64_t n, double *rmse) {
+                                     uint64_t n, double *rmse) try {
   if (!a || !b || !rmse || (!sample && n)) return fail(CGS_EINVAL, "NULL argument");
   if (a->space != b->space) return fail(CGS_EINVAL, "models predict different spaces");
   if (a->n_counters != b->n_counters) return fail(CGS_EINVAL, "models differ in counters");
@@ -1590,6 +1603,8 @@ extern "C" cgs_status cgs_model_rmse(cgs_model a, cgs_model b, const uint32_t *s
   for (double v : part) sum += v;
   *rmse = std::sqrt(sum / ((double)n * a->n_counters));
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_model_copy_leaf_ids(cgs_model m, uint64_t first, uint64_t count,
@@ -1927,12 +1942,14 @@ cgs_status mlp_train_run(cgs_model m, const uint32_t *cfg, const float *targets,
 
 extern "C" cgs_status cgs_mlp_train(cgs_model m, const uint32_t *cfg, const float *targets,
                                     uint64_t n, const int32_t *batch_idx,
-                                    const cgs_train_opts *o, float *loss_host) {
+                                    const cgs_train_opts *o, float *loss_host) try {
   return mlp_train_run(m, cfg, targets, n, batch_idx, o, loss_host, true);
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_mlp_gradients(cgs_model m, const uint32_t *cfg, const float *targets,
-                                        uint32_t n, float *grads, float *loss_host) {
+                                        uint32_t n, float *grads, float *loss_host) try {
   if (!m || !cfg || !targets || !grads) return fail(CGS_EINVAL, "NULL argument");
   if (m->kind != 1) return fail(CGS_EINVAL, "not a perceptron model");
   if (n < 1 || n > 4096) return fail(CGS_ERANGE, "n must be 1..4096");
@@ -1958,9 +1975,11 @@ extern "C" cgs_status cgs_mlp_gradients(cgs_model m, const uint32_t *cfg, const 
   if (e != hipSuccess) return fail(CGS_EDEVICE, "gradients: %s", hipGetErrorString(e));
   if (loss_host) *loss_host = loss;
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
-extern "C" cgs_status cgs_mlp_forward(cgs_model m, const uint32_t *cfg, uint32_t n, float *y) {
+extern "C" cgs_status cgs_mlp_forward(cgs_model m, const uint32_t *cfg, uint32_t n, float *y) try {
   if (!m || !cfg || !y) return fail(CGS_EINVAL, "NULL argument");
   if (m->kind != 1) return fail(CGS_EINVAL, "not a perceptron model");
   if (n < 1 || n > 4096) return fail(CGS_ERANGE, "n must be 1..4096");
@@ -1983,6 +2002,8 @@ extern "C" cgs_status cgs_mlp_forward(cgs_model m, const uint32_t *cfg, uint32_t
   for (uint32_t i = 0; i < n; ++i)
     for (int c = 0; c < m->sh.C; ++c) y[(size_t)i * m->sh.C + c] = rows[(size_t)i * Cp + c];
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_mlp_copy_params(cgs_model m, float *dst, uint64_t n) {
@@ -2303,7 +2324,7 @@ extern "C" cgs_status cgs_session_kernel_times(cgs_session s, double *total_ms, 
   return CGS_OK;
 }
 
-extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params, cgs_session *out) {
+extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params, cgs_session *out) try {
   if (!out) return fail(CGS_EINVAL, "NULL out");
   *out = nullptr;
   if (!sp) return fail(CGS_EINVAL, "NULL space");
@@ -2318,15 +2339,14 @@ extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params,
     return fail(CGS_ERANGE, "block_log2 must be 0 or 12..20");
   cgs_session s = new (std::nothrow) cgs_session_s();
   if (!s) return fail(CGS_ENOMEM, "host allocation");
+  std::unique_ptr<cgs_session_s, void (*)(cgs_session)> hold(s, destroy_session);
   s->space = sp;
   ++sp->refs;
   s->params = p;
   s->block_log2 = p.block_log2 ? p.block_log2 : auto_block_log2(sp->n_valid);
   s->n_blocks = (uint32_t)((sp->n_valid + (1ull << s->block_log2) - 1) >> s->block_log2);
-  if (s->n_blocks > (1u << 20)) {
-    destroy_session(s);
+  if (s->n_blocks > (1u << 20))
     return fail(CGS_ERANGE, "too many weight blocks; raise block_log2");
-  }
   const uint64_t stride = (sp->n_valid + 63) & ~(uint64_t)63;
   const uint64_t n_words = (sp->n_valid + 31) / 32;
   hipError_t e = dalloc(&s->d_explored, n_words);
@@ -2355,13 +2375,13 @@ extern "C" cgs_status cgs_session_create(cgs_space sp, const cgs_params *params,
   if (e == hipSuccess)
     e = launch_session_init(s->d_explored, std::max<uint64_t>(n_words, 1), s->d_s, stride, s->d_acc,
                             2 * kAccSlots, sp->stream);
-  if (e != hipSuccess) {
-    destroy_session(s);
+  if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "session buffers: %s",
                 hipGetErrorString(e));
-  }
-  *out = s;
+  *out = hold.release();
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 namespace {
@@ -2518,7 +2538,7 @@ extern "C" cgs_status cgs_search_step(cgs_session s, cgs_model m, uint64_t profi
 extern "C" cgs_status cgs_search_run(cgs_session s, cgs_model m, int n_steps,
                                      const double *measured, const cgs_expert_params *expert,
                                      const uint64_t *u64, uint64_t *raw_out, uint64_t *valid_out,
-                                     double *step_us) {
+                                     double *step_us) try {
   if (!s || !m || !u64 || !raw_out || (n_steps > 0 && (!measured || !expert)))
     return fail(CGS_EINVAL, "NULL argument");
   if (n_steps < 0) return fail(CGS_EINVAL, "negative n_steps");
@@ -2581,6 +2601,8 @@ extern "C" cgs_status cgs_search_run(cgs_session s, cgs_model m, int n_steps,
     t_prev = t;
   }
   return finish(CGS_OK);
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" void cgs_default_online_opts(cgs_online_opts *o) {
@@ -2660,7 +2682,7 @@ extern "C" cgs_status cgs_online_run(cgs_session s, cgs_model tree, cgs_model ml
                                      const uint32_t *val_sample, const uint64_t *batch_u64,
                                      const cgs_online_opts *opts, uint64_t *raw_out,
                                      uint64_t *valid_out, double *window_rmse,
-                                     int32_t *window_mlp, double *step_us, double *retrain_ms) {
+                                     int32_t *window_mlp, double *step_us, double *retrain_ms) try {
   if (!s || !tree || !mlp || !u64 || !noise || !val_sample || !opts || !raw_out ||
       !window_rmse || !window_mlp || (n_seed && (!seed_cfg || !seed_targets)))
     return fail(CGS_EINVAL, "NULL argument");
@@ -2781,12 +2803,18 @@ extern "C" cgs_status cgs_online_run(cgs_session s, cgs_model tree, cgs_model ml
     fresh_step.push_back(i);
   }
   return done(CGS_OK);
+} catch (const std::bad_alloc &) {
+  if (mlp && mlp->p_stale) { // the predictions follow the parameters outside this call
+    mlp->p_stale = false;
+    (void)evaluate_model(mlp);
+  }
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_search_step_neighbourhood(cgs_session s, cgs_model m,
                                                     uint64_t profile_raw, int radius,
                                                     const float *delta, const double *measured,
-                                                    const cgs_expert_params *expert) {
+                                                    const cgs_expert_params *expert) try {
   if (!s || !m) return fail(CGS_EINVAL, "NULL session or model");
   cgs_space sp = s->space;
   if (m->space != sp) return fail(CGS_EINVAL, "model and session belong to different spaces");
@@ -2832,6 +2860,8 @@ extern "C" cgs_status cgs_search_step_neighbourhood(cgs_session s, cgs_model m,
   s->n_active = act.n;
   s->last_total = 0;
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_session_copy_neighbourhood(cgs_session s, uint64_t capacity,
@@ -3168,7 +3198,7 @@ std::string batch_key(cgs_batch b) {
 } // namespace
 
 extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const cgs_model *models,
-                                       const cgs_batch_schedule *sched, cgs_batch *out) {
+                                       const cgs_batch_schedule *sched, cgs_batch *out) try {
   if (!out) return fail(CGS_EINVAL, "NULL out");
   *out = nullptr;
   if (n < 1 || n > 65535 || !sessions || !models) return fail(CGS_EINVAL, "need 1..65535 sessions");
@@ -3219,8 +3249,10 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     if (i == 0 || rows[i].first != rows[i - 1].first) row_bytes += rows[i].second;
   if (tiles > 0xffffffffull || blocks > 0xffffffffull)
     return fail(CGS_ERANGE, "batch too large");
+  std::vector<uint16_t> tile_sess(std::max<uint64_t>(tiles, 1)), blk_sess(std::max<uint64_t>(blocks, 1));
   cgs_batch b = new (std::nothrow) cgs_batch_s();
   if (!b) return fail(CGS_ENOMEM, "host allocation");
+  std::unique_ptr<cgs_batch_s, void (*)(cgs_batch)> hold(b, destroy_batch);
   b->n = n;
   b->sess.assign(sessions, sessions + n);
   b->models.assign(models, models + n);
@@ -3233,7 +3265,6 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
   b->small = small;
   b->max_tiles = max_tiles;
   b->max_per = max_per;
-  std::vector<uint16_t> tile_sess(std::max<uint64_t>(tiles, 1)), blk_sess(std::max<uint64_t>(blocks, 1));
   for (int i = 0; i < n; ++i) {
     const uint32_t nt = (desc[i].n_valid + kBatchTile - 1) / kBatchTile;
     for (uint32_t t = 0; t < nt; ++t) tile_sess[desc[i].tile0 + t] = (uint16_t)i;
@@ -3261,24 +3292,22 @@ extern "C" cgs_status cgs_batch_create(int n, const cgs_session *sessions, const
     e = hipMemcpyAsync(b->d_blk_sess, blk_sess.data(), blk_sess.size() * sizeof(uint16_t),
                        hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  if (e != hipSuccess) {
-    destroy_batch(b);
+  if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? CGS_ENOMEM : CGS_EDEVICE, "batch buffers: %s",
                 hipGetErrorString(e));
-  }
   b->sched = sched ? *sched : default_schedule(b);
   if (b->sched.score_grid < 1 || b->sched.weight_grid < 1 || b->sched.variant < 0 ||
-      b->sched.variant >= kBatchScoreVariants) {
-    destroy_batch(b);
+      b->sched.variant >= kBatchScoreVariants)
     return fail(CGS_EINVAL, "schedule: grids must be >= 1, variant 0..%d", kBatchScoreVariants - 1);
-  }
   if (b->sched.score_grid < 1 || b->sched.weight_grid < 1) {
     const cgs_batch_schedule d = default_schedule(b);
     if (b->sched.score_grid < 1) b->sched.score_grid = d.score_grid;
     if (b->sched.weight_grid < 1) b->sched.weight_grid = d.weight_grid;
   }
-  *out = b;
+  *out = hold.release();
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_batch_set_schedule(cgs_batch b, const cgs_batch_schedule *s) {
@@ -3365,7 +3394,7 @@ extern "C" cgs_status cgs_batch_step_time(cgs_batch b, float *ms) {
 }
 
 extern "C" cgs_status cgs_batch_autotune(cgs_batch b, const char *cache_path,
-                                         cgs_batch_schedule *chosen) {
+                                         cgs_batch_schedule *chosen) try {
   if (!b) return fail(CGS_EINVAL, "NULL batch");
   const std::string key = batch_key(b);
   if (cache_path) {
@@ -3509,6 +3538,8 @@ extern "C" cgs_status cgs_batch_autotune(cgs_batch b, const char *cache_path,
   }
   if (chosen) *chosen = best;
   return CGS_OK;
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" cgs_status cgs_batch_draw(cgs_batch b, const uint64_t *u64, uint64_t *raw_out,
@@ -3804,7 +3835,7 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
                                            const uint64_t *uniforms, uint64_t n_uniforms,
                                            const cgs_tuning_opts *opts, uint64_t capacity,
                                            uint64_t *tested, uint8_t *profiled,
-                                           uint64_t *n_tests, uint64_t *tests_to_well) {
+                                           uint64_t *n_tests, uint64_t *tests_to_well) try {
   if (!b || !runtime || !counters || !uniforms || !opts || !n_tests || !tests_to_well ||
       (capacity && !tested))
     return fail(CGS_EINVAL, "NULL argument");
@@ -3862,11 +3893,12 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
   // Once half of a batch's runs have ended, the live ones move to a new,
   // smaller batch (built from the same sessions and models) between
   // iterations, so finished runs stop costing score passes.
-  cgs_batch cur = b, own = nullptr;
+  cgs_batch cur = b;
+  std::unique_ptr<cgs_batch_s, void (*)(cgs_batch)> own(nullptr, destroy_batch);
   std::vector<int> map(n);
   for (int i = 0; i < n; ++i) map[i] = i;
   auto release = [&](cgs_status st) {
-    if (own) cgs_batch_destroy(own);
+    own.reset();
     if (st == CGS_OK) finish();
     return st;
   };
@@ -4064,12 +4096,14 @@ extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
       cgs_batch nb = nullptr;
       st = cgs_batch_create((int)ss.size(), ss.data(), ms.data(), nullptr, &nb);
       if (st != CGS_OK) return release(st);
-      if (own) cgs_batch_destroy(own);
-      own = cur = nb;
+      own.reset(nb);
+      cur = nb;
       map = keep;
     }
   }
   return release(CGS_OK);
+} catch (const std::bad_alloc &) {
+  return no_host_memory();
 }
 
 extern "C" void cgs_batch_destroy(cgs_batch b) { destroy_batch(b); }

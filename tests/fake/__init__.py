@@ -17,7 +17,7 @@ import ctypes
 fake = ctypes.CDLL({lib!r}, mode=ctypes.RTLD_GLOBAL)
 fake.fake_log.restype = ctypes.c_char_p
 fake.fake_used.restype = ctypes.c_size_t
-fake.fake_limit.argtypes = [ctypes.c_size_t]
+fake.fake_limit.argtypes = fake.fake_host_limit.argtypes = [ctypes.c_size_t]
 import numpy as np
 from paper_2102_05297_amd import cgs as m
 

@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <unordered_map>
 
@@ -29,6 +30,7 @@ std::unordered_map<const void *, int> g_lds;            // attribute of a kernel
 std::map<std::string, int> g_stream;                    // address -> number
 size_t g_used = 0, g_limit = (size_t)1 << 46;
 bool g_publish = true;
+size_t g_host_limit = SIZE_MAX;
 uint32_t g_every = 1;
 dim3 g_grid, g_block;
 size_t g_shared;
@@ -125,12 +127,23 @@ void run(const std::string &k, void **args) {
 
 } // namespace
 
+// the library's own (it binds to these before the C++ runtime's)
+void *operator new(size_t n) {
+  if (n > g_host_limit) throw std::bad_alloc();
+  void *p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 
 const char *fake_log() { return g_log.c_str(); }
 void fake_clear() { g_log.clear(); }
 void fake_limit(size_t bytes_left) { g_limit = g_used + bytes_left; }
 size_t fake_used() { return g_used; }
+void fake_host_limit(size_t bytes) { g_host_limit = bytes; } // larger host allocations fail
 void fake_publish(int on) { g_publish = on != 0; }
 void fake_every(unsigned n) { g_every = n; }
 
