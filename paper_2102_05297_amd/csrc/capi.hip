@@ -1618,7 +1618,8 @@ extern "C" cgs_status cgs_model_copy_leaf_ids(cgs_model m, uint64_t first, uint6
   uint16_t *d_out = nullptr;
   HIP_TRY(dalloc(&d_out, (size_t)m->n_trees * count));
   hipError_t e = launch_forest_eval(sp->d_desc, sp->d_idx, (uint32_t)sp->n_valid, m->d_nodes,
-                                    m->d_leaves, m->n_trees, m->depth, m->n_counters, sp->n_bits(), m->d_P,
+                                    m->d_leaves, m->n_trees, m->depth, m->n_counters, sp->n_bits(),
+                                    m->d_P,
                                     m->stride, d_out, (uint32_t)first, (uint32_t)count, sp->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(dst, d_out, (size_t)m->n_trees * count * sizeof(uint16_t),
@@ -2123,8 +2124,6 @@ cgs_status wait_draw(cgs_session s, const DrawResult *res, uint64_t seq, Pick *p
   return CGS_OK;
 }
 
-// Enqueues the recorded step: score pass, weight pass, and either its first
-// draw (do_draw) or just the marking of its profiled configuration.
 // Enqueues the recorded neighbourhood step: candidate scoring, compaction and
 // weights, then either its first draw or the marking of its profile.
 hipError_t launch_pending_nb(cgs_session s, bool do_draw, uint64_t u64) {
@@ -3826,9 +3825,9 @@ cgs_status tune_on_device(cgs_batch b, const float *runtime, const double *count
 // Alg. 1 for every session of a batch at once.  Each run follows exactly the
 // steps of cgs_tuning_run with its own random numbers; the runs advance in
 // lockstep.  On small spaces an iteration is one launch and a run that has
-// ended rests (or all runs are one launch, tune_on_device); otherwise it is one batch step, then batched draws, and a run
-// that has ended keeps stepping with no profile while its results are
-// ignored.
+// ended rests (or all runs are one launch, tune_on_device); otherwise it is one
+// batch step, then batched draws, and a run that has ended keeps stepping with
+// no profile while its results are ignored.
 extern "C" cgs_status cgs_tuning_run_batch(cgs_batch b, const float *runtime,
                                            const double *counters,
                                            const cgs_expert_params *expert,

@@ -259,7 +259,7 @@ hipError_t launch_weight_pass(const float *d_s, const uint32_t *d_explored, uint
                               float gamma, float w_min, int block_log2, uint64_t *d_bsum,
                               uint32_t n_blocks, hipStream_t stream,
                               const uint32_t *d_prof = nullptr);
-// The draw stores its result, then `seq` with a system-scope release; with
+// The draw publishes its result under number `seq` (DrawResult); with
 // d_prof_out also the pick's valid index (kNoProfile without a pick).
 // Up to kMaxDrawSeries further draws of one step in one launch (draw_many).
 constexpr int kMaxDrawSeries = 33;

@@ -3,8 +3,9 @@
 // A program that opens one session, batch or model after another on a space
 // pays the driver for every buffer: on MI355X a hipHostMalloc takes 20 to 50
 // us, a hipHostFree 20 to 270 us, a hipMalloc and hipFree 15 to 40 us each
-// (more for large blocks), a stream 600 to 900 us.  Released blocks and
-// streams are therefore kept for the next handle.
+// (more for large blocks), a stream 50 us and 40 more to destroy (12 ms the
+// process's first).  Released blocks and streams are therefore kept for the next
+// handle.
 //
 //   - Bounded: at most kDeviceCap bytes of device memory per GPU, kPinnedCap
 //     bytes of pinned host memory and kStreamCap streams are kept.  A block that

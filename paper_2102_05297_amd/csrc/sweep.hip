@@ -669,7 +669,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_many(
 
 // ------------------------------------------------------------ small spaces
 // A whole step of a space of at most kSmallMaxValid configurations in one
-// launch: 256 configurations a workgroup are scored, and the workgroup that
+// launch: 512 configurations a workgroup are scored, and the workgroup that
 // finishes last weighs all of them, keeps the weights in LDS and makes the
 // step's draws.
 // Bound: latency.  As separate launches (score, weight, draw, further draws)
