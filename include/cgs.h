@@ -646,9 +646,10 @@ void cgs_batch_destroy(cgs_batch batch);
  * results ignored, until half of the batch has finished: the live runs then
  * continue in a new batch of their sessions and models (freed on return).
  * On spaces of up to 32,768 configurations (and up to 33 draws) an iteration
- * is one launch instead and a finished run rests, or, for many runs, all
- * iterations of all runs are one launch; a finished run's session may hold up to
- * draws - 1 explored configurations more than its tests, as after
+ * is one launch instead and a finished run rests, or, where that is expected to
+ * be faster (many runs, many draws) and its buffers fit on the device, all
+ * iterations of all runs are one launch; a finished run's session may hold up
+ * to draws - 1 explored configurations more than its tests, as after
  * cgs_tuning_run.
  *   tested_host[n][capacity], profiled_host[n][capacity] (may be NULL),
  *   n_tests[n], tests_to_well[n]   as for cgs_tuning_run, per run

@@ -684,10 +684,11 @@ __global__ __launch_bounds__(kDrawThreads) void draw_many(
 // weighing waiting on its own latencies (2.6 against 1.5 us on 7,616
 // configurations), with 1,024 every barrier of a draw costs more (0.62 to
 // 1.2 us a draw).
-// Measured on 7,616 configurations, 9 to 13 active counters: 8.9 us with one
-// draw and 11.6 us with five, against 16.5 and 31 us for the separate
-// launches; of the 8.9 us, 2.3 to the scores, 1.4 for the handoff, 3.3 to
-// load and weigh, 0.6 the draw, 0.5 to publish, 0.4 the block sums.
+// Measured on 7,616 configurations, 9 to 13 active counters: 10.1 us with one
+// draw and 12.4 us with five, against 16.5 and 31 us for the separate launches'
+// kernels alone; of one with a draw about a quarter to the scores, a sixth for
+// the handoff, three eighths to load and weigh, the rest the draw, its result and
+// the block sums.
 // kSmallMaxValid: one accumulator slot per workgroup, and the weights fit in
 // the last workgroup's LDS.  It is also where the two ways meet: steps
 // enqueued ahead take 10.5 against 16.7 us on 8,192 configurations, 12.9
